@@ -75,6 +75,10 @@ size_t gram_table_workspace(int32_t N, int32_t M, int L);
 int rho1_generic(int32_t N, int32_t M, const mc_tables *t, const double *C_d, double *rho1_d,
                  void *ws_d, size_t ws_bytes, mc_stream stream);
 
+// Launches the staging of the case-split constants into cf.
+void launch_prep_split(int32_t M, int adjoint, const double *g_d, const double *h_d, double2 *cf,
+                       hipStream_t s);
+
 // Validates (N, M) ranges; MC_OK or MC_EINVAL.
 int check_nm(int32_t N, int32_t M);
 // D = C(N+M-1, N) with overflow check; -1 on overflow.

@@ -9,13 +9,11 @@
 // from an empty orbital) and padding rows load through a range-checked
 // buffer resource and read as zero, so the inner loops have no branches on
 // row validity; only the tile-uniform pair mask branches.
-#include <mutex>
 #include <utility>
 
 #include "mc_apply.h"
 #include "mc_split.h"
 #include "mc_sparse.h"
-#include "mc_direct.h"
 #include "mc_gram.h"
 #include "mc_internal.h"
 
@@ -66,14 +64,6 @@ __global__ void k_prep(int M, int adjoint, const double2 *__restrict__ g,
     }
 }
 
-// Staged constants of the case-split apply (layout in mc_split.h).
-__global__ void k_prep_split(int M, int adjoint, const double2 *__restrict__ g,
-                             const double2 *__restrict__ h, double2 *__restrict__ cf)
-{
-    stage_split_constants(M, adjoint, g, h, cf, blockIdx.x * blockDim.x + threadIdx.x,
-                          gridDim.x * blockDim.x);
-}
-
 // H.C in the case-split form walking only the nonzero constants (lists
 // built by k_sparse_lists); reduced tables, MAP as in k_apply_split.
 template <int MT, typename OccT, bool BIGC, bool MAP>
@@ -108,20 +98,6 @@ void k_apply_split(int N, int64_t D, int64_t tiles, int64_t nblocks, int64_t cap
     const int64_t tile = xcd_block(blockIdx.x, nblocks) * 4 + wave_in_block();
     if (tile >= tiles) return;
     apply_tile_split<MT, OccT, BIGC, MAP>(tile, D, cap, sq, occ, t1, pmask, t2_off, t2r, cf, C, HC);
-}
-
-// H.C with no table (occupations and targets in closed form, mc_direct.h).
-template <int MT, bool BIGC>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MC_APPLY_WAVES)))
-void k_apply_direct(int N, int nbits, int64_t D, int64_t tiles, int64_t nblocks,
-                    const double2 *__restrict__ cf, const double2 *__restrict__ C,
-                    double2 *__restrict__ HC)
-{
-    extern __shared__ double sq[];
-    if constexpr (kLdsRoots<MT>) fill_sqrt_table(sq, N + 3);
-    const int64_t tile = xcd_block_as<kDirectRemap<MT>>(blockIdx.x, nblocks) * 4 + wave_in_block();
-    if (tile >= tiles) return;
-    apply_tile_direct<MT, BIGC>(tile, N, nbits, D, sq, cf, C, HC);
 }
 
 template <int MT, typename OccT, bool BIGC>
@@ -759,8 +735,7 @@ static int apply_common(int32_t N, int32_t M, const double *h_d, const double *g
         const size_t sqb = (size_t)(N + 3) * 8;
         if (sqb > 65536) return MC_EINVAL;
         double2 *cf = (double2 *)ws_d;
-        hipLaunchKernelGGL(k_prep_split, dim3(4), dim3(256), 0, s, M, adjoint,
-                           (const double2 *)g_d, (const double2 *)h_d, cf);
+        launch_prep_split(M, adjoint, g_d, h_d, cf, s);
         const int64_t nblocks = (t->tiles + 3) / 4;
         const bool big = D * 16 > (int64_t)0xFFFFFFFFu;
         bool launched = false;
@@ -876,8 +851,7 @@ int mc_apply_H_sparse(int32_t N, int32_t M, const double *h_d, const double *g_d
     hipStream_t s = (hipStream_t)stream;
     double2 *cf = (double2 *)ws_d;
     int32_t *sl = (int32_t *)(cf + split_total(M));
-    hipLaunchKernelGGL(k_prep_split, dim3(4), dim3(256), 0, s, M, 0, (const double2 *)g_d,
-                       (const double2 *)h_d, cf);
+    launch_prep_split(M, 0, g_d, h_d, cf, s);
     hipLaunchKernelGGL(k_sparse_lists, dim3(1), dim3(64), 0, s, M, (const double2 *)cf, sl);
     const int64_t nblocks = (t->tiles + 3) / 4;
     const bool big = D * 16 > (int64_t)0xFFFFFFFFu;
@@ -902,101 +876,6 @@ int mc_apply_H_sparse(int32_t N, int32_t M, const double *h_d, const double *g_d
 #undef MC_SPARSE_LAUNCH
     if (!launched) return MC_EINVAL;
     return launch_status();
-}
-
-// Scratch of mc_apply_H_direct_noalloc: the staged constants of the apply
-// live in this file-scope device array (one copy per GPU, held until the
-// process ends) instead of a caller workspace.  Host code never passes the
-// array's name to a kernel: its device address is looked up once per device
-// (with that device current) and kept per device.
-static __device__ __align__(256) unsigned char scratch[MC_NOALLOC_SCRATCH_BYTES];
-
-namespace {
-constexpr int kMaxDevices = 64;
-std::mutex g_scratch_mutex;
-void *g_scratch_ptr[kMaxDevices] = {};
-}  // namespace
-
-static int noalloc_scratch(void **out)
-{
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return set_hip_error(e);
-    if (dev < 0 || dev >= kMaxDevices) return MC_EINVAL;
-    std::lock_guard<std::mutex> lock(g_scratch_mutex);
-    if (!g_scratch_ptr[dev]) {
-        void *p = nullptr;
-        e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-        if (e != hipSuccess || !p) return set_hip_error(e != hipSuccess ? e : hipErrorUnknown);
-        g_scratch_ptr[dev] = p;
-    }
-    *out = g_scratch_ptr[dev];
-    return MC_OK;
-}
-
-static int apply_direct_common(int32_t N, int32_t M, const double *h_d, const double *g_d,
-                               const double *C_d, double *HC_d, void *ws_d, size_t ws_bytes,
-                               int adjoint, mc_stream stream)
-{
-    int st = check_nm(N, M);
-    if (st) return st;
-    if (M > 8) return MC_EINVAL;
-    const int64_t D = dim_checked(N, M);
-    if (D < 0 || D >= ((int64_t)1 << 31)) return MC_ERANGE;
-    if (!h_d || !g_d || !C_d || !HC_d || !ws_d) return MC_EINVAL;
-    if (overlaps(C_d, (size_t)D * 16, HC_d, (size_t)D * 16)) return MC_EINVAL;
-    size_t need = 0;
-    mc_workspace_size(N, M, MC_OP_APPLY, &need);
-    if (ws_bytes < need) return MC_ENOMEM;
-    const size_t sqb = (size_t)(N + 3) * 8;
-    if (M >= MC_LDS_ROOTS_FROM && sqb > 65536) return MC_EINVAL;
-    hipStream_t s = (hipStream_t)stream;
-    double2 *cf = (double2 *)ws_d;
-    hipLaunchKernelGGL(k_prep_split, dim3(4), dim3(256), 0, s, M, adjoint, (const double2 *)g_d,
-                       (const double2 *)h_d, cf);
-    const int64_t tiles = (D + kTile - 1) / kTile;
-    const int64_t nblocks = (tiles + 3) / 4;
-    const int nbits = bit_width(N);
-    const bool big = D * 16 > (int64_t)0xFFFFFFFFu;
-    MC_DISPATCH_M(M, if constexpr (MT > 0 && MT <= 8) {
-        if (big)
-            hipLaunchKernelGGL((k_apply_direct<MT, true>), dim3(nblocks), dim3(256),
-                               kLdsRoots<MT> ? sqb : 0, s, N, nbits, D, tiles, nblocks,
-                               (const double2 *)cf, (const double2 *)C_d, (double2 *)HC_d);
-        else
-            hipLaunchKernelGGL((k_apply_direct<MT, false>), dim3(nblocks), dim3(256),
-                               kLdsRoots<MT> ? sqb : 0, s, N, nbits, D, tiles, nblocks,
-                               (const double2 *)cf, (const double2 *)C_d, (double2 *)HC_d);
-    });
-    return launch_status();
-}
-
-int mc_apply_H_direct(int32_t N, int32_t M, const double *h_d, const double *g_d,
-                      const double *C_d, double *HC_d, void *ws_d, size_t ws_bytes,
-                      mc_stream stream)
-{
-    return apply_direct_common(N, M, h_d, g_d, C_d, HC_d, ws_d, ws_bytes, 0, stream);
-}
-
-int mc_apply_H_direct_noalloc(int32_t N, int32_t M, const double *h_d, const double *g_d,
-                              const double *C_d, double *HC_d, mc_stream stream)
-{
-    size_t need = 0;
-    int st = mc_workspace_size(N, M, MC_OP_APPLY, &need);
-    if (st) return st;
-    if (need > (size_t)MC_NOALLOC_SCRATCH_BYTES) return MC_ENOMEM;
-    void *ws = nullptr;
-    st = noalloc_scratch(&ws);
-    if (st) return st;
-    return apply_direct_common(N, M, h_d, g_d, C_d, HC_d, ws, MC_NOALLOC_SCRATCH_BYTES, 0,
-                               stream);
-}
-
-int mc_apply_H_direct_adjoint(int32_t N, int32_t M, const double *h_d, const double *g_d,
-                              const double *C_d, double *HC_d, void *ws_d, size_t ws_bytes,
-                              mc_stream stream)
-{
-    return apply_direct_common(N, M, h_d, g_d, C_d, HC_d, ws_d, ws_bytes, 1, stream);
 }
 
 int mc_is_hermitian(int32_t M, const double *h_d, const double *g_d, int32_t *flag_d,
