@@ -19,7 +19,7 @@
 
 #include "mc_apply.h"
 #include "mc_split.h"
-#include "mc_direct.h"
+#include "mc_block.h"
 #include "mc_internal.h"
 
 namespace mc {
@@ -40,18 +40,35 @@ struct BatchInst {
     const double2 *h, *g;
     double2 *hp, *gp;    // staged h' and G' (paper form) / gp: case-split constants
     int64_t hp_off, gp_off;  // the same, as offsets into the plan's coefficient region
+    int32_t *btab;           // tables of the four-row kernel (instances that take it)
 };
 
 // Pointers read from a descriptor are generic (flat loads); the staged
 // constants are therefore reached through the __restrict__ coefficient-region
 // kernel argument, which keeps their loads scalar.
 
-// Staged complex constants per instance, enough for either form.
-inline int64_t batch_coef_elems(int M)
+// An item whose descriptor holds sizes but no buffers runs table-free.
+static bool table_free(const mc_tables *t)
+{
+    return !t->binom_d && !t->occ_d && !t->t1_d && !t->pmask_d && !t->t2_off_d && !t->t2_d;
+}
+
+// Staged complex constants of an instance of M orbitals, enough for either
+// form, and with the tables of the four-row kernel behind them where a
+// table-free instance takes it (as mc_apply_H_direct would).
+inline int64_t batch_const_elems(int M)
 {
     const int64_t paper = (int64_t)npairs(M) * M * M + (int64_t)M * M;
     const int64_t split = split_total(M);
     return paper > split ? paper : split;
+}
+inline bool batch_block(const mc_tables *t)
+{
+    return table_free(t) && block_serves(t->N, t->M, t->dim);
+}
+inline int64_t batch_coef_elems(const mc_tables *t)
+{
+    return batch_const_elems(t->M) + (batch_block(t) ? (block_table_ints(t->N, t->M) + 3) / 4 : 0);
 }
 
 struct BatchChunk {
@@ -75,6 +92,7 @@ struct SoloLaunch {
     const uint64_t *pmask;
     const int64_t *t2_off;
     const int32_t *t2;
+    const int32_t *btab;   // set: the four-row kernel
 };
 
 }  // namespace mc
@@ -110,7 +128,14 @@ __global__ void k_batch_prep(const BatchInst *__restrict__ inst, uint32_t *__res
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kMaxGroups) counters[threadIdx.x] = 0;
     const BatchInst I = inst[blockIdx.y];
     const int M = I.M;
-    const int first = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
+    // the last block of an instance makes its tables, the others its constants
+    if (blockIdx.x + 1 == gridDim.x) {
+        __shared__ int sum[256];
+        if (I.btab) stage_block_tables(I.N, M, I.btab, sum);
+        return;
+    }
+    const int first = blockIdx.x * blockDim.x + threadIdx.x;
+    const int stride = (gridDim.x - 1) * blockDim.x;
     if (I.kind == kSplitMap || I.kind == kSplitChain || I.kind == kDirect) {
         stage_split_constants(M, 0, I.g, I.h, I.gp, first, stride);
         return;
@@ -372,12 +397,6 @@ struct PlanLayout {
     size_t inst, prefix, chunks, partials, sorted, pos, counters, coef, total;
 };
 
-// An item whose descriptor holds sizes but no buffers runs table-free.
-static bool table_free(const mc_tables *t)
-{
-    return !t->binom_d && !t->occ_d && !t->t1_d && !t->pmask_d && !t->t2_off_d && !t->t2_d;
-}
-
 static int plan_layout(int32_t count, const mc_batch_item *items, int64_t *nchunks_out,
                        int64_t *coef_elems_out, PlanLayout *L)
 {
@@ -385,9 +404,8 @@ static int plan_layout(int32_t count, const mc_batch_item *items, int64_t *nchun
     for (int i = 0; i < count; ++i) {
         const mc_tables *t = items[i].tables;
         if (!t) return MC_EINVAL;
-        const int M = t->M;
         nchunks += (t->dim + kChunk - 1) / kChunk;
-        coef += batch_coef_elems(M);
+        coef += batch_coef_elems(t);
     }
     L->inst = 0;
     L->prefix = align256(L->inst + sizeof(BatchInst) * count);
@@ -506,9 +524,12 @@ int mc_batch_create(int32_t count, const mc_batch_item *items, const mc_batch_sc
         I.hp = coef + cpos + (int64_t)npairs(t->M) * t->M * t->M;
         I.gp_off = cpos;
         I.hp_off = cpos + (int64_t)npairs(t->M) * t->M * t->M;
-        cpos += batch_coef_elems(t->M);
-        // a large instance gets a launch of its own; the rest join groups
-        if (solo_min > 0 && t->tiles >= solo_min) {
+        const bool block = batch_block(t);
+        I.btab = block ? (int32_t *)(coef + cpos + batch_const_elems(t->M)) : nullptr;
+        cpos += batch_coef_elems(t);
+        // a large instance, and one of the four-row kernel, gets a launch of
+        // its own; the rest join groups
+        if (block || (solo_min > 0 && t->tiles >= solo_min)) {
             SoloLaunch &L1 = b->solo[b->nsolo++];
             L1.j = j;
             L1.M = t->M;
@@ -524,6 +545,7 @@ int mc_batch_create(int32_t count, const mc_batch_item *items, const mc_batch_sc
             L1.pmask = I.pmask;
             L1.t2_off = I.t2_off;
             L1.t2 = I.t2;
+            L1.btab = I.btab;
             prefix[j] = 0;
             continue;
         }
@@ -623,10 +645,16 @@ int mc_batch_apply_H(const mc_batch *b, const double *C_d, double *HC_d, mc_stre
     if (!b || !C_d || !HC_d) return MC_EINVAL;
     if (overlaps(C_d, (size_t)b->total_len * 16, HC_d, (size_t)b->total_len * 16)) return MC_EINVAL;
     hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(k_batch_prep, dim3(4, b->count), dim3(256), 0, s, b->inst_d, b->counters_d);
+    hipLaunchKernelGGL(k_batch_prep, dim3(5, b->count), dim3(256), 0, s, b->inst_d, b->counters_d);
     for (int k = 0; k < b->nsolo; ++k) {
         const SoloLaunch &L1 = b->solo[k];
         const int M = L1.M;
+        if (L1.btab) {
+            const int st = apply_block_run(L1.N, M, L1.dim, b->coef_d + L1.gp_off, L1.btab,
+                                           C_d + 2 * L1.vec_off, HC_d + 2 * L1.vec_off, s);
+            if (st) return st;
+            continue;
+        }
         const int64_t nblocks = (L1.tiles + 3) / 4;
 #define MC_SOLO_LAUNCH(KIND)                                                                    \
     hipLaunchKernelGGL((k_batch_solo<MT, KIND>), dim3(nblocks), dim3(256), 0, s, L1.N,           \

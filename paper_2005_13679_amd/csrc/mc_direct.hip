@@ -88,6 +88,8 @@ static int apply_direct_common(int32_t N, int32_t M, const double *h_d, const do
     const size_t sqb = (size_t)(N + 3) * 8;
     if (M >= MC_LDS_ROOTS_FROM && sqb > 65536) return MC_EINVAL;
     hipStream_t s = (hipStream_t)stream;
+    if (block_serves(N, M, D))
+        return apply_block_launch(N, M, D, h_d, g_d, adjoint, C_d, HC_d, ws_d, s);
     double2 *cf = (double2 *)ws_d;
     launch_prep_split(M, adjoint, g_d, h_d, cf, s);
     const int64_t tiles = (D + kTile - 1) / kTile;

@@ -698,6 +698,7 @@ int mc_workspace_size(int32_t N, int32_t M, int32_t op, size_t *bytes)
         const int64_t paper = (P * M * M + M * M) * 16;
         const int64_t split = M <= 8 ? split_total(M) * 16 + kSlInts * 4 : 0;
         *bytes = (size_t)(paper > split ? paper : split);
+        if (block_serves(N, M, D) && block_workspace(N, M) > *bytes) *bytes = block_workspace(N, M);
         return MC_OK;
     }
     case MC_OP_RHO1:
