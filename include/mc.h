@@ -373,6 +373,7 @@ int mc_rho2_direct(int32_t N, int32_t M, const double *C_d, double *rho2_d, void
  * reduction in ws_d (mc_workspace_size(DOT) for n = D of (N, M), or any
  * ws of at least 16 * MC_DOT_BLOCKS + 16 bytes). */
 #define MC_DOT_BLOCKS 1024
+#define MC_REORTH_BLOCKS 1024  /* partial sums of mc_lanczos_reorth per basis vector */
 int mc_zdotc(int64_t n, const double *x_d, const double *y_d, double *out_d,
              void *ws_d, size_t ws_bytes, mc_stream stream);
 
@@ -504,6 +505,17 @@ int mc_zgemv_c(int32_t K, int64_t n, const double *V_d, int64_t ldv, const doubl
 /* w_d[i] -= sum_{k<K} V_d[k*ldv + i] c_d[k] (complex128), k in order. */
 int mc_zgemv_sub(int32_t K, int64_t n, const double *V_d, int64_t ldv, const double *c_d,
                  double *w_d, mc_stream stream);
+
+/* One Lanczos vector with full reorthogonalisation against the basis rows
+ * V_d[k*ldv ...], k < K (complex128): classical Gram-Schmidt twice on w_d
+ * (destroyed), beta = the norm left, out_d = what is left / beta (0 if beta =
+ * 0).  alpha_d (complex128, may be NULL) = <V_{K-1}|w_d> of the given w_d,
+ * beta_d (double); every sum in a fixed order.  out_d may be w_d, and neither
+ * may overlap V_d.  K, n >= 1.  ws_d: (K + 1) * (MC_REORTH_BLOCKS + 2) * 16
+ * bytes. */
+int mc_lanczos_reorth(int32_t K, int64_t n, const double *V_d, int64_t ldv, double *w_d,
+                      double *out_d, double *alpha_d, double *beta_d, void *ws_d,
+                      size_t ws_bytes, mc_stream stream);
 
 /* beta = ||w_d|| (fixed-order reduction), out_d = w_d / beta (0 if beta = 0);
  * beta is written to beta_d[0] (double, may be NULL).  out_d may equal w_d.

@@ -30,6 +30,7 @@ MC_MAX_M = 32
 MC_MAX_N = 65535
 MC_TILE = 64
 MC_DOT_BLOCKS = 1024
+MC_REORTH_BLOCKS = 1024
 
 MC_CONJ_A = 1
 MC_CONJ_X = 2
@@ -106,6 +107,8 @@ SIGNATURES = {
     "mc_zdotc": (ctypes.c_int, [c_i64, c_p, c_p, c_p, c_p, c_sz, c_p]),
     "mc_zgemv_c": (ctypes.c_int, [c_i32, c_i64, c_p, c_i64, c_p, c_p, c_p, c_sz, c_p]),
     "mc_zgemv_sub": (ctypes.c_int, [c_i32, c_i64, c_p, c_i64, c_p, c_p, c_p]),
+    "mc_lanczos_reorth": (ctypes.c_int, [c_i32, c_i64, c_p, c_i64, c_p, c_p, c_p, c_p, c_p, c_sz,
+                                         c_p]),
     "mc_normalize": (ctypes.c_int, [c_i64, c_p, c_p, c_p, c_p, c_sz, c_p]),
     "mc_tridiag_lowest": (ctypes.c_int, [c_i32, c_p, c_p, c_p]),
     "mc_zgemv_n": (ctypes.c_int, [c_i32, c_i64, c_p, c_i64, c_p, c_p, c_p]),

@@ -18,7 +18,7 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmc.so")
 
 SOURCES = ["mc_host.hip", "mc_tables.hip", "mc_ops.hip", "mc_direct.hip", "mc_block.hip", "mc_batch.hip",
-           "mc_gram_direct.hip", "mc_gram_tables.hip"]
+           "mc_krylov.hip", "mc_gram_direct.hip", "mc_gram_tables.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

@@ -42,10 +42,10 @@ def ground_state(h, g, tables, v0: torch.Tensor, max_iter: int = 300, tol: float
     api._require(v0, "v0", torch.complex128, dev, numel=D)
     V = torch.empty((cap + 1 if reorthogonalize else 2, D), dtype=torch.complex128, device=dev)
     w = torch.empty(D, dtype=torch.complex128, device=dev)
-    c = torch.empty(cap + 1, dtype=torch.complex128, device=dev)
-    alpha_d = torch.empty((), dtype=torch.complex128, device=dev)
-    beta_d = torch.empty((), dtype=torch.float64, device=dev)
-    ws_g = torch.empty(max(16, (cap + 1) * 64 * 16), dtype=torch.uint8, device=dev)
+    ab = torch.empty(4, dtype=torch.float64, device=dev)    # alpha (complex), beta
+    alpha_d, beta_d = torch.view_as_complex(ab[:2]), ab[2]
+    ws_g = torch.empty((cap + 1) * (L.MC_REORTH_BLOCKS + 2) * 16 if reorthogonalize else 16,
+                       dtype=torch.uint8, device=dev)
     ws_n = torch.empty((L.MC_DOT_BLOCKS + 2) * 16, dtype=torch.uint8, device=dev)
     lib = L.load()
     st = api._stream(dev)
@@ -62,25 +62,22 @@ def ground_state(h, g, tables, v0: torch.Tensor, max_iter: int = 300, tol: float
     for j in range(cap):
         cur = V[j] if reorthogonalize else V[j % 2]
         (api.apply_H_sparse if sparse else api.apply_H)(h, g, cur, tables, out=w)
-        api.zdotc(cur, w, out=alpha_d)
         if reorthogonalize:
-            for _ in range(2):   # classical Gram-Schmidt, twice
-                with torch.cuda.device(dev):
-                    L.check(lib.mc_zgemv_c(j + 1, D, P(V), D, P(w), P(c), P(ws_g), ws_g.numel(),
-                                           st), "mc_zgemv_c")
-                    L.check(lib.mc_zgemv_sub(j + 1, D, P(V), D, P(c), P(w), st), "mc_zgemv_sub")
-            nxt = V[j + 1]
+            # classical Gram-Schmidt twice, norm and scaling; alpha = <cur|w>
+            with torch.cuda.device(dev):
+                L.check(lib.mc_lanczos_reorth(j + 1, D, P(V), D, P(w), P(V[j + 1]), P(alpha_d),
+                                              P(beta_d), P(ws_g), ws_g.numel(), st),
+                        "mc_lanczos_reorth")
         else:
+            api.zdotc(cur, w, out=alpha_d)
             prev_v = V[(j + 1) % 2] if j > 0 else None
             with torch.cuda.device(dev):
                 L.check(lib.mc_lanczos_orth(D, P(w), P(cur),
                                             P(prev_v) if prev_v is not None else None,
                                             P(alpha_d), P(beta_d) if j > 0 else None, st),
                         "mc_lanczos_orth")
-            nxt = V[(j + 1) % 2]
-        normalize(w, nxt)
-        a = float(alpha_d.real.item())
-        b = float(beta_d.item())
+            normalize(w, V[(j + 1) % 2])
+        a, _, b, _ = ab.tolist()
         alphas.append(a)
         e0 = tridiag_lowest(alphas, betas)
         if prev is not None and abs(e0 - prev) <= tol * max(1.0, abs(e0)):

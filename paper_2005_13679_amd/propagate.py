@@ -8,11 +8,12 @@ The basis grows until the a-posteriori error estimate
 |C| beta_k |y_{k-1}| (the weight the next Krylov vector would receive) falls
 below ``tol`` or ``kmax`` is reached.
 
-Every vector operation runs in the library's kernels (mc_apply_H, mc_zdotc,
-mc_zgemv_c / mc_zgemv_sub, mc_normalize, mc_zgemv_n); the k x k exponential,
-the scaling by |C| and the error estimate are the library's host routine
+Every vector operation runs in the library's kernels (mc_apply_H,
+mc_lanczos_reorth, mc_normalize, mc_zgemv_n); the k x k exponential, the
+scaling by |C| and the error estimate are the library's host routine
 mc_sil_coefficients.  alpha and beta are read back after each Lanczos step
-for the stopping test.
+for the stopping test, and once at the end where the number of vectors is
+given (each read waits for the GPU).
 """
 
 from __future__ import annotations
@@ -71,11 +72,10 @@ class SILStepper:
         D, k = self.D, self.kmax
         self.V = torch.empty((k + 1, D), dtype=torch.complex128, device=self.dev)
         self.w = torch.empty(D, dtype=torch.complex128, device=self.dev)
-        self.c = torch.empty(k + 1, dtype=torch.complex128, device=self.dev)
-        self.alpha_d = torch.empty((), dtype=torch.complex128, device=self.dev)
-        self.beta_d = torch.empty((), dtype=torch.float64, device=self.dev)
-        self.ws_g = torch.empty(max(16, (k + 1) * 64 * 16), dtype=torch.uint8, device=self.dev)
-        self.ws_n = torch.empty((L.MC_DOT_BLOCKS + 2) * 16, dtype=torch.uint8, device=self.dev)
+        # per vector: alpha (complex), beta; the last row: beta = |C|
+        self.ab = torch.empty((k + 1, 4), dtype=torch.float64, device=self.dev)
+        self.ws = torch.empty((k + 1) * (L.MC_REORTH_BLOCKS + 2) * 16, dtype=torch.uint8,
+                              device=self.dev)
 
     def step(self, C: torch.Tensor, dt: float, tol: float = 1e-12, out: torch.Tensor | None = None,
              k: int | None = None):
@@ -91,29 +91,42 @@ class SILStepper:
         st = api._stream(dev)
         P = api._ptr
         cap = self.kmax if k is None else int(min(k, self.kmax))
-        V, w, c = self.V, self.w, self.c
+        V, w, ab, ws = self.V, self.w, self.ab, self.ws
         with torch.cuda.device(dev):
-            L.check(lib.mc_normalize(D, P(C), P(V[0]), P(self.beta_d), P(self.ws_n),
-                                     self.ws_n.numel(), st), "mc_normalize")
-        norm_c = float(self.beta_d.item())
-        if norm_c == 0.0:
+            L.check(lib.mc_normalize(D, P(C), P(V[0]), P(ab[self.kmax, 2:]), P(ws), ws.numel(), st),
+                    "mc_normalize")
+        if k is None and float(ab[self.kmax, 2].item()) == 0.0:
             out.copy_(C)
             return out, 0, 0.0
         alphas, betas = [], []
         coef, err, m = None, float("inf"), 0
-        for j in range(cap):
+
+        def vector(j):
             api.apply_H(self.h, self.g, V[j], self.t, out=w)
-            api.zdotc(V[j], w, out=self.alpha_d)
-            for _ in range(2):   # classical Gram-Schmidt, twice
-                with torch.cuda.device(dev):
-                    L.check(lib.mc_zgemv_c(j + 1, D, P(V), D, P(w), P(c), P(self.ws_g),
-                                           self.ws_g.numel(), st), "mc_zgemv_c")
-                    L.check(lib.mc_zgemv_sub(j + 1, D, P(V), D, P(c), P(w), st), "mc_zgemv_sub")
             with torch.cuda.device(dev):
-                L.check(lib.mc_normalize(D, P(w), P(V[j + 1]), P(self.beta_d), P(self.ws_n),
-                                         self.ws_n.numel(), st), "mc_normalize")
-            alphas.append(float(self.alpha_d.real.item()))
-            b = float(self.beta_d.item())
+                L.check(lib.mc_lanczos_reorth(j + 1, D, P(V), D, P(w), P(V[j + 1]), P(ab[j]),
+                                              P(ab[j, 2:]), P(ws), ws.numel(), st),
+                        "mc_lanczos_reorth")
+
+        def rows(j):
+            """(alpha, beta) of vectors up to j and |C|, from the device."""
+            got = ab.tolist()
+            return [(r[0], r[2]) for r in got[: j + 1]], got[self.kmax][2]
+
+        scalars, norm_c = [], 0.0
+        if k is not None:
+            for j in range(cap):
+                vector(j)
+            scalars, norm_c = rows(cap - 1)
+            if norm_c == 0.0:
+                out.copy_(C)
+                return out, 0, 0.0
+        for j in range(cap):
+            if k is None:
+                vector(j)
+                scalars, norm_c = rows(j)
+            a, b = scalars[j]
+            alphas.append(a)
             m = j + 1
             coef, err, invariant = sil_coefficients(alphas, betas, b, norm_c, dt)
             if invariant or (k is None and err < tol):
