@@ -30,7 +30,7 @@ enum BatchKind : int32_t { kPaperMap = 0, kPaperChain = 1, kSplitMap = 2, kSplit
 
 struct BatchInst {
     int32_t N, M;
-    int32_t kind, nbits;  // nbits: bit width of N (table-free kind)
+    int32_t kind, pad;
     int64_t dim, tiles, cap, vec_off;
     const uint8_t *occ;
     const int32_t *t1;
@@ -187,7 +187,7 @@ __device__ __forceinline__ void batch_tile(const BatchInst &I, int64_t tile, con
     else if constexpr (KIND == kPaperChain)
         apply_tile_chained<MT, uint8_t, false>(tile, I.dim, sq, occ, t1, hp, gp, C, HC);
     else if constexpr (KIND == kDirect)
-        apply_tile_direct<MT, false>(tile, I.N, I.nbits, I.dim, sq, gp, C, HC);
+        apply_tile_direct<MT, false>(tile, I.N, I.dim, sq, gp, C, HC);
     else
         apply_tile_split<MT, uint8_t, false, KIND == kSplitMap>(tile, I.dim, I.cap, sq, occ, t1,
                                                                 pmask, t2_off, t2, gp, C, HC);
@@ -263,7 +263,7 @@ void k_batch_apply(const BatchInst *__restrict__ inst, const int64_t *__restrict
 // instance's vector segments arrive as kernel arguments.
 template <int MT, int KIND>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MC_APPLY_WAVES)))
-void k_batch_solo(int N, int nbits, int64_t D, int64_t tiles, int64_t nblocks, int64_t cap,
+void k_batch_solo(int N, int64_t D, int64_t tiles, int64_t nblocks, int64_t cap,
                   const uint8_t *__restrict__ occ, const int32_t *__restrict__ t1,
                   const uint64_t *__restrict__ pmask, const int64_t *__restrict__ t2_off,
                   const int32_t *__restrict__ t2, const double2 *__restrict__ gp,
@@ -282,7 +282,7 @@ void k_batch_solo(int N, int nbits, int64_t D, int64_t tiles, int64_t nblocks, i
     else if constexpr (KIND == kPaperChain)
         apply_tile_chained<MT, uint8_t, false>(tile, D, sq, occ, t1, hp, gp, C, HC);
     else if constexpr (KIND == kDirect)
-        apply_tile_direct<MT, false>(tile, N, nbits, D, sq, gp, C, HC);
+        apply_tile_direct<MT, false>(tile, N, D, sq, gp, C, HC);
     else
         apply_tile_split<MT, uint8_t, false, KIND == kSplitMap>(tile, D, cap, sq, occ, t1, pmask,
                                                                 t2_off, t2, gp, C, HC);
@@ -508,7 +508,7 @@ int mc_batch_create(int32_t count, const mc_batch_item *items, const mc_batch_sc
         I.N = t->N;
         I.M = t->M;
         I.kind = kind_of(t);
-        I.nbits = bit_width(t->N);
+        I.pad = 0;
         I.dim = t->dim;
         I.tiles = t->tiles;
         I.cap = t->t2_d ? t->t2_entries : 0;
@@ -657,8 +657,7 @@ int mc_batch_apply_H(const mc_batch *b, const double *C_d, double *HC_d, mc_stre
         }
         const int64_t nblocks = (L1.tiles + 3) / 4;
 #define MC_SOLO_LAUNCH(KIND)                                                                    \
-    hipLaunchKernelGGL((k_batch_solo<MT, KIND>), dim3(nblocks), dim3(256), 0, s, L1.N,           \
-                       bit_width(L1.N), L1.dim,                                                  \
+    hipLaunchKernelGGL((k_batch_solo<MT, KIND>), dim3(nblocks), dim3(256), 0, s, L1.N, L1.dim,      \
                        L1.tiles, nblocks, L1.cap, L1.occ, L1.t1, L1.pmask, L1.t2_off, L1.t2,     \
                        (const double2 *)b->coef_d + L1.gp_off,                                   \
                        (const double2 *)b->coef_d + L1.hp_off,                                   \

@@ -24,7 +24,7 @@ void launch_prep_split(int32_t M, int adjoint, const double *g_d, const double *
 // H.C with no table (occupations and targets in closed form, mc_direct.h).
 template <int MT, bool BIGC>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MC_APPLY_WAVES)))
-void k_apply_direct(int N, int nbits, int64_t D, int64_t tiles, int64_t nblocks,
+void k_apply_direct(int N, int64_t D, int64_t tiles, int64_t nblocks,
                     const double2 *__restrict__ cf, const double2 *__restrict__ C,
                     double2 *__restrict__ HC)
 {
@@ -32,7 +32,7 @@ void k_apply_direct(int N, int nbits, int64_t D, int64_t tiles, int64_t nblocks,
     if constexpr (kLdsRoots<MT>) fill_sqrt_table(sq, N + 3);
     const int64_t tile = xcd_block_as<kDirectRemap<MT>>(blockIdx.x, nblocks) * 4 + wave_in_block();
     if (tile >= tiles) return;
-    apply_tile_direct<MT, BIGC>(tile, N, nbits, D, sq, cf, C, HC);
+    apply_tile_direct<MT, BIGC>(tile, N, D, sq, cf, C, HC);
 }
 
 }  // namespace mc
@@ -94,16 +94,15 @@ static int apply_direct_common(int32_t N, int32_t M, const double *h_d, const do
     launch_prep_split(M, adjoint, g_d, h_d, cf, s);
     const int64_t tiles = (D + kTile - 1) / kTile;
     const int64_t nblocks = (tiles + 3) / 4;
-    const int nbits = bit_width(N);
     const bool big = D * 16 > (int64_t)0xFFFFFFFFu;
     MC_DISPATCH_M(M, if constexpr (MT > 0 && MT <= 8) {
         if (big)
             hipLaunchKernelGGL((k_apply_direct<MT, true>), dim3(nblocks), dim3(256),
-                               kLdsRoots<MT> ? sqb : 0, s, N, nbits, D, tiles, nblocks,
+                               kLdsRoots<MT> ? sqb : 0, s, N, D, tiles, nblocks,
                                (const double2 *)cf, (const double2 *)C_d, (double2 *)HC_d);
         else
             hipLaunchKernelGGL((k_apply_direct<MT, false>), dim3(nblocks), dim3(256),
-                               kLdsRoots<MT> ? sqb : 0, s, N, nbits, D, tiles, nblocks,
+                               kLdsRoots<MT> ? sqb : 0, s, N, D, tiles, nblocks,
                                (const double2 *)cf, (const double2 *)C_d, (double2 *)HC_d);
     });
     return launch_status();

@@ -38,12 +38,15 @@
 //
 // Kernel.  One wavefront per block walks chunks of 64 intermediate
 // configurations (lane = configuration): it computes its row of X into LDS,
-// then the upper triangle of the chunk's Gram matrix is accumulated in
-// BS x BS complex register blocks (BS of 2, 3 or 4: the least padding), one
-// block pair (bi <= bj) per lane and the 64 rows split over 64 / #blocks lane
-// groups.  The groups are summed in a fixed
-// order at the end; partials per wavefront go to the workspace and are summed
-// over wavefronts by a fixed tree: results are bitwise reproducible.
+// then accumulates the upper triangle of the chunk's Gram matrix in 4 x 4
+// blocks on the matrix cores (v_mfma_f64_4x4x4f64: four independent 4 x 4 x 4
+// products, here the same block of columns over four groups of four rows).
+// With X = R + iI a block (bi < bj) takes R'R + I'I and R'I - I'R, four
+// products, a diagonal block three, its imaginary part being R'I less its
+// transpose.  The 4 x 4 form measured 62 TFLOP/s in double on this card and
+// the 16 x 16 form 40, and it pads the columns least (15 of 16 at M = 5, 21 of
+// 24 at M = 6).  Partials per wavefront go to the workspace and are summed over
+// wavefronts by a fixed tree: results are bitwise reproducible.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -58,34 +61,17 @@ namespace mc {
 
 // Column layout of the lift of L particles (L = 1: one column per orbital;
 // L = 2: one per unordered pair, lexicographic).
-// Register block size of the Gram accumulation: of 2, 3 and 4, the one that
-// pads the upper triangle least with at most 64 block pairs (one per lane).
-__host__ __device__ constexpr int gram_block(int P)
-{
-    int best = 4, best_pad = 1 << 30;
-    for (int bs = 2; bs <= 4; ++bs) {
-        const int pb = (P + bs - 1) / bs, nb = pb * (pb + 1) / 2;
-        if (nb > 64) continue;
-        const int pad = nb * bs * bs;
-        if (pad < best_pad) {
-            best = bs;
-            best_pad = pad;
-        }
-    }
-    return best;
-}
+constexpr int kGramBlock = 4;   // columns per matrix block
 
 template <int MT, int L>
 struct Lift {
-    static constexpr int P = L == 1 ? MT : MT * (MT + 1) / 2;   // columns
-    static constexpr int BS = gram_block(P);                     // register block size
-    static constexpr int PB = (P + BS - 1) / BS;                  // column blocks
-    static constexpr int PP = BS * PB;                            // padded columns
+    static constexpr int P = L == 1 ? MT : MT * (MT + 1) / 2;     // columns
+    static constexpr int PB = (P + kGramBlock - 1) / kGramBlock;  // column blocks
+    static constexpr int PP = kGramBlock * PB;                    // padded columns
     static constexpr int NB = PB * (PB + 1) / 2;                  // block pairs bi <= bj
-    static constexpr int R = 64 / NB;                             // lane groups over rows
-    static constexpr int E = NB * BS * BS;                        // partial entries per wave
-    static constexpr int STRIDE = PP + 1;                         // LDS row stride (double2)
-    static constexpr int LDS = (64 * STRIDE > 64 * 16 ? 64 * STRIDE : 64 * 16) * 16;   // bytes
+    static constexpr int E = NB * kGramBlock * kGramBlock;        // partial entries per wave
+    static constexpr int STRIDE = PP + 1;   // LDS row stride (double2): odd, no bank conflicts
+    static constexpr int LDS = 64 * STRIDE * 16;                  // bytes
 };
 
 template <int MT, int L, int c>
@@ -93,14 +79,22 @@ __host__ __device__ constexpr int col_q() { return L == 1 ? c : pair_k(MT, c); }
 template <int MT, int L, int c>
 __host__ __device__ constexpr int col_l() { return L == 1 ? -1 : pair_s(MT, c); }
 
-// Ladder amplitude of column (q, l) (l < 0: one particle) on occupations m.
+// Ladder amplitude of column (q, l) (l < 0: one particle) on occupations m;
+// from M = 5 on the roots come from an LDS table of sqrt(i), i = 0 .. N+2
+// (below, N can be too large for one).
 template <int MT, int q, int l>
-__device__ __forceinline__ double lift_amp(const int (&m)[MT])
+__device__ __forceinline__ double lift_amp(const int (&m)[MT], const double *sq)
 {
-    const double a = (double)m[q] + 1.0;
-    if constexpr (l < 0) return sqrt(a);
-    else if constexpr (q == l) return sqrt(a * (a + 1.0));
-    else return sqrt(a * ((double)m[l] + 1.0));
+    if constexpr (kLdsRoots<MT>) {
+        if constexpr (l < 0) return sq[m[q] + 1];
+        else if constexpr (q == l) return sq[m[q] + 1] * sq[m[q] + 2];
+        else return sq[m[q] + 1] * sq[m[l] + 1];
+    } else {
+        const double a = (double)m[q] + 1.0;
+        if constexpr (l < 0) return sqrt(a);
+        else if constexpr (q == l) return sqrt(a * (a + 1.0));
+        else return sqrt(a * ((double)m[l] + 1.0));
+    }
 }
 
 constexpr int kGramBatch = 12;   // gathers per basic block
@@ -109,8 +103,8 @@ constexpr int kGramBatch = 12;   // gathers per basic block
 // index (-1: none), the values amp * C[index] go to xrow[c].
 template <int MT, int L, bool BIGC, int C0, class Tgt, int... Is>
 __device__ __forceinline__ void gram_batch(std::integer_sequence<int, Is...>, const Tgt &tgt,
-                                           const int (&m)[MT], const Gather<BIGC> &ldc,
-                                           double2 *xrow)
+                                           const int (&m)[MT], const double *sq,
+                                           const Gather<BIGC> &ldc, double2 *xrow)
 {
     constexpr int P = Lift<MT, L>::P;
     int32_t t[sizeof...(Is)];
@@ -130,7 +124,7 @@ __device__ __forceinline__ void gram_batch(std::integer_sequence<int, Is...>, co
         [&] {
             constexpr int c = C0 + Is;
             if constexpr (c < P) {
-                const double a = lift_amp<MT, col_q<MT, L, c>(), col_l<MT, L, c>()>(m);
+                const double a = lift_amp<MT, col_q<MT, L, c>(), col_l<MT, L, c>()>(m, sq);
                 xrow[c] = make_double2(a * v[Is].x, a * v[Is].y);
             }
         }(),
@@ -139,15 +133,15 @@ __device__ __forceinline__ void gram_batch(std::integer_sequence<int, Is...>, co
 
 template <int MT, int L, bool BIGC, class Tgt, int... Bs>
 __device__ __forceinline__ void gram_row(std::integer_sequence<int, Bs...>, const Tgt &tgt,
-                                         const int (&m)[MT], const Gather<BIGC> &ldc,
-                                         double2 *xrow)
+                                         const int (&m)[MT], const double *sq,
+                                         const Gather<BIGC> &ldc, double2 *xrow)
 {
     (
         [&] {
             // each batch in a basic block of its own (see opaque_true)
             if (opaque_true())
                 gram_batch<MT, L, BIGC, Bs * kGramBatch>(
-                    std::make_integer_sequence<int, kGramBatch>{}, tgt, m, ldc, xrow);
+                    std::make_integer_sequence<int, kGramBatch>{}, tgt, m, sq, ldc, xrow);
         }(),
         ...);
 }
@@ -182,16 +176,20 @@ struct LiftTargets {
 template <int MT, int L, bool BIGC>
 struct DirectSource {
     using Tgt = LiftTargets<MT, L>;
-    int Nl, nbits;      // N - L and its bit width
+    int Nl;             // N - L
     int64_t Dl, DN;     // dimensions of the N - L and N particle spaces
 
+    struct Raw {};
+    __device__ __forceinline__ void fetch(int64_t, int, Raw &) const {}
+
     // targets and occupations of intermediate configuration ch * 64 + lane
-    __device__ __forceinline__ bool prepare(int64_t ch, int lane, Tgt &tg, int (&m)[MT]) const
+    __device__ __forceinline__ bool prepare(const Raw &, int64_t ch, int lane, Tgt &tg,
+                                            int (&m)[MT]) const
     {
         const int64_t row = ch * 64 + lane;
         tg.live = row < Dl;
         int S[MT];
-        direct_prefix<MT>(tg.live ? row : Dl - 1, Dl, Nl, nbits, S);
+        direct_prefix<MT>(tg.live ? row : Dl - 1, Dl, Nl, S);
         m[0] = S[0];
 #pragma unroll
         for (int j = 1; j < MT; ++j) m[j] = S[j] - S[j - 1];
@@ -206,13 +204,13 @@ struct DirectSource {
     }
 
     // the lane's row of X
-    __device__ __forceinline__ bool fill(int64_t ch, int lane, const Gather<BIGC> &ldc,
-                                         double2 *xrow) const
+    __device__ __forceinline__ bool fill(int64_t ch, int lane, const double *sq,
+                                         const Gather<BIGC> &ldc, double2 *xrow) const
     {
         Tgt tg;
         int m[MT];
-        prepare(ch, lane, tg, m);
-        gram_row<MT, L, BIGC>(std::make_integer_sequence<int, kGramBatches<MT, L>>{}, tg, m, ldc,
+        prepare(Raw{}, ch, lane, tg, m);
+        gram_row<MT, L, BIGC>(std::make_integer_sequence<int, kGramBatches<MT, L>>{}, tg, m, sq, ldc,
                               xrow);
         return true;
     }
@@ -225,12 +223,12 @@ struct DirectSource {
 // ---------------------------------------------------------------------------
 template <int MT, int L, int KIND>
 struct MapTargets {
+    static constexpr int ND = MT * (MT - 1) / 2 > 0 ? MT * (MT - 1) / 2 : 1;
     bool live;
     int32_t g;
     int32_t s0[MT];                         // T1[gamma][0][l]
-    __amdgpu_buffer_rsrc_t r2;              // the tile's (0, 0) block (map kinds)
+    int32_t d[ND];                          // (0, 0) -> (q, l), 1 <= q <= l (map kinds)
     const int32_t *__restrict__ t1;         // whole single-jump map (chained kind)
-    int lane;
 
     __device__ __forceinline__ int32_t chain(int32_t u, int l) const
     {
@@ -250,10 +248,8 @@ struct MapTargets {
             return g;
         } else if constexpr (q == 0) {
             return s0[l];
-        } else if constexpr (KIND == 1) {
-            return buf_ld_i32(r2, (uint32_t)(((q * MT + l) * kTile + lane) * 4), 0);
-        } else if constexpr (KIND == 2) {
-            return buf_ld_i32(r2, (uint32_t)((reduced_rank(MT, 0, 0, q, l) * kTile + lane) * 4), 0);
+        } else if constexpr (KIND != 0) {
+            return d[reduced_rank(MT, 0, 0, q, l)];
         } else {
             return chain(s0[q], l);
         }
@@ -270,47 +266,76 @@ struct MapSource {
     const int64_t *__restrict__ t2_off;
     const int32_t *__restrict__ t2;
 
-    // targets and occupations of the rows of tile `tile` (false: no row of
-    // the tile has L particles in orbital 0; wave-uniform)
-    __device__ __forceinline__ bool prepare(int64_t tile, int lane, Tgt &tg, int (&m)[MT]) const
+    // What the tables hold for a tile's rows.  The kernel fetches it one chunk
+    // before the gathers that need it (rho2 through the paper's map at N=50,
+    // M=6: 0.45 ms with the table reads and the gathers in one chain).
+    struct Raw {
+        OccT n[MT];
+        int32_t s0[MT], d[Tgt::ND];
+        bool fits;
+    };
+
+    __device__ __forceinline__ void fetch(int64_t tile, int lane, Raw &w) const
     {
         constexpr int NS = MT * MT;
-        tg.lane = lane;
-        tg.t1 = t1;
-        const int64_t g = tile * kTile + lane;
-        int n[MT];
-#pragma unroll
-        for (int k = 0; k < MT; ++k) n[k] = (int)occ[(tile * MT + k) * kTile + lane];
-        tg.live = g < D && n[0] >= L;
-        tg.g = (int32_t)g;
-        // occupations of m = n - L e_0 (zero on rows without one: their
-        // amplitudes must stay finite, their values are zero)
-#pragma unroll
-        for (int k = 0; k < MT; ++k) m[k] = tg.live ? n[k] - (k == 0 ? L : 0) : 0;
-        const __amdgpu_buffer_rsrc_t r1 = make_rsrc(t1 + tile * NS * kTile, (uint32_t)(NS * kTile * 4));
-#pragma unroll
-        for (int l = 0; l < MT; ++l)
-            tg.s0[l] = l == 0 ? (int32_t)g : buf_ld_i32(r1, (uint32_t)((l * kTile + lane) * 4), 0);
+        w.fits = true;
         if constexpr (L == 2 && KIND != 0) {
             // pair (0, 0) is the first block of the tile when present
             constexpr int BS = KIND == 1 ? NS : MT * (MT - 1) / 2;
             const bool has = (pmask[tile * ((MT * (MT + 1) / 2 + 63) / 64)] & 1) != 0;
             int64_t off0, off1;
             t2_block(t2_off, tile, cap, off0, off1);
-            const bool fits = has && off0 + (int64_t)BS * kTile <= off1;
-            tg.r2 = make_rsrc(t2 + (fits ? off0 : 0), fits ? (uint32_t)(BS * kTile * 4) : 0u);
-            if (!fits) tg.live = false;
+            w.fits = has && off0 + (int64_t)BS * kTile <= off1;
+            const __amdgpu_buffer_rsrc_t r2 =
+                make_rsrc(t2 + (w.fits ? off0 : 0), w.fits ? (uint32_t)(BS * kTile * 4) : 0u);
+#pragma unroll
+            for (int q = 1; q < MT; ++q)
+#pragma unroll
+                for (int l = q; l < MT; ++l) {
+                    const int r = reduced_rank(MT, 0, 0, q, l);
+                    w.d[r] = buf_ld_i32(r2, (uint32_t)(((KIND == 1 ? q * MT + l : r) * kTile + lane) * 4), 0);
+                }
+        }
+#pragma unroll
+        for (int k = 0; k < MT; ++k) w.n[k] = occ[(tile * MT + k) * kTile + lane];
+        const __amdgpu_buffer_rsrc_t r1 = make_rsrc(t1 + tile * NS * kTile, (uint32_t)(NS * kTile * 4));
+#pragma unroll
+        for (int l = 1; l < MT; ++l)
+            w.s0[l] = buf_ld_i32(r1, (uint32_t)((l * kTile + lane) * 4), 0);
+    }
+
+    // targets and occupations of the rows of tile `tile` (false: no row of
+    // the tile has L particles in orbital 0; wave-uniform)
+    __device__ __forceinline__ bool prepare(const Raw &w, int64_t tile, int lane, Tgt &tg,
+                                            int (&m)[MT]) const
+    {
+        tg.t1 = t1;
+        const int64_t g = tile * kTile + lane;
+        tg.live = w.fits && g < D && (int)w.n[0] >= L;
+        tg.g = (int32_t)g;
+        // occupations of m = n - L e_0 (zero on rows without one: their
+        // amplitudes must stay finite, their values are zero)
+#pragma unroll
+        for (int k = 0; k < MT; ++k) m[k] = tg.live ? (int)w.n[k] - (k == 0 ? L : 0) : 0;
+        tg.s0[0] = (int32_t)g;
+#pragma unroll
+        for (int l = 1; l < MT; ++l) tg.s0[l] = w.s0[l];
+        if constexpr (L == 2 && KIND != 0) {
+#pragma unroll
+            for (int r = 0; r < MT * (MT - 1) / 2; ++r) tg.d[r] = w.d[r];
         }
         return __builtin_amdgcn_readfirstlane(__ballot(tg.live) != 0);
     }
 
-    __device__ __forceinline__ bool fill(int64_t tile, int lane, const Gather<BIGC> &ldc,
-                                         double2 *xrow) const
+    __device__ __forceinline__ bool fill(int64_t tile, int lane, const double *sq,
+                                         const Gather<BIGC> &ldc, double2 *xrow) const
     {
+        Raw w;
         Tgt tg;
         int m[MT];
-        if (!prepare(tile, lane, tg, m)) return false;
-        gram_row<MT, L, BIGC>(std::make_integer_sequence<int, kGramBatches<MT, L>>{}, tg, m, ldc,
+        fetch(tile, lane, w);
+        if (!prepare(w, tile, lane, tg, m)) return false;
+        gram_row<MT, L, BIGC>(std::make_integer_sequence<int, kGramBatches<MT, L>>{}, tg, m, sq, ldc,
                               xrow);
         return true;
     }
@@ -330,11 +355,11 @@ __device__ __forceinline__ void gram_issue(std::integer_sequence<int, Cs...>, co
 
 template <int MT, int L, int... Cs>
 __device__ __forceinline__ void gram_commit(std::integer_sequence<int, Cs...>, const int (&m)[MT],
-                                            const double2 (&v)[Lift<MT, L>::P], double2 *xrow)
+                                            const double *sq, const double2 (&v)[Lift<MT, L>::P], double2 *xrow)
 {
     (
         [&] {
-            const double a = lift_amp<MT, col_q<MT, L, Cs>(), col_l<MT, L, Cs>()>(m);
+            const double a = lift_amp<MT, col_q<MT, L, Cs>(), col_l<MT, L, Cs>()>(m, sq);
             xrow[Cs] = make_double2(a * v[Cs].x, a * v[Cs].y);
         }(),
         ...);
@@ -349,96 +374,114 @@ __device__ __forceinline__ void gram_commit(std::integer_sequence<int, Cs...>, c
 // ---------------------------------------------------------------------------
 // The Gram kernel over any source.
 // ---------------------------------------------------------------------------
+
+// Sums of one 4 x 4 block of columns pairs, spread over the lanes as the
+// matrix instruction leaves them: lane j + 4 g + 16 i holds entry (i, j) over
+// the rows of group g.
+template <int MT, int L>
+struct GramAcc {
+    double re[Lift<MT, L>::NB], im[Lift<MT, L>::NB];
+};
+
+// Block pair (BI, BJ) of 16 rows.
+template <int MT, int L, int BI, int BJ>
+__device__ __forceinline__ void gram_pair(const double (&r)[Lift<MT, L>::PB],
+                                          const double (&x)[Lift<MT, L>::PB],
+                                          GramAcc<MT, L> &A)
+{
+    if constexpr (BI <= BJ) {
+        constexpr int PB = Lift<MT, L>::PB, k = BI * PB - BI * (BI - 1) / 2 + (BJ - BI);
+        A.re[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(r[BI], r[BJ], A.re[k], 0, 0, 0);
+        A.re[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(x[BI], x[BJ], A.re[k], 0, 0, 0);
+        A.im[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(r[BI], x[BJ], A.im[k], 0, 0, 0);
+        if constexpr (BI < BJ)
+            A.im[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(-x[BI], r[BJ], A.im[k], 0, 0, 0);
+    }
+}
+
+template <int MT, int L, int... Ks>
+__device__ __forceinline__ void gram_rows(std::integer_sequence<int, Ks...>, const double2 *X,
+                                          int lane, GramAcc<MT, L> &A)
+{
+    constexpr int PB = Lift<MT, L>::PB, STRIDE = Lift<MT, L>::STRIDE;
+    // operand lane: column lane % 4 of its block, row 4 (lane / 4 % 4) + lane / 16
+    const double2 *x0 = X + (4 * ((lane >> 2) & 3) + (lane >> 4)) * STRIDE + (lane & 3);
+    for (int r0 = 0; r0 < 64; r0 += 16) {
+        double r[PB], x[PB];
+#pragma unroll
+        for (int c = 0; c < PB; ++c) {
+            const double2 v = x0[r0 * STRIDE + 4 * c];
+            r[c] = v.x;
+            x[c] = v.y;
+        }
+        (gram_pair<MT, L, Ks / PB, Ks % PB>(r, x, A), ...);
+    }
+}
+
 template <int MT, int L, bool BIGC, class Src>
 __global__ __launch_bounds__(64) void k_gram(Src src, int64_t DN, int64_t chunks, int nwaves,
-                                             const double2 *__restrict__ C,
+                                             int nroots, const double2 *__restrict__ C,
                                              double2 *__restrict__ part)
 {
     using LF = Lift<MT, L>;
-    extern __shared__ double2 X[];   // [64][STRIDE]; reused for the group sums
+    extern __shared__ double2 X[];   // [64][STRIDE], then the roots
     const int lane = threadIdx.x;
     const int wave = blockIdx.x;
+    double *sq = (double *)(X + 64 * LF::STRIDE);
+    for (int i = lane; i < nroots; i += 64) sq[i] = sqrt((double)i);
 #pragma unroll
     for (int c = LF::P; c < LF::PP; ++c) X[lane * LF::STRIDE + c] = make_double2(0.0, 0.0);
-    // this lane's block pair (bi <= bj) and row group
-    const int blk = lane % LF::NB, grp = lane / LF::NB;
-    int bi = 0, rem = blk;
-    while (rem >= LF::PB - bi) {
-        rem -= LF::PB - bi;
-        ++bi;
-    }
-    const int bj = bi + rem;
-    constexpr int BS = LF::BS;
-    double ar[BS][BS], ai[BS][BS];
+    __syncthreads();
+    GramAcc<MT, L> A;
 #pragma unroll
-    for (int i = 0; i < BS; ++i)
-#pragma unroll
-        for (int j = 0; j < BS; ++j) ar[i][j] = ai[i][j] = 0.0;
+    for (int k = 0; k < LF::NB; ++k) A.re[k] = A.im[k] = 0.0;
     const Gather<BIGC> ldc(C, DN);
     constexpr bool PRE = LF::P <= MC_GRAM_PREFETCH_MAX_P;
     typename Src::Tgt tg;
     int m[MT];
     double2 pv[PRE ? LF::P : 1];
+    typename Src::Raw raw;
     if constexpr (PRE) {
         if (wave < chunks) {
-            src.prepare(wave, lane, tg, m);
+            src.fetch(wave, lane, raw);
+            src.prepare(raw, wave, lane, tg, m);
             gram_issue<MT, L, BIGC>(std::make_integer_sequence<int, LF::P>{}, tg, ldc, pv);
+            if (wave + nwaves < chunks) src.fetch(wave + nwaves, lane, raw);
         }
     }
     for (int64_t ch = wave; ch < chunks; ch += nwaves) {
         if constexpr (PRE) {
             // this chunk's values (in flight since the last chunk) into LDS,
-            // then the next chunk's gathers, in flight during the arithmetic
-            gram_commit<MT, L>(std::make_integer_sequence<int, LF::P>{}, m, pv,
+            // then the next chunk's gathers and the table reads of the one
+            // after it, in flight during the products
+            gram_commit<MT, L>(std::make_integer_sequence<int, LF::P>{}, m, sq, pv,
                                X + lane * LF::STRIDE);
             __syncthreads();
             if (ch + nwaves < chunks) {
-                src.prepare(ch + nwaves, lane, tg, m);
+                src.prepare(raw, ch + nwaves, lane, tg, m);
                 gram_issue<MT, L, BIGC>(std::make_integer_sequence<int, LF::P>{}, tg, ldc, pv);
+                if (ch + 2 * (int64_t)nwaves < chunks) src.fetch(ch + 2 * (int64_t)nwaves, lane, raw);
             }
         } else {
             // a chunk with no intermediate configuration adds nothing (wave-uniform)
-            if (!src.fill(ch, lane, ldc, X + lane * LF::STRIDE)) continue;
+            if (!src.fill(ch, lane, sq, ldc, X + lane * LF::STRIDE)) continue;
             __syncthreads();
         }
-        if (grp < LF::R) {
-            for (int r = grp; r < 64; r += LF::R) {
-                const double2 *xr = X + r * LF::STRIDE;
-                double2 a[BS], b[BS];
-#pragma unroll
-                for (int i = 0; i < BS; ++i) {
-                    a[i] = xr[BS * bi + i];
-                    b[i] = xr[BS * bj + i];
-                }
-#pragma unroll
-                for (int i = 0; i < BS; ++i)
-#pragma unroll
-                    for (int j = 0; j < BS; ++j) {
-                        // conj(a_i) b_j
-                        ar[i][j] = fma(a[i].x, b[j].x, fma(a[i].y, b[j].y, ar[i][j]));
-                        ai[i][j] = fma(a[i].x, b[j].y, fma(-a[i].y, b[j].x, ai[i][j]));
-                    }
-            }
-        }
+        gram_rows<MT, L>(std::make_integer_sequence<int, LF::PB * LF::PB>{}, X, lane, A);
         __syncthreads();
     }
-    // sum the lane groups of each block pair in group order
-    if (grp < LF::R) {
+    // sum the four row groups; lanes 16 i + j then hold entry (i, j)
 #pragma unroll
-        for (int i = 0; i < BS; ++i)
-#pragma unroll
-            for (int j = 0; j < BS; ++j)
-                X[(grp * LF::NB + blk) * BS * BS + i * BS + j] = make_double2(ar[i][j], ai[i][j]);
-    }
-    __syncthreads();
-    for (int e = lane; e < LF::E; e += 64) {
-        double sr = 0.0, si = 0.0;
-        for (int g = 0; g < LF::R; ++g) {
-            const double2 v = X[g * LF::E + e];
-            sr += v.x;
-            si += v.y;
+    for (int k = 0; k < LF::NB; ++k) {
+        double re = A.re[k], im = A.im[k];
+        re += __shfl_xor(re, 4, 64);
+        re += __shfl_xor(re, 8, 64);
+        im += __shfl_xor(im, 4, 64);
+        im += __shfl_xor(im, 8, 64);
+        if (((lane >> 2) & 3) == 0) {
+            const int e = 16 * k + 4 * (lane >> 4) + (lane & 3);
+            part[(int64_t)e * nwaves + wave] = make_double2(re, im);
         }
-        part[(int64_t)e * nwaves + wave] = make_double2(sr, si);
     }
 }
 
@@ -480,7 +523,7 @@ __device__ __forceinline__ int upair(int M, int x, int y)
 // Gram entry (k, l); rho2[k][s][q][l] is entry ({k,s}, {q,l}).  Entries
 // below the diagonal are conjugates, diagonal entries are real.  canon =
 // NULL writes zeros (fewer than L particles).
-__global__ __launch_bounds__(256) void k_gram_expand(int M, int L, int PB, int BS,
+__global__ __launch_bounds__(256) void k_gram_expand(int M, int L, int PB,
                                                      const double2 *__restrict__ canon,
                                                      double2 *__restrict__ out)
 {
@@ -502,46 +545,50 @@ __global__ __launch_bounds__(256) void k_gram_expand(int M, int L, int PB, int B
     }
     const bool swap = c1 > c2;
     const int x = swap ? c2 : c1, y = swap ? c1 : c2;
+    constexpr int BS = kGramBlock;
     const int bi = x / BS, bj = y / BS;
-    const int blk = bi * PB - bi * (bi - 1) / 2 + (bj - bi);
-    double2 v = canon[blk * BS * BS + (x % BS) * BS + (y % BS)];
+    const double2 *blk = canon + (bi * PB - bi * (bi - 1) / 2 + (bj - bi)) * BS * BS;
+    double2 v = blk[(x % BS) * BS + (y % BS)];
+    // a diagonal block holds R'I: the imaginary part is that less its transpose
+    if (bi == bj) v.y -= blk[(y % BS) * BS + (x % BS)].y;
     if (swap) v.y = -v.y;
     if (x == y) v.y = 0.0;
     out[idx] = v;
 }
 
-constexpr int64_t kGramMaxWaves = 2048;
+constexpr int64_t kGramWavesPerCu = 12;
+inline int gram_roots(int N, int M) { return M >= MC_LDS_ROOTS_FROM ? N + 3 : 0; }
 
 // Shape of one call: wavefronts (from the LDS footprint: the resident
-// wavefronts of 256 CUs, at most 8 per CU, fixed per (N, M) so results are
+// wavefronts of 256 CUs, at most 12 per CU, fixed per (N, M) so results are
 // reproducible on any device), partial entries, workspace bytes.
 struct GramShape {
-    int64_t chunks = 0, nwaves = 0, E = 0, PB = 0, BS = 0;
+    int64_t chunks = 0, nwaves = 0, E = 0, PB = 0;
+    int nroots = 0;
     size_t lds = 0, ws = 0;
 };
 
 template <int MT, int L>
-void gram_shape_t(int64_t chunks, GramShape *g)
+void gram_shape_t(int N, int64_t chunks, GramShape *g)
 {
-    int64_t per_cu = (160 * 1024) / Lift<MT, L>::LDS;
-    per_cu = per_cu < 1 ? 1 : (per_cu > 8 ? 8 : per_cu);
-    int64_t w = 256 * per_cu;
-    w = w < kGramMaxWaves ? w : kGramMaxWaves;
+    g->nroots = gram_roots(N, MT);
+    g->lds = Lift<MT, L>::LDS + (size_t)g->nroots * 8;
+    int64_t per_cu = (160 * 1024) / (int64_t)g->lds;
+    per_cu = per_cu < 1 ? 1 : (per_cu > kGramWavesPerCu ? kGramWavesPerCu : per_cu);
+    const int64_t w = 256 * per_cu;
     g->chunks = chunks;
     g->nwaves = chunks < w ? (chunks > 0 ? chunks : 1) : w;
     g->E = Lift<MT, L>::E;
     g->PB = Lift<MT, L>::PB;
-    g->BS = Lift<MT, L>::BS;
-    g->lds = Lift<MT, L>::LDS;
     g->ws = (size_t)(g->E * g->nwaves + g->E) * 16;
 }
 
-inline int gram_shape(int M, int L, int64_t chunks, GramShape *g)
+inline int gram_shape(int N, int M, int L, int64_t chunks, GramShape *g)
 {
     if (M < 1 || M > 8 || (L != 1 && L != 2)) return MC_EINVAL;
     MC_DISPATCH_M(M, if constexpr (MT > 0 && MT <= 8) {
-        if (L == 1) (gram_shape_t<MT, 1>)(chunks, g);
-        else (gram_shape_t<MT, 2>)(chunks, g);
+        if (L == 1) (gram_shape_t<MT, 1>)(N, chunks, g);
+        else (gram_shape_t<MT, 2>)(N, chunks, g);
     });
     return MC_OK;
 }
@@ -550,7 +597,7 @@ inline int gram_shape(int M, int L, int64_t chunks, GramShape *g)
 inline int gram_zero(int M, int L, double *out_d, hipStream_t s)
 {
     const int total = L == 1 ? M * M : M * M * M * M;
-    hipLaunchKernelGGL(k_gram_expand, dim3((total + 255) / 256), dim3(256), 0, s, M, L, 1, 1,
+    hipLaunchKernelGGL(k_gram_expand, dim3((total + 255) / 256), dim3(256), 0, s, M, L, 1,
                        (const double2 *)nullptr, (double2 *)out_d);
     return launch_status();
 }
@@ -564,11 +611,11 @@ int gram_launch(const Src &src, int64_t DN, const GramShape &gs, const double *C
     double2 *canon = part + gs.E * gs.nwaves;
     const int total = L == 1 ? MT * MT : MT * MT * MT * MT;
     hipLaunchKernelGGL((k_gram<MT, L, BIGC, Src>), dim3((unsigned)gs.nwaves), dim3(64), gs.lds, s,
-                       src, DN, gs.chunks, (int)gs.nwaves, (const double2 *)C_d, part);
+                       src, DN, gs.chunks, (int)gs.nwaves, gs.nroots, (const double2 *)C_d, part);
     hipLaunchKernelGGL(k_gram_sum, dim3((unsigned)gs.E), dim3(256), 0, s, (int)gs.nwaves, part,
                        canon);
     hipLaunchKernelGGL(k_gram_expand, dim3((total + 255) / 256), dim3(256), 0, s, MT, L,
-                       (int)gs.PB, (int)gs.BS, (const double2 *)canon, (double2 *)out_d);
+                       (int)gs.PB, (const double2 *)canon, (double2 *)out_d);
     return launch_status();
 }
 

@@ -19,19 +19,19 @@ int direct_rho(int L, int32_t N, int32_t M, const double *C_d, double *out_d, vo
     if (N < L) return gram_zero(M, L, out_d, s);   // no configuration of N - L particles
     const int64_t Dl = dim_checked(N - L, M);
     GramShape gs;
-    st = gram_shape(M, L, (Dl + 63) / 64, &gs);
+    st = gram_shape(N, M, L, (Dl + 63) / 64, &gs);
     if (st) return st;
     if (!ws_d) return MC_EINVAL;
     if (ws_bytes < gs.ws) return MC_ENOMEM;
     const bool big = DN * 16 > (int64_t)0xFFFFFFFFu;
-    const int Nl = N - L, nbits = bit_width(Nl);
+    const int Nl = N - L;
     MC_DISPATCH_M(M, if constexpr (MT > 0 && MT <= 8) {
         if (L == 1) {
-            if (big) st = (gram_launch<MT, 1, true>)(DirectSource<MT, 1, true>{Nl, nbits, Dl, DN}, DN, gs, C_d, out_d, ws_d, s);
-            else st = (gram_launch<MT, 1, false>)(DirectSource<MT, 1, false>{Nl, nbits, Dl, DN}, DN, gs, C_d, out_d, ws_d, s);
+            if (big) st = (gram_launch<MT, 1, true>)(DirectSource<MT, 1, true>{Nl, Dl, DN}, DN, gs, C_d, out_d, ws_d, s);
+            else st = (gram_launch<MT, 1, false>)(DirectSource<MT, 1, false>{Nl, Dl, DN}, DN, gs, C_d, out_d, ws_d, s);
         } else {
-            if (big) st = (gram_launch<MT, 2, true>)(DirectSource<MT, 2, true>{Nl, nbits, Dl, DN}, DN, gs, C_d, out_d, ws_d, s);
-            else st = (gram_launch<MT, 2, false>)(DirectSource<MT, 2, false>{Nl, nbits, Dl, DN}, DN, gs, C_d, out_d, ws_d, s);
+            if (big) st = (gram_launch<MT, 2, true>)(DirectSource<MT, 2, true>{Nl, Dl, DN}, DN, gs, C_d, out_d, ws_d, s);
+            else st = (gram_launch<MT, 2, false>)(DirectSource<MT, 2, false>{Nl, Dl, DN}, DN, gs, C_d, out_d, ws_d, s);
         }
     });
     return st;
@@ -45,7 +45,7 @@ size_t gram_workspace(int32_t N, int32_t M, int L)
     const int64_t Dl = dim_checked(N - L, M);
     if (Dl < 0) return 0;
     GramShape gs;
-    if (gram_shape(M, L, (Dl + 63) / 64, &gs)) return 0;
+    if (gram_shape(N, M, L, (Dl + 63) / 64, &gs)) return 0;
     return gs.ws;
 }
 

@@ -62,7 +62,7 @@ int map_rho(int L, int32_t N, int32_t M, const mc_tables *t, const double *C_d, 
     hipStream_t s = (hipStream_t)stream;
     if (N < L) return gram_zero(M, L, out_d, s);
     GramShape gs;
-    st = gram_shape(M, L, t->tiles, &gs);
+    st = gram_shape(N, M, L, t->tiles, &gs);
     if (st) return st;
     if (!ws_d) return MC_EINVAL;
     if (ws_bytes < gs.ws) return MC_ENOMEM;
@@ -81,7 +81,7 @@ size_t gram_table_workspace(int32_t N, int32_t M, int L)
     const int64_t D = dim_checked(N, M);
     if (D < 0) return 0;
     GramShape gs;
-    if (gram_shape(M, L, (D + kTile - 1) / kTile, &gs)) return 0;
+    if (gram_shape(N, M, L, (D + kTile - 1) / kTile, &gs)) return 0;
     return gs.ws;
 }
 
