@@ -30,7 +30,7 @@ enum BatchKind : int32_t { kPaperMap = 0, kPaperChain = 1, kSplitMap = 2, kSplit
 
 struct BatchInst {
     int32_t N, M;
-    int32_t kind, pad;
+    int32_t kind, chunk0;  // chunk0: first chunk of the instance
     int64_t dim, tiles, cap, vec_off;
     const uint8_t *occ;
     const int32_t *t1;
@@ -54,8 +54,8 @@ static bool table_free(const mc_tables *t)
 }
 
 // Staged complex constants of an instance of M orbitals, enough for either
-// form, and with the tables of the four-row kernel behind them where a
-// table-free instance takes it (as mc_apply_H_direct would).
+// form, and with the tables of the four-row kernel behind them where the
+// instance takes it (as mc_apply_H_direct would).
 inline int64_t batch_const_elems(int M)
 {
     const int64_t paper = (int64_t)npairs(M) * M * M + (int64_t)M * M;
@@ -73,26 +73,37 @@ inline int64_t batch_coef_elems(const mc_tables *t)
 
 struct BatchChunk {
     int32_t inst;
+    int32_t first, count;   // the instance's chunks
     int32_t pad;
-    int64_t start, len;   // in batch-vector elements
+    int64_t start, len;     // in batch-vector elements
 };
 
-constexpr int64_t kChunk = 1 << 16;
+// Elements per chunk of the segmented vector operations: a chunk is one
+// block's work, so enough of them to fill the GPU, between 2,048 and 65,536
+// (24 instances of together 8e4 elements ran one block each, 11 us per
+// reduction where 4 us do).
+inline int64_t batch_chunk(int64_t total)
+{
+    int64_t c = 2048;
+    while (c < (1 << 16) && total / c > 2048) c <<= 1;
+    return c;
+}
 constexpr int kMaxGroups = 40;   // 8 orbital counts x 5 kinds
-constexpr int kGrab = 8;         // tiles a wavefront takes per counter increment (order 3)
+// Tiles a wavefront takes per counter increment (order 3): 8, fewer where the
+// group has no 8 per wavefront (8 small instances at M = 5: 165 us with 8 tiles
+// in a row on an eighth of the wavefronts, 25 us with one each).
+inline int batch_grab(int64_t items, int64_t blocks)
+{
+    const int64_t per = items / (blocks * 4);
+    return per >= 8 ? 8 : (per > 1 ? (int)per : 1);
+}
 
-// An instance launched on a grid of its own; its tables are passed to the
-// kernel as arguments (global, non-aliasing: the same loads as mc_apply_H).
-struct SoloLaunch {
+// An instance that the four-row kernel serves: a launch of its own.
+struct OwnLaunch {
     int32_t j;      // sorted position (index into the plan's descriptors)
-    int32_t M, kind, N;
-    int64_t tiles, dim, cap, vec_off, gp_off, hp_off;
-    const uint8_t *occ;
-    const int32_t *t1;
-    const uint64_t *pmask;
-    const int64_t *t2_off;
-    const int32_t *t2;
-    const int32_t *btab;   // set: the four-row kernel
+    int32_t M, N;
+    int64_t dim, vec_off, gp_off;
+    const int32_t *btab;
 };
 
 }  // namespace mc
@@ -112,13 +123,13 @@ struct mc_batch {
     mc::BatchInst *inst_d;    // [count], in sorted order
     int64_t *tile_prefix_d;   // [count + 1] per sorted instance, restarting per group
     mc::BatchChunk *chunks_d; // [nchunks]
-    double2 *partials_d;      // [nchunks]
+    double2 *partials_d;      // [2][nchunks]
     int32_t *sorted_d;        // [count] sorted position -> caller index
     int32_t *pos_d;           // [count] caller index -> sorted position
     uint32_t *counters_d;     // [kMaxGroups] work counters of order 3, zeroed per apply
     double2 *coef_d;          // staged coefficients of all instances
-    int32_t nsolo;            // instances launched on grids of their own
-    mc::SoloLaunch *solo;     // [nsolo] (host)
+    int32_t nown;             // instances with launches of their own
+    mc::OwnLaunch *own;       // [nown] (host)
 };
 
 namespace mc {
@@ -198,14 +209,14 @@ __device__ __forceinline__ void batch_tile(const BatchInst &I, int64_t tile, con
 // instance; with order 0 wavefront w takes items w, w + W, w + 2W, ...
 // (neighbouring tiles on neighbouring wavefronts), with order 1 a contiguous
 // range of items, with order 2 each XCD a contiguous share of the items,
-// interleaved over its wavefronts; with order 3 wavefronts take kGrab items
+// interleaved over its wavefronts; with order 3 wavefronts take a few items
 // at a time from a per-group counter (dynamic balance, like a plain launch).
 constexpr int kBatchMaxN = 255;
 
 template <int MT, int KIND>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MC_APPLY_WAVES)))
 void k_batch_apply(const BatchInst *__restrict__ inst, const int64_t *__restrict__ prefix,
-                   int first, int count, int64_t items, int64_t nblocks, int order,
+                   int first, int count, int64_t items, int64_t nblocks, int order, int grab,
                    uint32_t *__restrict__ counter, const double2 *__restrict__ coef,
                    const double2 *__restrict__ Cb, double2 *__restrict__ HCb)
 {
@@ -220,14 +231,14 @@ void k_batch_apply(const BatchInst *__restrict__ inst, const int64_t *__restrict
     };
     int j = 0;
     if (order == 3) {
-        // dynamic: take kGrab items at a time from the group's counter (a
+        // dynamic: take `grab` items at a time from the group's counter (a
         // vector atomic from lane 0; the count is zeroed by k_batch_prep)
         for (;;) {
             uint32_t base = 0;
-            if ((threadIdx.x & 63) == 0) base = atomicAdd(counter, (uint32_t)kGrab);
+            if ((threadIdx.x & 63) == 0) base = atomicAdd(counter, (uint32_t)grab);
             base = __builtin_amdgcn_readfirstlane(base);
             if ((int64_t)base >= items) break;
-            const int64_t end = (int64_t)base + kGrab < items ? (int64_t)base + kGrab : items;
+            const int64_t end = (int64_t)base + grab < items ? (int64_t)base + grab : items;
             for (int64_t i = base; i < end; ++i) tile_body(i, j);
         }
         return;
@@ -258,88 +269,148 @@ void k_batch_apply(const BatchInst *__restrict__ inst, const int64_t *__restrict
     for (int64_t i = i0; i < iend; i += step) tile_body(i, j);
 }
 
-// One large instance on a grid of its own: one wavefront per tile, blocks
-// remapped per XCD as in the plain apply; tables, staged constants and the
-// instance's vector segments arrive as kernel arguments.
-template <int MT, int KIND>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MC_APPLY_WAVES)))
-void k_batch_solo(int N, int64_t D, int64_t tiles, int64_t nblocks, int64_t cap,
-                  const uint8_t *__restrict__ occ, const int32_t *__restrict__ t1,
-                  const uint64_t *__restrict__ pmask, const int64_t *__restrict__ t2_off,
-                  const int32_t *__restrict__ t2, const double2 *__restrict__ gp,
-                  const double2 *__restrict__ hp, const double2 *__restrict__ C,
-                  double2 *__restrict__ HC)
+// conj(a) b added to (r, i); every reduction below adds its terms this way.
+__device__ __forceinline__ void dot_add(const double2 &a, const double2 &b, double &r, double &i)
 {
-    __shared__ double sq[kLdsRoots<MT> ? kBatchMaxN + 3 : 1];
-    // one instance: the roots it needs, as the plain launch fills them
-    if constexpr (kLdsRoots<MT>) fill_sqrt_table(sq, N + 3 < kBatchMaxN + 3 ? N + 3 : kBatchMaxN + 3);
-    const int64_t tile =
-        xcd_block_as<KIND == kDirect && kDirectRemap<MT>>(blockIdx.x, nblocks) * 4 + wave_in_block();
-    if (tile >= tiles) return;
-    if constexpr (KIND == kPaperMap)
-        apply_tile_paper<MT, uint8_t, false>(tile, D, cap, sq, occ, t1, pmask, t2_off, t2, hp, gp, C,
-                                          HC);
-    else if constexpr (KIND == kPaperChain)
-        apply_tile_chained<MT, uint8_t, false>(tile, D, sq, occ, t1, hp, gp, C, HC);
-    else if constexpr (KIND == kDirect)
-        apply_tile_direct<MT, false>(tile, N, D, sq, gp, C, HC);
-    else
-        apply_tile_split<MT, uint8_t, false, KIND == kSplitMap>(tile, D, cap, sq, occ, t1, pmask,
-                                                                t2_off, t2, gp, C, HC);
+    r = fma(a.x, b.x, fma(a.y, b.y, r));
+    i = fma(a.x, b.y, fma(-a.y, b.x, i));
 }
 
-// Segmented conj(x).y: chunk partials, then per-instance sums in chunk order.
+// The block's sum of (ar, ai) over 256 threads, on every thread.
+__device__ __forceinline__ double2 block_sum2(double ar, double ai, double *s)
+{
+    ar = wave_sum(ar);
+    ai = wave_sum(ai);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) {
+        s[wave_in_block()] = ar;
+        s[4 + wave_in_block()] = ai;
+    }
+    __syncthreads();
+    return make_double2((s[0] + s[1]) + (s[2] + s[3]), (s[4] + s[5]) + (s[6] + s[7]));
+}
+
+// The sum of an instance's chunk partials, on every thread of a block of 256:
+// a fixed strided split over the threads and a fixed tree.
+__device__ __forceinline__ double2 seg_total(const double2 *__restrict__ part, int first,
+                                             int count, double *s)
+{
+    double ar = 0.0, ai = 0.0;
+    for (int c = threadIdx.x; c < count; c += 256) {
+        const double2 v = part[first + c];
+        ar += v.x;
+        ai += v.y;
+    }
+    return block_sum2(ar, ai, s);
+}
+
+// Segmented conj(x).y: partials per chunk.
 __global__ __launch_bounds__(256) void k_seg_dot_partial(const BatchChunk *__restrict__ ch,
                                                           int64_t nchunks,
                                                           const double2 *__restrict__ x,
                                                           const double2 *__restrict__ y,
                                                           double2 *__restrict__ part)
 {
-    __shared__ double sr[4], si[4];
+    __shared__ double s[8];
     for (int64_t c = blockIdx.x; c < nchunks; c += gridDim.x) {
         const BatchChunk C = ch[c];
         double ar = 0.0, ai = 0.0;
-        for (int64_t i = C.start + threadIdx.x; i < C.start + C.len; i += blockDim.x) {
-            const double2 a = x[i], b = y[i];
-            ar += a.x * b.x + a.y * b.y;
-            ai += a.x * b.y - a.y * b.x;
-        }
-        ar = wave_sum(ar);
-        ai = wave_sum(ai);
-        if ((threadIdx.x & 63) == 0) {
-            sr[wave_in_block()] = ar;
-            si[wave_in_block()] = ai;
-        }
-        __syncthreads();
-        if (threadIdx.x == 0)
-            part[c] = make_double2((sr[0] + sr[1]) + (sr[2] + sr[3]), (si[0] + si[1]) + (si[2] + si[3]));
-        __syncthreads();
+        for (int64_t i = C.start + threadIdx.x; i < C.start + C.len; i += 256)
+            dot_add(x[i], y[i], ar, ai);
+        const double2 v = block_sum2(ar, ai, s);
+        if (threadIdx.x == 0) part[c] = v;
     }
 }
 
-// out[caller index] = sum of the instance's chunk partials (chunks of an
-// instance are contiguous and in order); sqrt_real: write sqrt(Re) as double.
-__global__ void k_seg_final(const BatchChunk *__restrict__ ch, int64_t nchunks, int count,
-                            const int32_t *__restrict__ sorted, const double2 *__restrict__ part,
-                            double2 *__restrict__ out_c, double *__restrict__ out_norm)
+// out[caller index] = sum of the instance's chunk partials (one block per
+// instance); out_norm: sqrt(Re) as double.
+__global__ __launch_bounds__(256) void k_seg_final(const BatchInst *__restrict__ inst,
+                                                    const BatchChunk *__restrict__ ch,
+                                                    const int32_t *__restrict__ sorted,
+                                                    const double2 *__restrict__ part,
+                                                    double2 *__restrict__ out_c,
+                                                    double *__restrict__ out_norm)
 {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= count) return;
-    // binary search for the first chunk of sorted instance j
-    int64_t lo = 0, hi = nchunks;
-    while (lo < hi) {
-        const int64_t mid = (lo + hi) >> 1;
-        if (ch[mid].inst < j) lo = mid + 1;
-        else hi = mid;
+    __shared__ double s[8];
+    const BatchChunk C = ch[inst[blockIdx.x].chunk0];
+    const double2 v = seg_total(part, C.first, C.count, s);
+    if (threadIdx.x) return;
+    const int dst = sorted[blockIdx.x];
+    if (out_c) out_c[dst] = v;
+    if (out_norm) out_norm[dst] = sqrt(v.x);
+}
+
+// w - a v - b v_prev at element i
+__device__ __forceinline__ double2 seg_orth_at(double2 x, const double2 &y,
+                                               const double2 *__restrict__ vp, int64_t i, double a,
+                                               double b)
+{
+    x.x = fma(-a, y.x, x.x);
+    x.y = fma(-a, y.y, x.y);
+    if (b != 0.0) {
+        const double2 z = vp[i];
+        x.x = fma(-b, z.x, x.x);
+        x.y = fma(-b, z.y, x.y);
     }
-    double sr = 0.0, si = 0.0;
-    for (int64_t c = lo; c < nchunks && ch[c].inst == j; ++c) {
-        sr += part[c].x;
-        si += part[c].y;
+    return x;
+}
+
+// One three-term step on a chunk's instance, as k_seg_final(alpha), k_seg_orth
+// and k_seg_dot_partial(w, w) leave it, in one pass: alpha from the partials of
+// <v|w>, w -= Re(alpha) v + beta v_prev, and the partials of the norm.
+__global__ __launch_bounds__(256) void k_seg_step(const BatchChunk *__restrict__ ch,
+                                                   int64_t nchunks,
+                                                   const int32_t *__restrict__ sorted,
+                                                   double2 *__restrict__ w,
+                                                   const double2 *__restrict__ v,
+                                                   const double2 *__restrict__ vp,
+                                                   const double2 *__restrict__ part,
+                                                   double2 *__restrict__ alpha,
+                                                   const double *__restrict__ beta,
+                                                   double2 *__restrict__ norm)
+{
+    __shared__ double s[8];
+    for (int64_t c = blockIdx.x; c < nchunks; c += gridDim.x) {
+        const BatchChunk C = ch[c];
+        const int dst = sorted[C.inst];
+        const double2 al = seg_total(part, C.first, C.count, s);
+        if (c == C.first && threadIdx.x == 0) alpha[dst] = al;
+        const double a = al.x, b = vp ? beta[dst] : 0.0;
+        double ar = 0.0, ai = 0.0;
+        for (int64_t i = C.start + threadIdx.x; i < C.start + C.len; i += 256) {
+            const double2 x = seg_orth_at(w[i], v[i], vp, i, a, b);
+            w[i] = x;
+            dot_add(x, x, ar, ai);
+        }
+        const double2 n = block_sum2(ar, ai, s);
+        if (threadIdx.x == 0) norm[c] = n;
     }
-    const int dst = sorted[j];
-    if (out_c) out_c[dst] = make_double2(sr, si);
-    if (out_norm) out_norm[dst] = sqrt(sr);
+}
+
+// out = w / beta per instance, beta from the partials of the norm (as
+// k_seg_final and k_seg_scale leave it).  `counters`, if any, are zeroed for
+// the apply that follows.
+__global__ __launch_bounds__(256) void k_seg_norm_scale(const BatchChunk *__restrict__ ch,
+                                                         int64_t nchunks,
+                                                         const int32_t *__restrict__ sorted,
+                                                         const double2 *__restrict__ w,
+                                                         const double2 *__restrict__ norm,
+                                                         double *__restrict__ beta,
+                                                         double2 *__restrict__ out,
+                                                         uint32_t *__restrict__ counters)
+{
+    __shared__ double s[8];
+    if (blockIdx.x == 0 && threadIdx.x < kMaxGroups) counters[threadIdx.x] = 0;
+    for (int64_t c = blockIdx.x; c < nchunks; c += gridDim.x) {
+        const BatchChunk C = ch[c];
+        const double b = sqrt(seg_total(norm, C.first, C.count, s).x);
+        if (c == C.first && threadIdx.x == 0) beta[sorted[C.inst]] = b;
+        const double inv = b > 0.0 ? 1.0 / b : 0.0;
+        for (int64_t i = C.start + threadIdx.x; i < C.start + C.len; i += 256) {
+            const double2 x = w[i];
+            out[i] = make_double2(x.x * inv, x.y * inv);
+        }
+    }
 }
 
 // w -= Re(alpha_i) v + beta_i v_prev per instance segment (three-term step)
@@ -357,18 +428,8 @@ __global__ __launch_bounds__(256) void k_seg_orth(const BatchChunk *__restrict__
         const int dst = sorted[C.inst];
         const double a = alpha[dst].x;
         const double b = (vp && beta) ? beta[dst] : 0.0;
-        for (int64_t i = C.start + threadIdx.x; i < C.start + C.len; i += blockDim.x) {
-            double2 x = w[i];
-            const double2 y = v[i];
-            x.x -= a * y.x;
-            x.y -= a * y.y;
-            if (b != 0.0) {
-                const double2 z = vp[i];
-                x.x -= b * z.x;
-                x.y -= b * z.y;
-            }
-            w[i] = x;
-        }
+        for (int64_t i = C.start + threadIdx.x; i < C.start + C.len; i += blockDim.x)
+            w[i] = seg_orth_at(w[i], v[i], vp, i, a, b);
     }
 }
 
@@ -398,20 +459,25 @@ struct PlanLayout {
 };
 
 static int plan_layout(int32_t count, const mc_batch_item *items, int64_t *nchunks_out,
-                       int64_t *coef_elems_out, PlanLayout *L)
+                       int64_t *chunk_out, int64_t *coef_elems_out, PlanLayout *L)
 {
-    int64_t nchunks = 0, coef = 0;
+    int64_t nchunks = 0, coef = 0, total = 0;
+    for (int i = 0; i < count; ++i) {
+        if (!items[i].tables) return MC_EINVAL;
+        total += items[i].tables->dim;
+    }
+    const int64_t chunk = batch_chunk(total);
+    *chunk_out = chunk;
     for (int i = 0; i < count; ++i) {
         const mc_tables *t = items[i].tables;
-        if (!t) return MC_EINVAL;
-        nchunks += (t->dim + kChunk - 1) / kChunk;
+        nchunks += (t->dim + chunk - 1) / chunk;
         coef += batch_coef_elems(t);
     }
     L->inst = 0;
     L->prefix = align256(L->inst + sizeof(BatchInst) * count);
     L->chunks = align256(L->prefix + sizeof(int64_t) * (count + 1));
     L->partials = align256(L->chunks + sizeof(BatchChunk) * nchunks);
-    L->sorted = align256(L->partials + sizeof(double2) * nchunks);
+    L->sorted = align256(L->partials + sizeof(double2) * 2 * nchunks);
     L->pos = align256(L->sorted + sizeof(int32_t) * count);
     L->counters = align256(L->pos + sizeof(int32_t) * count);
     L->coef = align256(L->counters + sizeof(uint32_t) * kMaxGroups);
@@ -431,8 +497,8 @@ int mc_batch_plan_size(int32_t count, const mc_batch_item *items, size_t *bytes)
 {
     if (count < 1 || !items || !bytes) return MC_EINVAL;
     PlanLayout L;
-    int64_t nch, coef;
-    const int st = plan_layout(count, items, &nch, &coef, &L);
+    int64_t nch, chunk, coef;
+    const int st = plan_layout(count, items, &nch, &chunk, &coef, &L);
     if (st) return st;
     *bytes = L.total;
     return MC_OK;
@@ -460,8 +526,8 @@ int mc_batch_create(int32_t count, const mc_batch_item *items, const mc_batch_sc
         if (t->M > 8 || occ_width(t->N) != 1 || t->dim * 16 > (int64_t)0xFFFFFFFFu) return MC_EINVAL;
     }
     PlanLayout L;
-    int64_t nchunks, coef_elems;
-    int st = plan_layout(count, items, &nchunks, &coef_elems, &L);
+    int64_t nchunks, chunk, coef_elems;
+    int st = plan_layout(count, items, &nchunks, &chunk, &coef_elems, &L);
     if (st) return st;
     if (plan_bytes < L.total) return MC_ENOMEM;
     const int bpc = sched && sched->blocks_per_cu > 0 ? sched->blocks_per_cu : 2;
@@ -484,12 +550,11 @@ int mc_batch_create(int32_t count, const mc_batch_item *items, const mc_batch_sc
     });
     mc_batch *b = (mc_batch *)calloc(1, sizeof(mc_batch));
     if (!b) return MC_ENOMEM;
-    b->solo = (SoloLaunch *)calloc((size_t)count, sizeof(SoloLaunch));
-    if (!b->solo) {
+    b->own = (OwnLaunch *)calloc((size_t)count, sizeof(OwnLaunch));
+    if (!b->own) {
         free(b);
         return MC_ENOMEM;
     }
-    const int64_t solo_min = sched && sched->solo_tiles > 0 ? sched->solo_tiles : 0;
     b->count = count;
     b->order = order;
     std::vector<int32_t> pos(count);
@@ -508,7 +573,6 @@ int mc_batch_create(int32_t count, const mc_batch_item *items, const mc_batch_sc
         I.N = t->N;
         I.M = t->M;
         I.kind = kind_of(t);
-        I.pad = 0;
         I.dim = t->dim;
         I.tiles = t->tiles;
         I.cap = t->t2_d ? t->t2_entries : 0;
@@ -527,25 +591,16 @@ int mc_batch_create(int32_t count, const mc_batch_item *items, const mc_batch_sc
         const bool block = batch_block(t);
         I.btab = block ? (int32_t *)(coef + cpos + batch_const_elems(t->M)) : nullptr;
         cpos += batch_coef_elems(t);
-        // a large instance, and one of the four-row kernel, gets a launch of
-        // its own; the rest join groups
-        if (block || (solo_min > 0 && t->tiles >= solo_min)) {
-            SoloLaunch &L1 = b->solo[b->nsolo++];
-            L1.j = j;
-            L1.M = t->M;
-            L1.kind = I.kind;
-            L1.N = t->N;
-            L1.tiles = t->tiles;
-            L1.dim = t->dim;
-            L1.cap = I.cap;
-            L1.gp_off = I.gp_off;
-            L1.hp_off = I.hp_off;
-            L1.occ = I.occ;
-            L1.t1 = I.t1;
-            L1.pmask = I.pmask;
-            L1.t2_off = I.t2_off;
-            L1.t2 = I.t2;
-            L1.btab = I.btab;
+        // an instance of the four-row kernel gets a launch of its own; the
+        // rest join groups
+        if (block) {
+            OwnLaunch &o = b->own[b->nown++];
+            o.j = j;
+            o.M = t->M;
+            o.N = t->N;
+            o.dim = t->dim;
+            o.gp_off = I.gp_off;
+            o.btab = I.btab;
             prefix[j] = 0;
             continue;
         }
@@ -573,15 +628,19 @@ int mc_batch_create(int32_t count, const mc_batch_item *items, const mc_batch_sc
             voff += items[i].tables->dim;
         }
         for (int j = 0; j < count; ++j) inst[j].vec_off = off[sorted[j]];
-        for (int k = 0; k < b->nsolo; ++k) b->solo[k].vec_off = inst[b->solo[k].j].vec_off;
+        for (int k = 0; k < b->nown; ++k) b->own[k].vec_off = inst[b->own[k].j].vec_off;
         for (int j = 0; j < count; ++j) {
             const int64_t D = inst[j].dim;
-            for (int64_t s = 0; s < D; s += kChunk) {
+            const int32_t first = (int32_t)chunks.size();
+            inst[j].chunk0 = first;
+            for (int64_t s = 0; s < D; s += chunk) {
                 BatchChunk c;
                 c.inst = j;
+                c.first = first;
+                c.count = (int32_t)((D + chunk - 1) / chunk);
                 c.pad = 0;
                 c.start = inst[j].vec_off + s;
-                c.len = D - s < kChunk ? D - s : kChunk;
+                c.len = D - s < chunk ? D - s : chunk;
                 chunks.push_back(c);
             }
         }
@@ -623,7 +682,7 @@ int mc_batch_create(int32_t count, const mc_batch_item *items, const mc_batch_sc
     // host staging vectors go out of scope: wait for the copies
     if (!st) st = set_hip_error(hipStreamSynchronize(s));
     if (st) {
-        free(b->solo);
+        free(b->own);
         free(b);
         return st;
     }
@@ -633,50 +692,34 @@ int mc_batch_create(int32_t count, const mc_batch_item *items, const mc_batch_sc
 
 int mc_batch_destroy(mc_batch *b)
 {
-    if (b) free(b->solo);
+    if (b) free(b->own);
     free(b);
     return MC_OK;
 }
 
 int64_t mc_batch_vector_length(const mc_batch *b) { return b ? b->total_len : (int64_t)MC_EINVAL; }
 
-int mc_batch_apply_H(const mc_batch *b, const double *C_d, double *HC_d, mc_stream stream)
+static void batch_stage(const mc_batch *b, hipStream_t s)
 {
-    if (!b || !C_d || !HC_d) return MC_EINVAL;
-    if (overlaps(C_d, (size_t)b->total_len * 16, HC_d, (size_t)b->total_len * 16)) return MC_EINVAL;
-    hipStream_t s = (hipStream_t)stream;
     hipLaunchKernelGGL(k_batch_prep, dim3(5, b->count), dim3(256), 0, s, b->inst_d, b->counters_d);
-    for (int k = 0; k < b->nsolo; ++k) {
-        const SoloLaunch &L1 = b->solo[k];
-        const int M = L1.M;
-        if (L1.btab) {
-            const int st = apply_block_run(L1.N, M, L1.dim, b->coef_d + L1.gp_off, L1.btab,
-                                           C_d + 2 * L1.vec_off, HC_d + 2 * L1.vec_off, s);
-            if (st) return st;
-            continue;
-        }
-        const int64_t nblocks = (L1.tiles + 3) / 4;
-#define MC_SOLO_LAUNCH(KIND)                                                                    \
-    hipLaunchKernelGGL((k_batch_solo<MT, KIND>), dim3(nblocks), dim3(256), 0, s, L1.N, L1.dim,      \
-                       L1.tiles, nblocks, L1.cap, L1.occ, L1.t1, L1.pmask, L1.t2_off, L1.t2,     \
-                       (const double2 *)b->coef_d + L1.gp_off,                                   \
-                       (const double2 *)b->coef_d + L1.hp_off,                                   \
-                       (const double2 *)C_d + L1.vec_off, (double2 *)HC_d + L1.vec_off)
-        switch (L1.kind) {
-        case kPaperMap: MC_DISPATCH_M(M, if constexpr (MT > 0) MC_SOLO_LAUNCH(kPaperMap)); break;
-        case kPaperChain: MC_DISPATCH_M(M, if constexpr (MT > 0) MC_SOLO_LAUNCH(kPaperChain)); break;
-        case kSplitMap: MC_DISPATCH_M(M, if constexpr (MT > 0) MC_SOLO_LAUNCH(kSplitMap)); break;
-        case kDirect: MC_DISPATCH_M(M, if constexpr (MT > 0) MC_SOLO_LAUNCH(kDirect)); break;
-        default: MC_DISPATCH_M(M, if constexpr (MT > 0) MC_SOLO_LAUNCH(kSplitChain)); break;
-        }
-#undef MC_SOLO_LAUNCH
+}
+
+// The apply on staged constants and zeroed counters.
+static int batch_apply_staged(const mc_batch *b, const double *C_d, double *HC_d, hipStream_t s)
+{
+    for (int k = 0; k < b->nown; ++k) {
+        const OwnLaunch &o = b->own[k];
+        const int st = apply_block_run(o.N, o.M, o.dim, b->coef_d + o.gp_off, o.btab,
+                                       C_d + 2 * o.vec_off, HC_d + 2 * o.vec_off, s);
+        if (st) return st;
     }
     for (int gi = 0; gi < b->ngroups; ++gi) {
         const int M = b->group_M[gi];
 #define MC_BATCH_LAUNCH(KIND)                                                                   \
     hipLaunchKernelGGL((k_batch_apply<MT, KIND>), dim3(b->group_blocks[gi]), dim3(256), 0, s,   \
                        b->inst_d, b->tile_prefix_d, b->group_first[gi], b->group_count[gi],     \
-                       b->group_tiles[gi], b->group_blocks[gi], b->order, b->counters_d + gi,   \
+                       b->group_tiles[gi], b->group_blocks[gi], b->order,                       \
+                       batch_grab(b->group_tiles[gi], b->group_blocks[gi]), b->counters_d + gi, \
                        (const double2 *)b->coef_d, (const double2 *)C_d, (double2 *)HC_d)
         switch (b->group_kind[gi]) {
         case kPaperMap: MC_DISPATCH_M(M, if constexpr (MT > 0) MC_BATCH_LAUNCH(kPaperMap)); break;
@@ -690,6 +733,14 @@ int mc_batch_apply_H(const mc_batch *b, const double *C_d, double *HC_d, mc_stre
     return launch_status();
 }
 
+int mc_batch_apply_H(const mc_batch *b, const double *C_d, double *HC_d, mc_stream stream)
+{
+    if (!b || !C_d || !HC_d) return MC_EINVAL;
+    if (overlaps(C_d, (size_t)b->total_len * 16, HC_d, (size_t)b->total_len * 16)) return MC_EINVAL;
+    batch_stage(b, (hipStream_t)stream);
+    return batch_apply_staged(b, C_d, HC_d, (hipStream_t)stream);
+}
+
 int mc_batch_dot(const mc_batch *b, const double *x_d, const double *y_d, double *out_d,
                  mc_stream stream)
 {
@@ -698,9 +749,8 @@ int mc_batch_dot(const mc_batch *b, const double *x_d, const double *y_d, double
     const int64_t grid = b->nchunks < 4096 ? b->nchunks : 4096;
     hipLaunchKernelGGL(k_seg_dot_partial, dim3(grid), dim3(256), 0, s, b->chunks_d, b->nchunks,
                        (const double2 *)x_d, (const double2 *)y_d, b->partials_d);
-    hipLaunchKernelGGL(k_seg_final, dim3((b->count + 255) / 256), dim3(256), 0, s, b->chunks_d,
-                       b->nchunks, b->count, b->sorted_d, b->partials_d, (double2 *)out_d,
-                       (double *)nullptr);
+    hipLaunchKernelGGL(k_seg_final, dim3(b->count), dim3(256), 0, s, b->inst_d, b->chunks_d,
+                       b->sorted_d, b->partials_d, (double2 *)out_d, (double *)nullptr);
     return launch_status();
 }
 
@@ -724,9 +774,8 @@ int mc_batch_normalize(const mc_batch *b, const double *w_d, double *out_d, doub
     const int64_t grid = b->nchunks < 4096 ? b->nchunks : 4096;
     hipLaunchKernelGGL(k_seg_dot_partial, dim3(grid), dim3(256), 0, s, b->chunks_d, b->nchunks,
                        (const double2 *)w_d, (const double2 *)w_d, b->partials_d);
-    hipLaunchKernelGGL(k_seg_final, dim3((b->count + 255) / 256), dim3(256), 0, s, b->chunks_d,
-                       b->nchunks, b->count, b->sorted_d, b->partials_d, (double2 *)nullptr,
-                       beta_d);
+    hipLaunchKernelGGL(k_seg_final, dim3(b->count), dim3(256), 0, s, b->inst_d, b->chunks_d,
+                       b->sorted_d, b->partials_d, (double2 *)nullptr, beta_d);
     const int64_t grid2 = b->nchunks < 8192 ? b->nchunks : 8192;
     hipLaunchKernelGGL(k_seg_scale, dim3(grid2), dim3(256), 0, s, b->chunks_d, b->nchunks,
                        b->sorted_d, (const double2 *)w_d, beta_d, (double2 *)out_d);
@@ -756,18 +805,32 @@ int mc_batch_lanczos_graph(const mc_batch *b, int32_t steps, const double *v0_d,
     if (cs != hipStreamCaptureStatusNone) return MC_EINVAL;
     st = set_hip_error(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
     if (st) return st;
-    // the recurrence; every call below only enqueues kernels
+    // the recurrence; every call below only enqueues kernels.  The constants
+    // are staged once per replay, and a step after its product takes three
+    // passes with the sums of the calls it stands for (mc_batch_dot,
+    // mc_batch_lanczos_orth, mc_batch_normalize: seven launches).
+    const int64_t nch = b->nchunks, grid = nch < 8192 ? nch : 8192;
+    double2 *dots = b->partials_d, *norms = dots + nch;
+    batch_stage(b, s);
     int rec = mc_batch_normalize(b, v0_d, V[0], beta_d + (int64_t)steps * b->count, stream);
     for (int32_t j = 0; j < steps && rec == MC_OK; ++j) {
         double *cur = V[j % 3], *prev = V[(j + 2) % 3], *nxt = V[(j + 1) % 3];
         double *alpha_j = alpha_d + (int64_t)2 * j * b->count;
-        rec = mc_batch_apply_H(b, cur, w_d, stream);
-        if (rec == MC_OK) rec = mc_batch_dot(b, cur, w_d, alpha_j, stream);
-        if (rec == MC_OK)
-            rec = mc_batch_lanczos_orth(b, w_d, cur, j > 0 ? prev : nullptr, alpha_j,
-                                        j > 0 ? beta_d + (int64_t)(j - 1) * b->count : nullptr,
-                                        stream);
-        if (rec == MC_OK) rec = mc_batch_normalize(b, w_d, nxt, beta_d + (int64_t)j * b->count, stream);
+        rec = batch_apply_staged(b, cur, w_d, s);
+        if (rec != MC_OK) break;
+        hipLaunchKernelGGL(k_seg_dot_partial, dim3(grid), dim3(256), 0, s, b->chunks_d, nch,
+                           (const double2 *)cur, (const double2 *)w_d, dots);
+        hipLaunchKernelGGL(k_seg_step, dim3(grid), dim3(256), 0, s, b->chunks_d, nch, b->sorted_d,
+                           (double2 *)w_d, (const double2 *)cur,
+                           j > 0 ? (const double2 *)prev : (const double2 *)nullptr,
+                           (const double2 *)dots, (double2 *)alpha_j,
+                           j > 0 ? (const double *)beta_d + (int64_t)(j - 1) * b->count
+                                 : (const double *)nullptr,
+                           norms);
+        hipLaunchKernelGGL(k_seg_norm_scale, dim3(grid), dim3(256), 0, s, b->chunks_d, nch,
+                           b->sorted_d, (const double2 *)w_d, (const double2 *)norms,
+                           beta_d + (int64_t)j * b->count, (double2 *)nxt, b->counters_d);
+        rec = launch_status();
     }
     hipGraph_t graph = nullptr;
     st = set_hip_error(hipStreamEndCapture(s, &graph));
