@@ -247,6 +247,13 @@ int mc_workspace_size(int32_t N, int32_t M, int32_t op, size_t *bytes);
  * HC_d must not overlap C_d (MC_EINVAL).  ws_d: mc_workspace_size(APPLY);
  * the call stages h and G' there, so concurrent calls need separate ws.
  * No symmetry of h or g is assumed. */
+/* Spaces of at least 131,072 rows (786,432 for M = 8) and at most 2^27, 3 <= M
+ * <= 8 and N < 4096, are evaluated four rows per lane with every target in
+ * closed form, as mc_apply_H_direct does there: it is faster than reading the
+ * tables, which are checked and not read.  Results agree with the table-driven
+ * kernels up to rounding order.  The same holds for mc_apply_H_adjoint and for
+ * the instances of a batch.  A workspace smaller than mc_workspace_size's, if
+ * it holds the staged constants, takes the table-driven kernels. */
 /* Table reads of the apply through a double-jump map (host query, no
  * device work).  Within a run of rows (consecutive indices that differ by one
  * particle moved between orbitals 0 and 1, Eq. TotalCost) a jump's target is
@@ -299,8 +306,8 @@ int mc_apply_H_sparse(int32_t N, int32_t M, const double *h_d, const double *g_d
  * (N+3)*8 <= 65536 for M >= 5 (an LDS table of square roots; M <= 4 keeps
  * them in registers); ws_d: mc_workspace_size(APPLY) bytes (staged constants,
  * so concurrent calls need separate ws); HC_d must not overlap C_d.  The
- * terms and their order are those of mc_apply_H on reduced-form tables, so
- * the results agree with it up to the sign of zero. */
+ * terms are those of mc_apply_H on reduced-form tables, so the results agree
+ * with it up to rounding order; batched instances get the same bits. */
 int mc_apply_H_direct(int32_t N, int32_t M, const double *h_d, const double *g_d,
                       const double *C_d, double *HC_d, void *ws_d, size_t ws_bytes,
                       mc_stream stream);
@@ -426,13 +433,12 @@ typedef struct mc_batch_schedule {
                                 wavefront takes a contiguous range of items; 2: each
                                 XCD takes a contiguous share of the items (in
                                 proportion to its blocks) and its wavefronts
-                                interleave within it; 3: wavefronts take 8 items at
-                                a time from a per-group counter in the plan (zeroed
+                                interleave within it; 3: wavefronts take up to 8
+                                items at a time from a per-group counter in the plan (zeroed
                                 by a kernel at the start of each apply) */
-    int32_t solo_tiles;      /* > 0: an instance of at least this many 64-row tiles
-                                gets a launch of its own (one wavefront per tile, like
-                                mc_apply_H) instead of joining its group's persistent
-                                kernel; 0: every instance joins its group */
+    int32_t solo_tiles;      /* taken and ignored: an instance that the four-row kernel
+                                serves (see mc_apply_H) always gets a launch of its
+                                own, every other one joins its group */
     int32_t reserved;
 } mc_batch_schedule;
 

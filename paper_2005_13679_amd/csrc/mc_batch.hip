@@ -55,7 +55,7 @@ static bool table_free(const mc_tables *t)
 
 // Staged complex constants of an instance of M orbitals, enough for either
 // form, and with the tables of the four-row kernel behind them where the
-// instance takes it (as mc_apply_H_direct would).
+// instance takes it (as mc_apply_H and mc_apply_H_direct would).
 inline int64_t batch_const_elems(int M)
 {
     const int64_t paper = (int64_t)npairs(M) * M * M + (int64_t)M * M;
@@ -64,7 +64,7 @@ inline int64_t batch_const_elems(int M)
 }
 inline bool batch_block(const mc_tables *t)
 {
-    return table_free(t) && block_serves(t->N, t->M, t->dim);
+    return block_serves(t->N, t->M, t->dim);
 }
 inline int64_t batch_coef_elems(const mc_tables *t)
 {
@@ -147,7 +147,7 @@ __global__ void k_batch_prep(const BatchInst *__restrict__ inst, uint32_t *__res
     }
     const int first = blockIdx.x * blockDim.x + threadIdx.x;
     const int stride = (gridDim.x - 1) * blockDim.x;
-    if (I.kind == kSplitMap || I.kind == kSplitChain || I.kind == kDirect) {
+    if (I.kind == kSplitMap || I.kind == kSplitChain || I.kind == kDirect || I.btab) {
         stage_split_constants(M, 0, I.g, I.h, I.gp, first, stride);
         return;
     }

@@ -82,13 +82,11 @@ static int apply_direct_common(int32_t N, int32_t M, const double *h_d, const do
     if (D < 0 || D >= ((int64_t)1 << 31)) return MC_ERANGE;
     if (!h_d || !g_d || !C_d || !HC_d || !ws_d) return MC_EINVAL;
     if (overlaps(C_d, (size_t)D * 16, HC_d, (size_t)D * 16)) return MC_EINVAL;
-    size_t need = 0;
-    mc_workspace_size(N, M, MC_OP_APPLY, &need);
-    if (ws_bytes < need) return MC_ENOMEM;
+    if (ws_bytes < apply_workspace_least(M)) return MC_ENOMEM;
     const size_t sqb = (size_t)(N + 3) * 8;
     if (M >= MC_LDS_ROOTS_FROM && sqb > 65536) return MC_EINVAL;
     hipStream_t s = (hipStream_t)stream;
-    if (block_serves(N, M, D))
+    if (block_serves(N, M, D) && ws_bytes >= block_workspace(N, M))
         return apply_block_launch(N, M, D, h_d, g_d, adjoint, C_d, HC_d, ws_d, s);
     double2 *cf = (double2 *)ws_d;
     launch_prep_split(M, adjoint, g_d, h_d, cf, s);

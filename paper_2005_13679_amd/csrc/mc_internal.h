@@ -68,11 +68,14 @@ size_t gram_table_workspace(int32_t N, int32_t M, int L);
 int rho1_generic(int32_t N, int32_t M, const mc_tables *t, const double *C_d, double *rho1_d,
                  void *ws_d, size_t ws_bytes, mc_stream stream);
 
-// Table-free H.C with four rows per lane (mc_block.h): whether it serves the
-// space, its workspace bytes, staging and launch, and the launch alone on
-// staged constants `cf` and tables `tab`.
+// H.C with four rows per lane and targets in closed form (mc_block.h): whether
+// it serves the space, its workspace bytes, staging and launch, and the launch
+// alone on staged constants `cf` and tables `tab`.
 bool block_serves(int32_t N, int32_t M, int64_t D);
 size_t block_workspace(int32_t N, int32_t M);
+// Workspace bytes without which no apply of M orbitals runs; one between
+// these and mc_workspace_size's takes the one-row kernels.
+size_t apply_workspace_least(int32_t M);
 int apply_block_launch(int32_t N, int32_t M, int64_t D, const double *h_d, const double *g_d,
                        int adjoint, const double *C_d, double *HC_d, void *ws_d, hipStream_t s);
 int apply_block_run(int32_t N, int32_t M, int64_t D, const double2 *cf, const int32_t *tab,

@@ -690,17 +690,11 @@ int mc_workspace_size(int32_t N, int32_t M, int32_t op, size_t *bytes)
     const int64_t D = dim_checked(N, M);
     if (D < 0) return MC_ERANGE;
     const int64_t tiles = (D + kTile - 1) / kTile;
-    const int64_t P = npairs(M);
     switch (op) {
-    case MC_OP_APPLY: {
-        // staged constants of either form (plus the sparse lists of the
-        // case-split form)
-        const int64_t paper = (P * M * M + M * M) * 16;
-        const int64_t split = M <= 8 ? split_total(M) * 16 + kSlInts * 4 : 0;
-        *bytes = (size_t)(paper > split ? paper : split);
+    case MC_OP_APPLY:
+        *bytes = apply_workspace_least(M);
         if (block_serves(N, M, D) && block_workspace(N, M) > *bytes) *bytes = block_workspace(N, M);
         return MC_OK;
-    }
     case MC_OP_RHO1:
         *bytes = M > 8 ? (size_t)rho_waves(tiles) * M * M * 16 : gram_table_workspace(N, M, 1);
         return *bytes ? MC_OK : MC_ERANGE;
@@ -714,6 +708,23 @@ int mc_workspace_size(int32_t N, int32_t M, int32_t op, size_t *bytes)
     }
 }
 
+}  // extern "C"
+
+namespace mc {
+
+size_t apply_workspace_least(int32_t M)
+{
+    // staged constants of either form (plus the sparse lists of the
+    // case-split form)
+    const size_t paper = ((size_t)npairs(M) * M * M + (size_t)M * M) * 16;
+    const size_t split = M <= 8 ? (size_t)split_total(M) * 16 + kSlInts * 4 : 0;
+    return paper > split ? paper : split;
+}
+
+}  // namespace mc
+
+extern "C" {
+
 static int apply_common(int32_t N, int32_t M, const double *h_d, const double *g_d,
                         const mc_tables *t, const double *C_d, double *HC_d, void *ws_d,
                         size_t ws_bytes, int adjoint, mc_stream stream)
@@ -726,11 +737,17 @@ static int apply_common(int32_t N, int32_t M, const double *h_d, const double *g
     if (!h_d || !g_d || !C_d || !HC_d || !ws_d) return MC_EINVAL;
     const int64_t D = t->dim;
     if (overlaps(C_d, (size_t)D * 16, HC_d, (size_t)D * 16)) return MC_EINVAL;
-    size_t need = 0;
-    mc_workspace_size(N, M, MC_OP_APPLY, &need);
-    if (ws_bytes < need) return MC_ENOMEM;
+    if (ws_bytes < apply_workspace_least(M)) return MC_ENOMEM;
     if (M > 8 && (chained || (size_t)5 * M * kTile * 8 > 65536)) return MC_EINVAL;
     hipStream_t s = (hipStream_t)stream;
+    // Spaces that the four-row kernel serves are fastest with every target in
+    // closed form, whatever the tables hold: N=200, M=5 7.9 ms through the
+    // reduced map, 10.7 through the paper's map, 9.5 and 22.4 chained, 3.4 so;
+    // N=50, M=6 0.89, 1.42 and 0.41.  Its lower limits were measured against
+    // the table-free kernel; through the maps the smaller spaces take about as
+    // long as that.
+    if (block_serves(N, M, D) && ws_bytes >= block_workspace(N, M))
+        return apply_block_launch(N, M, D, h_d, g_d, adjoint, C_d, HC_d, ws_d, s);
     if (t->form == MC_FORM_REDUCED) {
         if (M > 8) return MC_EINVAL;
         const size_t sqb = (size_t)(N + 3) * 8;
@@ -844,9 +861,7 @@ int mc_apply_H_sparse(int32_t N, int32_t M, const double *h_d, const double *g_d
     if (!h_d || !g_d || !C_d || !HC_d || !ws_d) return MC_EINVAL;
     const int64_t D = t->dim;
     if (overlaps(C_d, (size_t)D * 16, HC_d, (size_t)D * 16)) return MC_EINVAL;
-    size_t need = 0;
-    mc_workspace_size(N, M, MC_OP_APPLY, &need);
-    if (ws_bytes < need) return MC_ENOMEM;
+    if (ws_bytes < apply_workspace_least(M)) return MC_ENOMEM;
     const size_t sqb = (size_t)(N + 3) * 8;
     if (sqb > 65536) return MC_EINVAL;
     hipStream_t s = (hipStream_t)stream;
