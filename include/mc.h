@@ -247,13 +247,14 @@ int mc_workspace_size(int32_t N, int32_t M, int32_t op, size_t *bytes);
  * HC_d must not overlap C_d (MC_EINVAL).  ws_d: mc_workspace_size(APPLY);
  * the call stages h and G' there, so concurrent calls need separate ws.
  * No symmetry of h or g is assumed. */
-/* Spaces of at least 131,072 rows (786,432 for M = 8) and at most 2^27, 3 <= M
- * <= 8 and N < 4096, are evaluated four rows per lane with every target in
+/* Spaces of more than 65,536 rows (M <= 8) are evaluated with every target in
  * closed form, as mc_apply_H_direct does there: it is faster than reading the
- * tables, which are checked and not read.  Results agree with the table-driven
- * kernels up to rounding order.  The same holds for mc_apply_H_adjoint and for
- * the instances of a batch.  A workspace smaller than mc_workspace_size's, if
- * it holds the staged constants, takes the table-driven kernels. */
+ * tables, which are checked and not read.  From 131,072 rows (786,432 for M =
+ * 8) to 2^27, with M >= 3 and N < 4096, four rows per lane; else one, and so
+ * too with a workspace smaller than mc_workspace_size's that holds the staged
+ * constants.  Results agree with the table-driven kernels up to rounding
+ * order.  The same holds for mc_apply_H_adjoint and for the instances of a
+ * batch. */
 /* Table reads of the apply through a double-jump map (host query, no
  * device work).  Within a run of rows (consecutive indices that differ by one
  * particle moved between orbitals 0 and 1, Eq. TotalCost) a jump's target is

@@ -17,8 +17,13 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmc.so")
 
-SOURCES = ["mc_host.hip", "mc_tables.hip", "mc_ops.hip", "mc_direct.hip", "mc_block.hip", "mc_batch.hip",
-           "mc_krylov.hip", "mc_gram_direct.hip", "mc_gram_tables.hip"]
+# (source, object, extra flags); mc_tiles.hip holds the kernels of one orbital
+# count and part per compilation, the longest ones first
+SOURCES = [("mc_tiles.hip", f"mc_tiles_{m}_{p}", (f"-DMC_TILES_M={m}", f"-DMC_TILES_PART={p}"))
+           for m in range(8, 0, -1) for p in (2, 0, 1)]
+SOURCES += [(f"{n}.hip", n, ()) for n in
+            ("mc_ops", "mc_block", "mc_host", "mc_tables", "mc_direct", "mc_batch", "mc_krylov",
+             "mc_gram_direct", "mc_gram_tables")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
@@ -40,12 +45,13 @@ FLAGS = [
 ]
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
-    cmd = [HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+def _compile(unit) -> str:
+    src, name, extra = unit
+    obj = os.path.join(BUILD, name + ".o")
+    cmd = [HIPCC, *FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
-        raise RuntimeError(f"hipcc failed for {src}:\n{r.stderr}")
+        raise RuntimeError(f"hipcc failed for {src} ({name}):\n{r.stderr}")
     return obj
 
 

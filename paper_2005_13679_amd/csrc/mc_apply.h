@@ -124,6 +124,66 @@ __device__ __forceinline__ void load_row(const OccT *__restrict__ occ, int64_t t
     R.init(n, sq);
 }
 
+// A wave-uniform true that the compiler cannot see through.  Branching on
+// it puts each batch of a long straight-line stream into a basic block of its
+// own; within one huge block the instruction scheduler issues every load of
+// the stream first and keeps all gathered values live (hundreds of spilled
+// registers), across blocks it cannot move them.
+__device__ __forceinline__ bool opaque_true()
+{
+    int v;
+    asm volatile("s_mov_b32 %0, 1" : "=s"(v));
+    return v != 0;
+}
+
+// A tile's terms come in units that are basic blocks of their own (a batch of
+// slots, a removal pair).  In a large space one wavefront does them all; in a
+// small one, where there are fewer tiles than the GPU has room for wavefronts
+// and a tile's chain of loads is all the time there is, kTileParts wavefronts
+// of one block share the tile, unit I going to wavefront I mod kTileParts, and
+// their sums are added in order.  Whole calls without tables: N=6, M=8 94 us with
+// one wavefront per tile, 21 with eight; N=8, M=7 59 and 15; N=10, M=5 18.6 and
+// 14.7 (15 us is the caller's own time); through the paper's map 161 and 25, 97
+// and 20, 28 and 15.
+constexpr int kTileParts = 8;
+template <int MT>
+constexpr int kSmallParts = MT >= 5 ? kTileParts : 1;   // M <= 4: at most 55 slots
+
+template <int NP>
+struct Part {
+    int part;   // wave-uniform, 0 .. NP-1
+    template <int I>
+    __device__ __forceinline__ bool has() const
+    {
+        if constexpr (NP == 1) return opaque_true();
+        else return part == I % NP;
+    }
+    // the row's own term
+    __device__ __forceinline__ bool own() const { return NP == 1 || part == NP - 1; }
+};
+
+// Adds the parts of a tile (`red` holds NP * 64 double2) and stores its rows.
+// Block-uniform; with NP > 1 the block is one tile's wavefronts.
+template <int NP>
+__device__ __forceinline__ void store_tile(double2 v, int part, int64_t tile, int64_t D,
+                                           double2 *red, double2 *__restrict__ HC)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t g = tile * kTile + lane;
+    if constexpr (NP > 1) {
+        __syncthreads();   // the last tile's sums are read
+        red[part * kTile + lane] = v;
+        __syncthreads();
+        if (part != 0) return;
+#pragma unroll
+        for (int p = 1; p < NP; ++p) {
+            v.x += red[p * kTile + lane].x;
+            v.y += red[p * kTile + lane].y;
+        }
+    }
+    if (g < D) HC[g] = v;
+}
+
 // Removal pair p (lexicographic k <= s) -> (k, s), for compile-time use.
 __host__ __device__ constexpr int pair_k(int M, int p)
 {
@@ -289,8 +349,8 @@ __device__ __forceinline__ void pair_term(const int32_t *t2, int64_t pos, int64_
 // (uniform branch on the tile's pair mask), which keeps the scheduler from
 // hoisting later pairs' loads.  `tf` carries the prefetched first index
 // batch of the next block from pair to pair.
-template <int MT, bool BIGC, int... Ps>
-__device__ __forceinline__ void all_pairs(std::integer_sequence<int, Ps...>,
+template <int MT, bool BIGC, int NP, int... Ps>
+__device__ __forceinline__ void all_pairs(std::integer_sequence<int, Ps...>, Part<NP> part,
                                           const uint64_t *pm, const int32_t *t2, int64_t off0,
                                           int64_t off1, int lane, const int (&n)[MT],
                                           const RowSq<MT> &R, const double2 *__restrict__ gp,
@@ -302,7 +362,8 @@ __device__ __forceinline__ void all_pairs(std::integer_sequence<int, Ps...>,
         [&] {
             constexpr int NSB = MT * MT * kTile;
             if (((pm[Ps >> 6] >> (Ps & 63)) & 1) && pos + NSB <= off1) {
-                pair_term<MT, BIGC, Ps>(t2, pos, off1, lane, n, R, gp, ldc, tf, ar, ai);
+                if (NP == 1 || part.template has<Ps>())
+                    pair_term<MT, BIGC, Ps>(t2, pos, off1, lane, n, R, gp, ldc, tf, ar, ai);
                 pos += NSB;
             }
         }(),
@@ -312,8 +373,8 @@ __device__ __forceinline__ void all_pairs(std::integer_sequence<int, Ps...>,
 // One 64-row tile of H.C for a compile-time orbital count MT (1..8) through
 // the single- and double-jump maps; every orbital, pair and slot index is a
 // compile-time constant.  Called by one whole wavefront.
-template <int MT, typename OccT, bool BIGC>
-__device__ __forceinline__ void apply_tile_t2(int64_t tile, int64_t D, int64_t cap, const double *sq,
+template <int MT, typename OccT, bool BIGC, int NP>
+__device__ __forceinline__ double2 apply_tile_t2(Part<NP> part, int64_t tile, int64_t D, int64_t cap, const double *sq,
                                               const OccT *__restrict__ occ,
                                               const int32_t *__restrict__ t1,
                                               const uint64_t *__restrict__ pmask,
@@ -321,8 +382,7 @@ __device__ __forceinline__ void apply_tile_t2(int64_t tile, int64_t D, int64_t c
                                               const int32_t *__restrict__ t2,
                                               const double2 *__restrict__ h,
                                               const double2 *__restrict__ gp,
-                                              const double2 *__restrict__ C,
-                                              double2 *__restrict__ HC)
+                                              const double2 *__restrict__ C)
 {
     constexpr int M = MT;
     constexpr int P = M * (M + 1) / 2;
@@ -346,8 +406,8 @@ __device__ __forceinline__ void apply_tile_t2(int64_t tile, int64_t D, int64_t c
 
     // diagonal one-body part: sum_k h_kk n_k C_g
     const double2 cg = ldc(live ? (int32_t)g : -1);
-    double ar, ai;
-    {
+    double ar = 0.0, ai = 0.0;
+    if (part.own()) {
         double dr = 0.0, di = 0.0;
 #pragma unroll
         for (int k = 0; k < M; ++k) {
@@ -367,6 +427,7 @@ __device__ __forceinline__ void apply_tile_t2(int64_t tile, int64_t D, int64_t c
             make_rsrc(t1 + tile * NS * kTile, (uint32_t)(NS * kTile * 4));
 #pragma unroll
         for (int j0 = 0; j0 < NS; j0 += SB) {
+            if (NP > 1 && part.part != j0 / SB % NP) continue;
             int32_t t[SB];
             double2 c[SB];
 #pragma unroll
@@ -398,9 +459,9 @@ __device__ __forceinline__ void apply_tile_t2(int64_t tile, int64_t D, int64_t c
     }
 
     // double jumps: one block of M*M*64 entries per pair present in the tile
-    all_pairs<MT, BIGC>(std::make_integer_sequence<int, P>{}, pmask + tile * W, t2, off0, off1,
+    all_pairs<MT, BIGC>(std::make_integer_sequence<int, P>{}, part, pmask + tile * W, t2, off0, off1,
                         lane, n, R, gp, ldc, tf, ar, ai);
-    if (live) HC[g] = make_double2(ar, ai);
+    return make_double2(ar, ai);
 }
 
 
@@ -489,8 +550,8 @@ __device__ __forceinline__ void pair_term_chained(int64_t D, const int32_t *__re
 // values live at once there.  K and S are wave-uniform loop counters; q and
 // l stay compile-time, so the per-row occupations are picked with selects and
 // the roots come from the block's sqrt table.
-template <int MT, bool BIGC>
-__device__ __forceinline__ void pairs_chained_loop(int64_t D, int64_t g,
+template <int MT, bool BIGC, int NP>
+__device__ __forceinline__ void pairs_chained_loop(Part<NP> part, int64_t D, int64_t g,
                                                    const int32_t *__restrict__ t1,
                                                    __amdgpu_buffer_rsrc_t r1, int lane,
                                                    const int (&n)[MT], const double *sq,
@@ -503,6 +564,7 @@ __device__ __forceinline__ void pairs_chained_loop(int64_t D, int64_t g,
     for (int K = 0; K < MT; ++K) {
 #pragma unroll 1
         for (int S = K; S < MT; ++S, ++P) {
+            if (NP > 1 && part.part != P % NP) continue;
             int nK = 0, nS = 0;
 #pragma unroll
             for (int m = 0; m < MT; ++m) {
@@ -571,26 +633,30 @@ __device__ __forceinline__ void pairs_chained_loop(int64_t D, int64_t g,
     }
 }
 
-template <int MT, bool BIGC, int... Ps>
-__device__ __forceinline__ void all_pairs_chained(std::integer_sequence<int, Ps...>, int64_t D,
+template <int MT, bool BIGC, int NP, int... Ps>
+__device__ __forceinline__ void all_pairs_chained(std::integer_sequence<int, Ps...>, Part<NP> part, int64_t D,
                                                   const int32_t *__restrict__ t1,
                                                   __amdgpu_buffer_rsrc_t r1, int lane,
                                                   const int (&n)[MT], const RowSq<MT, kLdsRootsChained<MT>> &R,
                                                   const double2 *__restrict__ gp,
                                                   const Gather<BIGC> &ldc, double &ar, double &ai)
 {
-    (pair_term_chained<MT, BIGC, Ps>(D, t1, r1, lane, n, R, gp, ldc, ar, ai), ...);
+    (
+        [&] {
+            if (NP == 1 || part.template has<Ps>())
+                pair_term_chained<MT, BIGC, Ps>(D, t1, r1, lane, n, R, gp, ldc, ar, ai);
+        }(),
+        ...);
 }
 
 // One 64-row tile of H.C through single jumps only (see above).
-template <int MT, typename OccT, bool BIGC>
-__device__ __forceinline__ void apply_tile_chained(int64_t tile, int64_t D, const double *sq,
+template <int MT, typename OccT, bool BIGC, int NP>
+__device__ __forceinline__ double2 apply_tile_chained(Part<NP> part, int64_t tile, int64_t D, const double *sq,
                                                    const OccT *__restrict__ occ,
                                                    const int32_t *__restrict__ t1,
                                                    const double2 *__restrict__ h,
                                                    const double2 *__restrict__ gp,
-                                                   const double2 *__restrict__ C,
-                                                   double2 *__restrict__ HC)
+                                                   const double2 *__restrict__ C)
 {
     constexpr int M = MT;
     constexpr int P = M * (M + 1) / 2;
@@ -605,8 +671,8 @@ __device__ __forceinline__ void apply_tile_chained(int64_t tile, int64_t D, cons
     const __amdgpu_buffer_rsrc_t r1 =
         make_rsrc(t1 + tile * NS * kTile, (uint32_t)(NS * kTile * 4));
     const double2 cg = ldc(live ? (int32_t)g : -1);
-    double ar, ai;
-    {
+    double ar = 0.0, ai = 0.0;
+    if (part.own()) {
         double dr = 0.0, di = 0.0;
 #pragma unroll
         for (int k = 0; k < M; ++k) {
@@ -620,6 +686,7 @@ __device__ __forceinline__ void apply_tile_chained(int64_t tile, int64_t D, cons
     // single jumps k -> l (k != l), in batches
 #pragma unroll
     for (int j0 = 0; j0 < NS; j0 += SB) {
+        if (NP > 1 && part.part != j0 / SB % NP) continue;
         int32_t t[SB];
         double2 c[SB];
 #pragma unroll
@@ -648,11 +715,11 @@ __device__ __forceinline__ void apply_tile_chained(int64_t tile, int64_t D, cons
         }
     }
     if constexpr (kLdsRootsChained<MT>)
-        pairs_chained_loop<MT, BIGC>(D, g, t1, r1, lane, n, sq, gp, ldc, ar, ai);
+        pairs_chained_loop<MT, BIGC>(part, D, g, t1, r1, lane, n, sq, gp, ldc, ar, ai);
     else
-        all_pairs_chained<MT, BIGC>(std::make_integer_sequence<int, P>{}, D, t1, r1, lane, n, R, gp,
-                                    ldc, ar, ai);
-    if (live) HC[g] = make_double2(ar, ai);
+        all_pairs_chained<MT, BIGC>(std::make_integer_sequence<int, P>{}, part, D, t1, r1, lane, n, R,
+                                    gp, ldc, ar, ai);
+    return make_double2(ar, ai);
 }
 
 }  // namespace mc

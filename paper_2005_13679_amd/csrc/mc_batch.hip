@@ -17,35 +17,10 @@
 #include <numeric>
 #include <vector>
 
-#include "mc_apply.h"
-#include "mc_split.h"
 #include "mc_block.h"
-#include "mc_internal.h"
+#include "mc_tiles.h"
 
 namespace mc {
-
-// How an instance's tile body runs: paper form through its map or chained,
-// case-split form through its reduced map or chained.
-enum BatchKind : int32_t { kPaperMap = 0, kPaperChain = 1, kSplitMap = 2, kSplitChain = 3, kDirect = 4 };
-
-struct BatchInst {
-    int32_t N, M;
-    int32_t kind, chunk0;  // chunk0: first chunk of the instance
-    int64_t dim, tiles, cap, vec_off;
-    const uint8_t *occ;
-    const int32_t *t1;
-    const uint64_t *pmask;
-    const int64_t *t2_off;
-    const int32_t *t2;   // null: chain single jumps
-    const double2 *h, *g;
-    double2 *hp, *gp;    // staged h' and G' (paper form) / gp: case-split constants
-    int64_t hp_off, gp_off;  // the same, as offsets into the plan's coefficient region
-    int32_t *btab;           // tables of the four-row kernel (instances that take it)
-};
-
-// Pointers read from a descriptor are generic (flat loads); the staged
-// constants are therefore reached through the __restrict__ coefficient-region
-// kernel argument, which keeps their loads scalar.
 
 // An item whose descriptor holds sizes but no buffers runs table-free.
 static bool table_free(const mc_tables *t)
@@ -88,13 +63,13 @@ inline int64_t batch_chunk(int64_t total)
     while (c < (1 << 16) && total / c > 2048) c <<= 1;
     return c;
 }
-constexpr int kMaxGroups = 40;   // 8 orbital counts x 5 kinds
+constexpr int kMaxGroups = 48;   // 8 orbital counts x 6 kinds
 // Tiles a wavefront takes per counter increment (order 3): 8, fewer where the
 // group has no 8 per wavefront (8 small instances at M = 5: 165 us with 8 tiles
 // in a row on an eighth of the wavefronts, 25 us with one each).
-inline int batch_grab(int64_t items, int64_t blocks)
+inline int batch_grab(int64_t items, int64_t workers)
 {
-    const int64_t per = items / (blocks * 4);
+    const int64_t per = items / workers;
     return per >= 8 ? 8 : (per > 1 ? (int)per : 1);
 }
 
@@ -111,12 +86,12 @@ struct OwnLaunch {
 struct mc_batch {
     int32_t count;
     int32_t ngroups;
-    int32_t group_M[40];
-    int32_t group_kind[40];   // BatchKind of the group's instances
-    int32_t group_first[40];  // first entry in the sorted instance order
-    int32_t group_count[40];
-    int64_t group_tiles[40];
-    int64_t group_blocks[40];
+    int32_t group_M[48];
+    int32_t group_kind[48];   // BatchKind of the group's instances
+    int32_t group_first[48];  // first entry in the sorted instance order
+    int32_t group_count[48];
+    int64_t group_tiles[48];
+    int64_t group_blocks[48];
     int64_t nchunks;
     int64_t total_len;        // batch-vector length
     int32_t order;
@@ -147,7 +122,7 @@ __global__ void k_batch_prep(const BatchInst *__restrict__ inst, uint32_t *__res
     }
     const int first = blockIdx.x * blockDim.x + threadIdx.x;
     const int stride = (gridDim.x - 1) * blockDim.x;
-    if (I.kind == kSplitMap || I.kind == kSplitChain || I.kind == kDirect || I.btab) {
+    if (I.kind >= kSplitMap || I.btab) {   // every kind but the paper's sum
         stage_split_constants(M, 0, I.g, I.h, I.gp, first, stride);
         return;
     }
@@ -175,98 +150,6 @@ __global__ void k_batch_prep(const BatchInst *__restrict__ inst, uint32_t *__res
         }
         I.gp[idx] = make_double2(0.5 * a.x, 0.5 * a.y);
     }
-}
-
-// One tile of one instance, in the instance's kind.
-template <int MT, int KIND>
-__device__ __forceinline__ void batch_tile(const BatchInst &I, int64_t tile, const double *sq,
-                                           const double2 *__restrict__ coef,
-                                           const double2 *__restrict__ Cb,
-                                           double2 *__restrict__ HCb)
-{
-    const double2 *C = Cb + I.vec_off;
-    double2 *HC = HCb + I.vec_off;
-    const uint8_t *occ = I.occ;
-    const int32_t *t1 = I.t1;
-    const uint64_t *pmask = I.pmask;
-    const int64_t *t2_off = I.t2_off;
-    const int32_t *t2 = I.t2;
-    const double2 *gp = coef + I.gp_off, *hp = coef + I.hp_off;
-    if constexpr (KIND == kPaperMap)
-        apply_tile_paper<MT, uint8_t, false>(tile, I.dim, I.cap, sq, occ, t1, pmask, t2_off, t2, hp,
-                                          gp, C, HC);
-    else if constexpr (KIND == kPaperChain)
-        apply_tile_chained<MT, uint8_t, false>(tile, I.dim, sq, occ, t1, hp, gp, C, HC);
-    else if constexpr (KIND == kDirect)
-        apply_tile_direct<MT, false>(tile, I.N, I.dim, sq, gp, C, HC);
-    else
-        apply_tile_split<MT, uint8_t, false, KIND == kSplitMap>(tile, I.dim, I.cap, sq, occ, t1,
-                                                                pmask, t2_off, t2, gp, C, HC);
-}
-
-// Persistent H.C over one group (one orbital count and one BatchKind).
-// Work item i of the group is tile (i - prefix[j]) of the group's j-th
-// instance; with order 0 wavefront w takes items w, w + W, w + 2W, ...
-// (neighbouring tiles on neighbouring wavefronts), with order 1 a contiguous
-// range of items, with order 2 each XCD a contiguous share of the items,
-// interleaved over its wavefronts; with order 3 wavefronts take a few items
-// at a time from a per-group counter (dynamic balance, like a plain launch).
-constexpr int kBatchMaxN = 255;
-
-template <int MT, int KIND>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MC_APPLY_WAVES)))
-void k_batch_apply(const BatchInst *__restrict__ inst, const int64_t *__restrict__ prefix,
-                   int first, int count, int64_t items, int64_t nblocks, int order, int grab,
-                   uint32_t *__restrict__ counter, const double2 *__restrict__ coef,
-                   const double2 *__restrict__ Cb, double2 *__restrict__ HCb)
-{
-    __shared__ double sq[kLdsRoots<MT> ? kBatchMaxN + 3 : 1];
-    if constexpr (kLdsRoots<MT>) fill_sqrt_table(sq, kBatchMaxN + 3);
-    auto tile_body = [&](int64_t i, int &j) __attribute__((always_inline)) {
-        // instance of item i (prefix is non-decreasing; a wavefront visits
-        // items in increasing order, so the search resumes where it stopped)
-        while (j + 1 < count && prefix[first + j + 1] <= i) ++j;
-        const BatchInst I = inst[first + j];
-        batch_tile<MT, KIND>(I, i - prefix[first + j], sq, coef, Cb, HCb);
-    };
-    int j = 0;
-    if (order == 3) {
-        // dynamic: take `grab` items at a time from the group's counter (a
-        // vector atomic from lane 0; the count is zeroed by k_batch_prep)
-        for (;;) {
-            uint32_t base = 0;
-            if ((threadIdx.x & 63) == 0) base = atomicAdd(counter, (uint32_t)grab);
-            base = __builtin_amdgcn_readfirstlane(base);
-            if ((int64_t)base >= items) break;
-            const int64_t end = (int64_t)base + grab < items ? (int64_t)base + grab : items;
-            for (int64_t i = base; i < end; ++i) tile_body(i, j);
-        }
-        return;
-    }
-    const int64_t W = nblocks * 4;
-    const int64_t w = xcd_block(blockIdx.x, nblocks) * 4 + wave_in_block();
-    int64_t i0, step, iend;
-    if (order == 2) {
-        // blocks go to XCD b % 8; this XCD's blocks own items [ib, ie)
-        const int64_t xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
-        const int64_t bper = nblocks >> 3, brem = nblocks & 7;
-        const int64_t nbx = bper + (xcd < brem ? 1 : 0);
-        const int64_t fb = xcd * bper + (xcd < brem ? xcd : brem);
-        const int64_t ib = items * fb / nblocks, ie = items * (fb + nbx) / nblocks;
-        i0 = ib + local * 4 + wave_in_block();
-        step = nbx * 4;
-        iend = ie;
-    } else if (order == 1) {
-        const int64_t per = (items + W - 1) / W;
-        i0 = w * per;
-        step = 1;
-        iend = i0 + per < items ? i0 + per : items;
-    } else {
-        i0 = w;
-        step = W;
-        iend = items;
-    }
-    for (int64_t i = i0; i < iend; i += step) tile_body(i, j);
 }
 
 // conj(a) b added to (r, i); every reduction below adds its terms this way.
@@ -536,7 +419,10 @@ int mc_batch_create(int32_t count, const mc_batch_item *items, const mc_batch_sc
 
     // instance order: by orbital count, then kind, then decreasing dimension
     auto kind_of = [](const mc_tables *t) -> int32_t {
-        if (table_free(t)) return kDirect;
+        // above kSmallTiles, what the four-row kernel does not serve runs
+        // table-free as in mc_apply_H
+        if (table_free(t) || t->tiles > kSmallTiles)
+            return t->tiles > kSmallTiles && t->M >= 5 ? kDirectLarge : kDirect;
         const bool split = t->form == MC_FORM_REDUCED, map = t->t2_d != nullptr;
         return split ? (map ? kSplitMap : kSplitChain) : (map ? kPaperMap : kPaperChain);
     };
@@ -653,7 +539,8 @@ int mc_batch_create(int32_t count, const mc_batch_item *items, const mc_batch_sc
         if (hipGetDeviceProperties(&prop, dev) == hipSuccess) cus = prop.multiProcessorCount;
     }
     for (int gi = 0; gi < b->ngroups; ++gi) {
-        const int64_t need = (b->group_tiles[gi] + 3) / 4;
+        const bool parts = small_parts(b->group_M[gi], b->group_kind[gi]);
+        const int64_t need = parts ? b->group_tiles[gi] : (b->group_tiles[gi] + 3) / 4;
         const int64_t cap_blocks = (int64_t)bpc * cus;
         b->group_blocks[gi] = need < cap_blocks ? need : cap_blocks;
         if (b->group_blocks[gi] < 1) b->group_blocks[gi] = 1;
@@ -715,20 +602,14 @@ static int batch_apply_staged(const mc_batch *b, const double *C_d, double *HC_d
     }
     for (int gi = 0; gi < b->ngroups; ++gi) {
         const int M = b->group_M[gi];
-#define MC_BATCH_LAUNCH(KIND)                                                                   \
-    hipLaunchKernelGGL((k_batch_apply<MT, KIND>), dim3(b->group_blocks[gi]), dim3(256), 0, s,   \
-                       b->inst_d, b->tile_prefix_d, b->group_first[gi], b->group_count[gi],     \
-                       b->group_tiles[gi], b->group_blocks[gi], b->order,                       \
-                       batch_grab(b->group_tiles[gi], b->group_blocks[gi]), b->counters_d + gi, \
-                       (const double2 *)b->coef_d, (const double2 *)C_d, (double2 *)HC_d)
-        switch (b->group_kind[gi]) {
-        case kPaperMap: MC_DISPATCH_M(M, if constexpr (MT > 0) MC_BATCH_LAUNCH(kPaperMap)); break;
-        case kPaperChain: MC_DISPATCH_M(M, if constexpr (MT > 0) MC_BATCH_LAUNCH(kPaperChain)); break;
-        case kSplitMap: MC_DISPATCH_M(M, if constexpr (MT > 0) MC_BATCH_LAUNCH(kSplitMap)); break;
-        case kDirect: MC_DISPATCH_M(M, if constexpr (MT > 0) MC_BATCH_LAUNCH(kDirect)); break;
-        default: MC_DISPATCH_M(M, if constexpr (MT > 0) MC_BATCH_LAUNCH(kSplitChain)); break;
-        }
-#undef MC_BATCH_LAUNCH
+        const int64_t blocks = b->group_blocks[gi];
+        const int64_t workers = small_parts(M, b->group_kind[gi]) ? blocks : blocks * 4;
+        const GroupCall c{b->group_kind[gi], b->group_first[gi], b->group_count[gi], b->order,
+                          batch_grab(b->group_tiles[gi], workers), b->group_tiles[gi], blocks,
+                          b->inst_d, b->tile_prefix_d, b->counters_d + gi, b->coef_d,
+                          (const double2 *)C_d, (double2 *)HC_d, s};
+        const int st = MC_TILES_CALL(group, M, c);
+        if (st) return st;
     }
     return launch_status();
 }

@@ -223,68 +223,62 @@ __device__ __forceinline__ void direct_fmas(std::integer_sequence<int, Is...>,
         ...);
 }
 
+// A_KS of the pair that batch B ends inside of times the pair's sum so far:
+// with a wavefront per part of the batches, a pair does not go on in the next.
+template <int MT, int LAST>
+__device__ __forceinline__ void direct_flush(const int (&n)[MT], const RowSq<MT> &R, double &br,
+                                             double &bi, double &ar, double &ai)
+{
+    constexpr int NSING = FlatTile<MT>::NSING;
+    if constexpr (LAST >= NSING) {
+        constexpr int P = flat_pair(MT, LAST - NSING), r = flat_slot(MT, LAST - NSING);
+        constexpr int K = pair_k(MT, P), S = pair_s(MT, P);
+        if constexpr (r != reduced_slots(MT, K, S) - 1) {
+            const bool valid = K == S ? n[K] >= 2 : (n[K] >= 1 && n[S] >= 1);
+            const double A = valid ? R.template root<0>(K) *
+                                         (K == S ? R.template root<-1>(K) : R.template root<0>(S))
+                                   : 0.0;
+            ar = fma(A, br, ar);
+            ai = fma(A, bi, ai);
+        }
+    }
+    br = 0.0;
+    bi = 0.0;
+}
+
 // Batch B of the stream in a basic block of its own (see opaque_true):
 // its targets, its gathers, its arithmetic.
-template <int MT, bool BIGC, int B>
-__device__ __forceinline__ void direct_batches(const DirectRow<MT> &row, const int (&n)[MT],
-                                               const RowSq<MT> &R, const double (&x)[MT],
+template <int MT, bool BIGC, int B, int NP>
+__device__ __forceinline__ void direct_batches(Part<NP> part, const DirectRow<MT> &row,
+                                               const int (&n)[MT], const RowSq<MT> &R,
+                                               const double (&x)[MT],
                                                const double2 *__restrict__ HS,
                                                const double2 *__restrict__ GS,
                                                const double2 *__restrict__ GD,
                                                const Gather<BIGC> &ldc, double &br, double &bi,
                                                double &ar, double &ai)
 {
-    constexpr int SB = DirectStream<MT>::SB, NB = DirectStream<MT>::NB;
+    constexpr int SB = DirectStream<MT>::SB, NB = DirectStream<MT>::NB, U = DirectStream<MT>::U;
     if constexpr (B < NB) {
-        if (opaque_true()) {
+        if (part.template has<B>()) {
             double2 c[SB];
             direct_gathers<MT, BIGC, B * SB>(std::make_integer_sequence<int, SB>{}, c, row, n, ldc);
             direct_fmas<MT, B * SB>(std::make_integer_sequence<int, SB>{}, c, n, R, x, HS, GS, GD,
                                     br, bi, ar, ai);
+            if constexpr (NP > 1)
+                direct_flush<MT, ((B + 1) * SB < U ? (B + 1) * SB : U) - 1>(n, R, br, bi, ar, ai);
         }
-        direct_batches<MT, BIGC, B + 1>(row, n, R, x, HS, GS, GD, ldc, br, bi, ar, ai);
-    }
-}
-
-// With MC_DIRECT_PIPE: batch B's block first issues batch B+1's gathers
-// into the other buffer, then does batch B's arithmetic.
-#ifndef MC_DIRECT_PIPE
-#define MC_DIRECT_PIPE 0
-#endif
-
-template <int MT, bool BIGC, int B>
-__device__ __forceinline__ void direct_batches_pipe(double2 (&cur)[DirectStream<MT>::SB],
-                                                    double2 (&nxt)[DirectStream<MT>::SB],
-                                                    const DirectRow<MT> &row, const int (&n)[MT],
-                                                    const RowSq<MT> &R, const double (&x)[MT],
-                                                    const double2 *__restrict__ HS,
-                                                    const double2 *__restrict__ GS,
-                                                    const double2 *__restrict__ GD,
-                                                    const Gather<BIGC> &ldc, double &br,
-                                                    double &bi, double &ar, double &ai)
-{
-    constexpr int SB = DirectStream<MT>::SB, NB = DirectStream<MT>::NB;
-    if constexpr (B < NB) {
-        if (opaque_true()) {
-            if constexpr (B + 1 < NB)
-                direct_gathers<MT, BIGC, (B + 1) * SB>(std::make_integer_sequence<int, SB>{}, nxt,
-                                                       row, n, ldc);
-            direct_fmas<MT, B * SB>(std::make_integer_sequence<int, SB>{}, cur, n, R, x, HS, GS,
-                                    GD, br, bi, ar, ai);
-        }
-        direct_batches_pipe<MT, BIGC, B + 1>(nxt, cur, row, n, R, x, HS, GS, GD, ldc, br, bi, ar,
-                                             ai);
+        direct_batches<MT, BIGC, B + 1>(part, row, n, R, x, HS, GS, GD, ldc, br, bi, ar, ai);
     }
 }
 
 // One 64-row tile of H.C with no table (M <= 8, D < 2^31); `cf` holds the
 // constants staged by k_prep_split.
-template <int MT, bool BIGC>
-__device__ __forceinline__ void apply_tile_direct(int64_t tile, int N, int64_t D,
-                                                  const double *sq,
-                                                  const double2 *__restrict__ cf,
-                                                  const double2 *__restrict__ C,
-                                                  double2 *__restrict__ HC)
+template <int MT, bool BIGC, int NP>
+__device__ __forceinline__ double2 apply_tile_direct(Part<NP> part, int64_t tile, int N, int64_t D,
+                                                     const double *sq,
+                                                     const double2 *__restrict__ cf,
+                                                     const double2 *__restrict__ C)
 {
     constexpr int M = MT;
     constexpr int P = M * (M + 1) / 2;
@@ -308,8 +302,8 @@ __device__ __forceinline__ void apply_tile_direct(int64_t tile, int N, int64_t D
 
     // the row's own coefficient (one-body diagonal and coincident pairs)
     const double2 cg = ldc(live ? (int32_t)g : -1);
-    double ar, ai;
-    {
+    double ar = 0.0, ai = 0.0;
+    if (part.own()) {
         double dr = 0.0, di = 0.0;
 #pragma unroll
         for (int k = 0; k < M; ++k) {
@@ -327,15 +321,8 @@ __device__ __forceinline__ void apply_tile_direct(int64_t tile, int N, int64_t D
     }
     // single jumps, then the true double jumps pair by pair
     double br = 0.0, bi = 0.0;
-    if constexpr (MC_DIRECT_PIPE && DirectStream<MT>::NB > 1) {
-        double2 ca[DirectStream<MT>::SB], cb[DirectStream<MT>::SB];
-        direct_gathers<MT, BIGC, 0>(std::make_integer_sequence<int, DirectStream<MT>::SB>{}, ca,
-                                    row, n, ldc);
-        direct_batches_pipe<MT, BIGC, 0>(ca, cb, row, n, R, x, HS, GS, GD, ldc, br, bi, ar, ai);
-    } else {
-        direct_batches<MT, BIGC, 0>(row, n, R, x, HS, GS, GD, ldc, br, bi, ar, ai);
-    }
-    if (live) HC[g] = make_double2(ar, ai);
+    direct_batches<MT, BIGC, 0>(part, row, n, R, x, HS, GS, GD, ldc, br, bi, ar, ai);
+    return make_double2(ar, ai);
 }
 
 }  // namespace mc

@@ -1,8 +1,9 @@
-// Table-free H.C: the one-row kernel of mc_direct.h, its entry points, and
-// the staging of the case-split constants.
+// Table-free H.C: its entry points, and the staging of the case-split
+// constants.
 #include <mutex>
 
-#include "mc_direct.h"
+#include "mc_split.h"
+#include "mc_tiles.h"
 
 namespace mc {
 
@@ -21,18 +22,13 @@ void launch_prep_split(int32_t M, int adjoint, const double *g_d, const double *
                        (const double2 *)h_d, cf);
 }
 
-// H.C with no table (occupations and targets in closed form, mc_direct.h).
-template <int MT, bool BIGC>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MC_APPLY_WAVES)))
-void k_apply_direct(int N, int64_t D, int64_t tiles, int64_t nblocks,
-                    const double2 *__restrict__ cf, const double2 *__restrict__ C,
-                    double2 *__restrict__ HC)
+int apply_direct_launch(int32_t N, int32_t M, int64_t D, const double *h_d, const double *g_d,
+                        int adjoint, const double *C_d, double *HC_d, void *ws_d, hipStream_t s)
 {
-    extern __shared__ double sq[];
-    if constexpr (kLdsRoots<MT>) fill_sqrt_table(sq, N + 3);
-    const int64_t tile = xcd_block_as<kDirectRemap<MT>>(blockIdx.x, nblocks) * 4 + wave_in_block();
-    if (tile >= tiles) return;
-    apply_tile_direct<MT, BIGC>(tile, N, D, sq, cf, C, HC);
+    double2 *cf = (double2 *)ws_d;
+    launch_prep_split(M, adjoint, g_d, h_d, cf, s);
+    const DirectCall c{N, D <= kSmallTiles * kTile, D, cf, (const double2 *)C_d, (double2 *)HC_d, s};
+    return MC_TILES_CALL(direct, M, c);
 }
 
 }  // namespace mc
@@ -88,22 +84,7 @@ static int apply_direct_common(int32_t N, int32_t M, const double *h_d, const do
     hipStream_t s = (hipStream_t)stream;
     if (block_serves(N, M, D) && ws_bytes >= block_workspace(N, M))
         return apply_block_launch(N, M, D, h_d, g_d, adjoint, C_d, HC_d, ws_d, s);
-    double2 *cf = (double2 *)ws_d;
-    launch_prep_split(M, adjoint, g_d, h_d, cf, s);
-    const int64_t tiles = (D + kTile - 1) / kTile;
-    const int64_t nblocks = (tiles + 3) / 4;
-    const bool big = D * 16 > (int64_t)0xFFFFFFFFu;
-    MC_DISPATCH_M(M, if constexpr (MT > 0 && MT <= 8) {
-        if (big)
-            hipLaunchKernelGGL((k_apply_direct<MT, true>), dim3(nblocks), dim3(256),
-                               kLdsRoots<MT> ? sqb : 0, s, N, D, tiles, nblocks,
-                               (const double2 *)cf, (const double2 *)C_d, (double2 *)HC_d);
-        else
-            hipLaunchKernelGGL((k_apply_direct<MT, false>), dim3(nblocks), dim3(256),
-                               kLdsRoots<MT> ? sqb : 0, s, N, D, tiles, nblocks,
-                               (const double2 *)cf, (const double2 *)C_d, (double2 *)HC_d);
-    });
-    return launch_status();
+    return apply_direct_launch(N, M, D, h_d, g_d, adjoint, C_d, HC_d, ws_d, s);
 }
 
 int mc_apply_H_direct(int32_t N, int32_t M, const double *h_d, const double *g_d,

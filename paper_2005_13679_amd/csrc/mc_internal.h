@@ -80,6 +80,9 @@ int apply_block_launch(int32_t N, int32_t M, int64_t D, const double *h_d, const
                        int adjoint, const double *C_d, double *HC_d, void *ws_d, hipStream_t s);
 int apply_block_run(int32_t N, int32_t M, int64_t D, const double2 *cf, const int32_t *tab,
                     const double *C_d, double *HC_d, hipStream_t s);
+// The one-row table-free apply (mc_direct.h): staging and launch.
+int apply_direct_launch(int32_t N, int32_t M, int64_t D, const double *h_d, const double *g_d,
+                        int adjoint, const double *C_d, double *HC_d, void *ws_d, hipStream_t s);
 // Launches the staging of the case-split constants into cf.
 void launch_prep_split(int32_t M, int adjoint, const double *g_d, const double *h_d, double2 *cf,
                        hipStream_t s);

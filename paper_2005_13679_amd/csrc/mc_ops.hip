@@ -16,6 +16,7 @@
 #include "mc_sparse.h"
 #include "mc_gram.h"
 #include "mc_internal.h"
+#include "mc_tiles.h"
 
 namespace mc {
 
@@ -81,53 +82,6 @@ void k_apply_sparse(int N, int64_t D, int64_t tiles, int64_t nblocks, int64_t ca
     if (tile >= tiles) return;
     apply_tile_sparse<MT, OccT, BIGC, MAP>(tile, D, cap, sq, occ, t1, pmask, t2_off, t2r, cf, sl,
                                            C, HC);
-}
-
-// H.C in the case-split form (reduced tables); MAP: reduced double-jump map
-// present, else chained single jumps.
-template <int MT, typename OccT, bool BIGC, bool MAP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MC_APPLY_WAVES)))
-void k_apply_split(int N, int64_t D, int64_t tiles, int64_t nblocks, int64_t cap,
-                   const OccT *__restrict__ occ, const int32_t *__restrict__ t1,
-                   const uint64_t *__restrict__ pmask, const int64_t *__restrict__ t2_off,
-                   const int32_t *__restrict__ t2r, const double2 *__restrict__ cf,
-                   const double2 *__restrict__ C, double2 *__restrict__ HC)
-{
-    extern __shared__ double sq[];
-    if constexpr (kLdsRoots<MT>) fill_sqrt_table(sq, N + 3);
-    const int64_t tile = xcd_block(blockIdx.x, nblocks) * 4 + wave_in_block();
-    if (tile >= tiles) return;
-    apply_tile_split<MT, OccT, BIGC, MAP>(tile, D, cap, sq, occ, t1, pmask, t2_off, t2r, cf, C, HC);
-}
-
-template <int MT, typename OccT, bool BIGC>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MC_APPLY_WAVES)))
-void k_apply(int N, int64_t D, int64_t tiles, int64_t nblocks, int64_t cap,
-             const OccT *__restrict__ occ, const int32_t *__restrict__ t1,
-             const uint64_t *__restrict__ pmask, const int64_t *__restrict__ t2_off,
-             const int32_t *__restrict__ t2, const double2 *__restrict__ h,
-             const double2 *__restrict__ gp, const double2 *__restrict__ C,
-             double2 *__restrict__ HC)
-{
-    extern __shared__ double sq[];
-    if constexpr (kLdsRoots<MT>) fill_sqrt_table(sq, N + 3);
-    const int64_t tile = xcd_block(blockIdx.x, nblocks) * 4 + wave_in_block();
-    if (tile >= tiles) return;
-    apply_tile_paper<MT, OccT, BIGC>(tile, D, cap, sq, occ, t1, pmask, t2_off, t2, h, gp, C, HC);
-}
-
-template <int MT, typename OccT, bool BIGC>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MC_APPLY_WAVES)))
-void k_apply_chained(int N, int64_t D, int64_t tiles, int64_t nblocks,
-                     const OccT *__restrict__ occ, const int32_t *__restrict__ t1,
-                     const double2 *__restrict__ h, const double2 *__restrict__ gp,
-                     const double2 *__restrict__ C, double2 *__restrict__ HC)
-{
-    extern __shared__ double sq[];
-    if constexpr (kLdsRoots<MT>) fill_sqrt_table(sq, N + 3);
-    const int64_t tile = xcd_block(blockIdx.x, nblocks) * 4 + wave_in_block();
-    if (tile >= tiles) return;
-    apply_tile_chained<MT, OccT, BIGC>(tile, D, sq, occ, t1, h, gp, C, HC);
 }
 
 // H.C for any M (run-time orbital loops; the occupations and roots of each
@@ -740,97 +694,53 @@ static int apply_common(int32_t N, int32_t M, const double *h_d, const double *g
     if (ws_bytes < apply_workspace_least(M)) return MC_ENOMEM;
     if (M > 8 && (chained || (size_t)5 * M * kTile * 8 > 65536)) return MC_EINVAL;
     hipStream_t s = (hipStream_t)stream;
+    const bool split = t->form == MC_FORM_REDUCED;
+    if (split && M > 8) return MC_EINVAL;
+    if ((size_t)(N + 3) * 8 > 65536) return MC_EINVAL;   // LDS square-root table
+    const bool big = D * 16 > (int64_t)0xFFFFFFFFu;
+    if (M <= 8 && big && !chained) return MC_EINVAL;     // no map of that size fits the GPU
     // Spaces that the four-row kernel serves are fastest with every target in
     // closed form, whatever the tables hold: N=200, M=5 7.9 ms through the
     // reduced map, 10.7 through the paper's map, 9.5 and 22.4 chained, 3.4 so;
-    // N=50, M=6 0.89, 1.42 and 0.41.  Its lower limits were measured against
-    // the table-free kernel; through the maps the smaller spaces take about as
-    // long as that.
-    if (block_serves(N, M, D) && ws_bytes >= block_workspace(N, M))
-        return apply_block_launch(N, M, D, h_d, g_d, adjoint, C_d, HC_d, ws_d, s);
-    if (t->form == MC_FORM_REDUCED) {
-        if (M > 8) return MC_EINVAL;
-        const size_t sqb = (size_t)(N + 3) * 8;
-        if (sqb > 65536) return MC_EINVAL;
+    // N=50, M=6 0.89, 1.42 and 0.41.  So are, one row per lane, those above
+    // kSmallTiles that it does not serve (M = 8, N = 17, 346 k rows: 290 us
+    // through the reduced map, 456 through the paper's, 339 and 729 chained,
+    // 198 so; M = 5, N = 38, 112 k rows: 29, 32, 28, 48 and 22).  Below, the
+    // wavefronts of a block share a tile and both ways are near the launch's
+    // own latency.
+    if (M <= 8 && t->tiles > kSmallTiles) {
+        if (block_serves(N, M, D) && ws_bytes >= block_workspace(N, M))
+            return apply_block_launch(N, M, D, h_d, g_d, adjoint, C_d, HC_d, ws_d, s);
+        return apply_direct_launch(N, M, D, h_d, g_d, adjoint, C_d, HC_d, ws_d, s);
+    }
+    if (split) {
         double2 *cf = (double2 *)ws_d;
         launch_prep_split(M, adjoint, g_d, h_d, cf, s);
-        const int64_t nblocks = (t->tiles + 3) / 4;
-        const bool big = D * 16 > (int64_t)0xFFFFFFFFu;
-        bool launched = false;
-        // same instantiation rules as the paper form: 16-bit occupations only
-        // for M <= 5, 64-bit gathers only without a map
-#define MC_SPLIT_LAUNCH(OT, BIG, MAP)                                                          \
-    MC_DISPATCH_M(M, if constexpr (MT > 0 && (MT <= 5 || sizeof(OT) == 1) && !(BIG && MAP)) {   \
-        hipLaunchKernelGGL((k_apply_split<MT, OT, BIG, MAP>), dim3(nblocks), dim3(256),         \
-                           kLdsRoots<MT> ? sqb : 0, s, N, D, t->tiles, nblocks, t->t2_entries,   \
-                           (const OT *)t->occ_d, t->t1_d, t->pmask_d, t->t2_off_d, t->t2_d,     \
-                           (const double2 *)cf, (const double2 *)C_d, (double2 *)HC_d);         \
-        launched = true;                                                                       \
-    })
-        if (chained) {
-            if (occ_width(N) == 1) {
-                if (big) { MC_SPLIT_LAUNCH(uint8_t, true, false); } else { MC_SPLIT_LAUNCH(uint8_t, false, false); }
-            } else {
-                if (big) { MC_SPLIT_LAUNCH(uint16_t, true, false); } else { MC_SPLIT_LAUNCH(uint16_t, false, false); }
-            }
-        } else if (!big) {
-            if (occ_width(N) == 1) { MC_SPLIT_LAUNCH(uint8_t, false, true); } else { MC_SPLIT_LAUNCH(uint16_t, false, true); }
-        }
-#undef MC_SPLIT_LAUNCH
-        if (!launched) return MC_EINVAL;
-        return launch_status();
+        const TablesCall c{N, chained ? kSplitChain : kSplitMap, t, cf, nullptr,
+                           (const double2 *)C_d, (double2 *)HC_d, s};
+        return MC_TILES_CALL(tables, M, c);
     }
     double2 *gp = (double2 *)ws_d;
     double2 *hp = gp + (size_t)npairs(M) * M * M;
     hipLaunchKernelGGL(k_prep, dim3(4), dim3(256), 0, s, M, adjoint, (const double2 *)g_d,
                        (const double2 *)h_d, gp, hp);
-    const int64_t nblocks = (t->tiles + 3) / 4;
-    const bool big = D * 16 > (int64_t)0xFFFFFFFFu;
-    const size_t sqb = (size_t)(N + 3) * 8;   // LDS square-root table (kLdsRoots)
-    if (sqb > 65536) return MC_EINVAL;
-    // Instantiated combinations: 16-bit occupations only for M <= 5 (M >= 6
-    // with N > 255 has D > 2^31), 64-bit gathers (D >= 2^28) only without the
-    // double-jump map (a double-jump map of that size cannot fit in HBM).
-    bool launched = false;
-#define MC_APPLY_LAUNCH(OT, BIG)                                                               \
-    if (M <= 8) {                                                                              \
-        MC_DISPATCH_M(M, if constexpr (MT > 0 && !BIG && (MT <= 5 || sizeof(OT) == 1)) {        \
-            hipLaunchKernelGGL((k_apply<MT, OT, BIG>), dim3(nblocks), dim3(256),                \
-                               kLdsRoots<MT> ? sqb : 0, s, N, D,                               \
-                               t->tiles, nblocks, t->t2_entries, (const OT *)t->occ_d, t->t1_d,  \
-                               t->pmask_d, t->t2_off_d, t->t2_d, (const double2 *)hp,            \
-                               (const double2 *)gp, (const double2 *)C_d, (double2 *)HC_d);     \
-            launched = true;                                                                   \
-        });                                                                                    \
-    } else {                                                                                   \
-        hipLaunchKernelGGL((k_apply_generic<OT, BIG>), dim3(t->tiles), dim3(64),                \
-                           (size_t)5 * M * kTile * 8, s, M, D, t->tiles, t->t2_entries,        \
-                           (const OT *)t->occ_d, t->t1_d, t->pmask_d, t->t2_off_d, t->t2_d,    \
-                           (const double2 *)hp, (const double2 *)gp, (const double2 *)C_d,     \
-                           (double2 *)HC_d);                                                   \
-        launched = true;                                                                       \
+    if (M <= 8) {
+        const TablesCall c{N, chained ? kPaperChain : kPaperMap, t, hp, gp, (const double2 *)C_d,
+                           (double2 *)HC_d, s};
+        return MC_TILES_CALL(tables, M, c);
     }
-#define MC_CHAINED_LAUNCH(OT, BIG)                                                             \
-    MC_DISPATCH_M(M, if constexpr (MT > 0 && (MT <= 5 || sizeof(OT) == 1)) {                     \
-        hipLaunchKernelGGL((k_apply_chained<MT, OT, BIG>), dim3(nblocks), dim3(256),            \
-                           kLdsRoots<MT> ? sqb : 0, s, N, D,                                     \
-                           t->tiles, nblocks, (const OT *)t->occ_d, t->t1_d, (const double2 *)hp, \
-                           (const double2 *)gp, (const double2 *)C_d, (double2 *)HC_d);         \
-        launched = true;                                                                       \
-    })
-    if (chained) {
-        if (occ_width(N) == 1) {
-            if (big) { MC_CHAINED_LAUNCH(uint8_t, true); } else { MC_CHAINED_LAUNCH(uint8_t, false); }
-        } else {
-            if (big) { MC_CHAINED_LAUNCH(uint16_t, true); } else { MC_CHAINED_LAUNCH(uint16_t, false); }
-        }
-    } else if (occ_width(N) == 1) {
-        if (big) { MC_APPLY_LAUNCH(uint8_t, true); } else { MC_APPLY_LAUNCH(uint8_t, false); }
+#define MC_GENERIC_LAUNCH(OT, BIG)                                                             \
+    hipLaunchKernelGGL((k_apply_generic<OT, BIG>), dim3(t->tiles), dim3(64),                    \
+                       (size_t)5 * M * kTile * 8, s, M, D, t->tiles, t->t2_entries,            \
+                       (const OT *)t->occ_d, t->t1_d, t->pmask_d, t->t2_off_d, t->t2_d,        \
+                       (const double2 *)hp, (const double2 *)gp, (const double2 *)C_d,         \
+                       (double2 *)HC_d)
+    if (occ_width(N) == 1) {
+        if (big) MC_GENERIC_LAUNCH(uint8_t, true); else MC_GENERIC_LAUNCH(uint8_t, false);
     } else {
-        if (big) { MC_APPLY_LAUNCH(uint16_t, true); } else { MC_APPLY_LAUNCH(uint16_t, false); }
+        if (big) MC_GENERIC_LAUNCH(uint16_t, true); else MC_GENERIC_LAUNCH(uint16_t, false);
     }
-#undef MC_APPLY_LAUNCH
-    if (!launched) return MC_EINVAL;
+#undef MC_GENERIC_LAUNCH
     return launch_status();
 }
 

@@ -28,20 +28,9 @@
 #include <utility>
 
 #include "mc_apply.h"
+#include "mc_tiles.h"
 
 namespace mc {
-
-// A wave-uniform true that the compiler cannot see through.  Branching on
-// it puts each batch of a long straight-line stream into a basic block of its
-// own; within one huge block the instruction scheduler issues every load of
-// the stream first and keeps all gathered values live (hundreds of spilled
-// registers), across blocks it cannot move them.
-__device__ __forceinline__ bool opaque_true()
-{
-    int v;
-    asm volatile("s_mov_b32 %0, 1" : "=s"(v));
-    return v != 0;
-}
 
 // Rank of the creation pair (q, l), q <= l, among the pairs of orbitals
 // outside {K, S}, in lexicographic order (closed form, so that it folds to a
@@ -193,8 +182,8 @@ __device__ __forceinline__ void split_pair_map(const int32_t *t2r, int64_t pos, 
     ai = fma(A, bi, ai);
 }
 
-template <int MT, bool BIGC, int... Ps>
-__device__ __forceinline__ void split_pairs_map(std::integer_sequence<int, Ps...>,
+template <int MT, bool BIGC, int NP, int... Ps>
+__device__ __forceinline__ void split_pairs_map(std::integer_sequence<int, Ps...>, Part<NP> part,
                                                 const uint64_t *pm, const int32_t *t2r,
                                                 int64_t off0, int64_t off1, int lane,
                                                 const int (&n)[MT], const RowSq<MT> &R,
@@ -207,7 +196,8 @@ __device__ __forceinline__ void split_pairs_map(std::integer_sequence<int, Ps...
             constexpr int NSB = reduced_slots(MT, pair_k(MT, Ps), pair_s(MT, Ps)) * kTile;
             if constexpr (NSB > 0) {
                 if (((pm[Ps >> 6] >> (Ps & 63)) & 1) && pos + NSB <= off1) {
-                    split_pair_map<MT, BIGC, Ps>(t2r, pos, lane, n, R, gd, ldc, ar, ai);
+                    if (NP == 1 || part.template has<Ps>())
+                        split_pair_map<MT, BIGC, Ps>(t2r, pos, lane, n, R, gd, ldc, ar, ai);
                     pos += NSB;
                 }
             }
@@ -320,26 +310,27 @@ __device__ __forceinline__ void split_pair_chain(int64_t D, const int32_t *__res
     }
 }
 
-template <int MT, bool BIGC, int... Ps>
-__device__ __forceinline__ void split_pairs_chain(std::integer_sequence<int, Ps...>, int64_t D,
+template <int MT, bool BIGC, int NP, int... Ps>
+__device__ __forceinline__ void split_pairs_chain(std::integer_sequence<int, Ps...>, Part<NP> part, int64_t D,
                                                   const int32_t *__restrict__ t1,
                                                   __amdgpu_buffer_rsrc_t r1, int lane,
                                                   const int (&n)[MT], const RowSq<MT> &R,
                                                   const double2 *__restrict__ gd,
                                                   const Gather<BIGC> &ldc, double &ar, double &ai)
 {
-    (split_pair_chain<MT, BIGC, Ps>(D, t1, r1, lane, n, R, gd, ldc, ar, ai), ...);
+    (
+        [&] {
+            if (NP == 1 || part.template has<Ps>())
+                split_pair_chain<MT, BIGC, Ps>(D, t1, r1, lane, n, R, gd, ldc, ar, ai);
+        }(),
+        ...);
 }
 
 // ---------------------------------------------------------------------------
-// Tiles whose pair mask has every pair (nearly all tiles of large spaces):
-// the tile's single jumps and reduced-map blocks form one stream of
-// U = M(M-1) + sum_p nd(p) slots with a compile-time layout, processed in
-// batches of MC_FLAT_BATCH slots; the next batch's index loads are issued
-// while the current batch's gathers are in flight.  Same arithmetic, in the
-// same order, as the per-pair path.  The build default walks the same slots
-// in class-major order instead (below), which gathers fewer coefficients and
-// groups the terms differently (results agree to rounding).
+// The case-split slots in one order: a row's single jumps, then the reduced
+// slots pair by pair, U = M(M-1) + sum_p nd(p) in all.  The table-free apply
+// walks them in it; tiles through the maps whose pair mask has every pair walk
+// them class by class (below).
 // ---------------------------------------------------------------------------
 #ifndef MC_FLAT_BATCH
 #define MC_FLAT_BATCH 16
@@ -383,19 +374,6 @@ __host__ __device__ constexpr int reduced_ql(int M, int K, int S, int r, int whi
             if (r-- == 0) return which ? l : q;
         }
     return -1;
-}
-
-template <int MT, int U>
-__device__ __forceinline__ int32_t flat_load(__amdgpu_buffer_rsrc_t r1, __amdgpu_buffer_rsrc_t r2,
-                                             int lane)
-{
-    constexpr int NSING = FlatTile<MT>::NSING;
-    if constexpr (U < NSING) {
-        constexpr int a = U / (MT - 1), bb = U % (MT - 1), b = bb + (bb >= a);
-        return buf_ld_i32(r1, (uint32_t)(((a * MT + b) * kTile + lane) * 4), 0);
-    } else {
-        return buf_ld_i32(r2, (uint32_t)(((U - NSING) * kTile + lane) * 4), 0);
-    }
 }
 
 template <int MT, int U>
@@ -448,65 +426,6 @@ __device__ __forceinline__ void flat_fma(const double2 &c, const int (&n)[MT], c
     }
 }
 
-template <int MT, int U0, int... Is>
-__device__ __forceinline__ void flat_loads(std::integer_sequence<int, Is...>,
-                                           int32_t (&t)[FlatTile<MT>::SB],
-                                           __amdgpu_buffer_rsrc_t r1, __amdgpu_buffer_rsrc_t r2,
-                                           int lane)
-{
-    ((U0 + Is < FlatTile<MT>::U ? (void)(t[Is] = flat_load<MT, U0 + Is>(r1, r2, lane)) : (void)0),
-     ...);
-}
-
-template <int MT, int U0, int... Is>
-__device__ __forceinline__ void flat_fmas(std::integer_sequence<int, Is...>,
-                                          const double2 (&c)[FlatTile<MT>::SB], const int (&n)[MT],
-                                          const RowSq<MT> &R, const double (&x)[MT],
-                                          const double2 *__restrict__ HS,
-                                          const double2 *__restrict__ GS,
-                                          const double2 *__restrict__ GD, double &br, double &bi,
-                                          double &ar, double &ai)
-{
-    (
-        [&] {
-            if constexpr (U0 + Is < FlatTile<MT>::U)
-                flat_fma<MT, U0 + Is>(c[Is], n, R, x, HS, GS, GD, br, bi, ar, ai);
-        }(),
-        ...);
-}
-
-// batch B: gathers for the indices in `cur`, then the next batch's index
-// loads into `nxt`, then the arithmetic of batch B
-template <int MT, bool BIGC, int B>
-__device__ __forceinline__ void flat_batches(int32_t (&cur)[FlatTile<MT>::SB],
-                                             int32_t (&nxt)[FlatTile<MT>::SB],
-                                             __amdgpu_buffer_rsrc_t r1, __amdgpu_buffer_rsrc_t r2,
-                                             int lane, const int (&n)[MT], const RowSq<MT> &R,
-                                             const double (&x)[MT], const double2 *__restrict__ HS,
-                                             const double2 *__restrict__ GS,
-                                             const double2 *__restrict__ GD,
-                                             const Gather<BIGC> &ldc, double &br, double &bi,
-                                             double &ar, double &ai)
-{
-    constexpr int SB = FlatTile<MT>::SB, NB = FlatTile<MT>::NB, U = FlatTile<MT>::U;
-    if constexpr (B < NB) {
-        // each batch in a basic block of its own (see opaque_true)
-        if (opaque_true()) {
-            double2 c[SB];
-#pragma unroll
-            for (int i = 0; i < SB; ++i)
-                if (B * SB + i < U) c[i] = ldc(cur[i]);
-            if constexpr (B + 1 < NB)
-                flat_loads<MT, (B + 1) * SB>(std::make_integer_sequence<int, SB>{}, nxt, r1, r2,
-                                             lane);
-            flat_fmas<MT, B * SB>(std::make_integer_sequence<int, SB>{}, c, n, R, x, HS, GS, GD, br,
-                                  bi, ar, ai);
-        }
-        flat_batches<MT, BIGC, B + 1>(nxt, cur, r1, r2, lane, n, R, x, HS, GS, GD, ldc, br, bi, ar,
-                                      ai);
-    }
-}
-
 // ---------------------------------------------------------------------------
 // Class-major stream: fewer coefficient gathers per tile.
 //
@@ -554,9 +473,6 @@ __host__ __device__ constexpr void flat_jump(int U, int &R1, int &R2, int &A1, i
     A2 = reduced_ql(MT, R1, R2, r, 1);
 }
 
-#ifndef MC_CLASS_STREAM
-#define MC_CLASS_STREAM 1
-#endif
 // largest orbital count whose full tiles take the class-major stream, per
 // form (the paper form's slots grow as M^4: 786 at M = 6, 1414 at M = 7;
 // the reduced form's stream at M = 7 measured slower than its per-pair path,
@@ -1054,10 +970,11 @@ __device__ __forceinline__ void class_targets(std::integer_sequence<int, Is...>,
         ...);
 }
 
-// The whole stream: batch B's block issues batch B+1's targets (table loads
-// in flight during B's gathers), then B's gathers and arithmetic.
-template <int MT, int FORM, bool BIGC, int B, class Src>
-__device__ __forceinline__ void class_batches(int32_t (&cur)[MC_CLASS_BATCH],
+// The whole stream.  One wavefront: batch B's block issues batch B+1's targets
+// (table loads in flight during B's gathers), then B's gathers and arithmetic;
+// several: each batch by itself.
+template <int MT, int FORM, bool BIGC, int B, int NP, class Src>
+__device__ __forceinline__ void class_batches(Part<NP> part, int32_t (&cur)[MC_CLASS_BATCH],
                                               int32_t (&nxt)[MC_CLASS_BATCH], const Src &src,
                                               int32_t own_t, double2 own_c, const RowSq<MT> &R,
                                               const RunKeys<MT> &rk,
@@ -1067,29 +984,34 @@ __device__ __forceinline__ void class_batches(int32_t (&cur)[MC_CLASS_BATCH],
     constexpr int NB = kClassPlan<MT, FORM>.nb;
     if constexpr (B < NB) {
         // each batch in a basic block of its own (see opaque_true)
-        if (opaque_true()) {
-            if constexpr (B + 1 < NB)
+        if (part.template has<B>()) {
+            if constexpr (NP > 1)
+                class_targets<MT, FORM, B>(std::make_integer_sequence<int, MC_CLASS_BATCH>{}, src,
+                                           cur);
+            else if constexpr (B + 1 < NB)
                 class_targets<MT, FORM, B + 1>(std::make_integer_sequence<int, MC_CLASS_BATCH>{},
                                                src, nxt);
             class_batch<MT, FORM, BIGC, B>(std::make_integer_sequence<int, MC_CLASS_BATCH>{}, src,
                                            cur, own_t, own_c, R, rk, k, ldc, ar, ai);
         }
-        class_batches<MT, FORM, BIGC, B + 1>(nxt, cur, src, own_t, own_c, R, rk, k, ldc, ar, ai);
+        class_batches<MT, FORM, BIGC, B + 1>(part, nxt, cur, src, own_t, own_c, R, rk, k, ldc, ar,
+                                             ai);
     }
 }
 
 // `n`: the row's occupations; own_t: its index (negative past the end).
-template <int MT, int FORM, bool BIGC, class Src>
-__device__ __forceinline__ void class_stream(const Src &src, int32_t own_t, double2 own_c,
-                                             const int (&n)[MT], const RowSq<MT> &R,
-                                             const ClassConsts<MT, FORM> &k,
+template <int MT, int FORM, bool BIGC, int NP, class Src>
+__device__ __forceinline__ void class_stream(Part<NP> part, const Src &src, int32_t own_t,
+                                             double2 own_c, const int (&n)[MT],
+                                             const RowSq<MT> &R, const ClassConsts<MT, FORM> &k,
                                              const Gather<BIGC> &ldc, double &ar, double &ai)
 {
     RunKeys<MT> rk{n, own_t >= 0 ? own_t + n[0] : -1, {}};
     run_key_shifts(std::make_integer_sequence<int, 2 * kMaxShift + 1>{}, rk.key, rk.at);
     int32_t ta[MC_CLASS_BATCH], tb[MC_CLASS_BATCH];
-    class_targets<MT, FORM, 0>(std::make_integer_sequence<int, MC_CLASS_BATCH>{}, src, ta);
-    class_batches<MT, FORM, BIGC, 0>(ta, tb, src, own_t, own_c, R, rk, k, ldc, ar, ai);
+    if constexpr (NP == 1)
+        class_targets<MT, FORM, 0>(std::make_integer_sequence<int, MC_CLASS_BATCH>{}, src, ta);
+    class_batches<MT, FORM, BIGC, 0>(part, ta, tb, src, own_t, own_c, R, rk, k, ldc, ar, ai);
 }
 
 // Targets of a full tile through the tables: the tile's single-jump block
@@ -1115,16 +1037,15 @@ struct MapSlots {
 
 // One 64-row tile of H.C in the case-split form; MAP: true double jumps from
 // the reduced map, else chained.  `cf` holds the staged constants.
-template <int MT, typename OccT, bool BIGC, bool MAP>
-__device__ __forceinline__ void apply_tile_split(int64_t tile, int64_t D, int64_t cap,
+template <int MT, typename OccT, bool BIGC, bool MAP, int NP>
+__device__ __forceinline__ double2 apply_tile_split(Part<NP> part, int64_t tile, int64_t D, int64_t cap,
                                                  const double *sq, const OccT *__restrict__ occ,
                                                  const int32_t *__restrict__ t1,
                                                  const uint64_t *__restrict__ pmask,
                                                  const int64_t *__restrict__ t2_off,
                                                  const int32_t *__restrict__ t2r,
                                                  const double2 *__restrict__ cf,
-                                                 const double2 *__restrict__ C,
-                                                 double2 *__restrict__ HC)
+                                                 const double2 *__restrict__ C)
 {
     constexpr int M = MT;
     constexpr int P = M * (M + 1) / 2;
@@ -1148,8 +1069,8 @@ __device__ __forceinline__ void apply_tile_split(int64_t tile, int64_t D, int64_
 
     // the row's own coefficient (one-body diagonal and coincident pairs)
     const double2 cg = ldc(live ? (int32_t)g : -1);
-    double ar, ai;
-    {
+    double ar = 0.0, ai = 0.0;
+    if (part.own()) {
         double dr = 0.0, di = 0.0;
 #pragma unroll
         for (int k = 0; k < M; ++k) {
@@ -1181,24 +1102,17 @@ __device__ __forceinline__ void apply_tile_split(int64_t tile, int64_t D, int64_
         if (full) {
             const __amdgpu_buffer_rsrc_t r2 =
                 make_rsrc(t2r + off0, (uint32_t)(FlatTile<MT>::NDBL * kTile * 4));
-#if MC_CLASS_STREAM
             const MapSlots<MT, 0> src{r1, r2, lane};
             const ClassConsts<MT, 0> k{HS, GS, GD, x};
-            class_stream<MT, 0, BIGC>(src, live ? (int32_t)g : -2, cg, n, R, k, ldc, ar, ai);
-#else
-            int32_t ta[FlatTile<MT>::SB], tb[FlatTile<MT>::SB];
-            flat_loads<MT, 0>(std::make_integer_sequence<int, FlatTile<MT>::SB>{}, ta, r1, r2, lane);
-            double br = 0.0, bi = 0.0;
-            flat_batches<MT, BIGC, 0>(ta, tb, r1, r2, lane, n, R, x, HS, GS, GD, ldc, br, bi, ar, ai);
-#endif
-            if (live) HC[g] = make_double2(ar, ai);
-            return;
+            class_stream<MT, 0, BIGC>(part, src, live ? (int32_t)g : -2, cg, n, R, k, ldc, ar, ai);
+            return make_double2(ar, ai);
         }
     }
 
     // single jumps a -> b with coefficient sqrt(n_a (n_b+1)) (HS + sum_c n_c GS)
 #pragma unroll
     for (int j0 = 0; j0 < NS; j0 += SB) {
+        if (NP > 1 && part.part != j0 / SB % NP) continue;
         int32_t t[SB];
         double2 c[SB];
 #pragma unroll
@@ -1240,13 +1154,13 @@ __device__ __forceinline__ void apply_tile_split(int64_t tile, int64_t D, int64_
     if constexpr (MAP) {
         int64_t off0, off1;
         t2_block(t2_off, tile, cap, off0, off1);
-        split_pairs_map<MT, BIGC>(std::make_integer_sequence<int, P>{}, pmask + tile * W, t2r, off0,
-                                  off1, lane, n, R, GD, ldc, ar, ai);
+        split_pairs_map<MT, BIGC>(std::make_integer_sequence<int, P>{}, part, pmask + tile * W, t2r,
+                                  off0, off1, lane, n, R, GD, ldc, ar, ai);
     } else {
-        split_pairs_chain<MT, BIGC>(std::make_integer_sequence<int, P>{}, D, t1, r1, lane, n, R, GD,
+        split_pairs_chain<MT, BIGC>(std::make_integer_sequence<int, P>{}, part, D, t1, r1, lane, n, R, GD,
                                     ldc, ar, ai);
     }
-    if (live) HC[g] = make_double2(ar, ai);
+    return make_double2(ar, ai);
 }
 
 // One 64-row tile of H.C in the paper's form (the paper's double-jump map,
@@ -1255,12 +1169,8 @@ __device__ __forceinline__ void apply_tile_split(int64_t tile, int64_t D, int64_
 // stream: the paper's sum over all its slots, reading only the anchors'
 // table columns and gathering each distinct target once; other tiles take
 // the per-pair path.
-#ifndef MC_PAPER_STREAM
-#define MC_PAPER_STREAM 1
-#endif
-
-template <int MT, typename OccT, bool BIGC>
-__device__ __forceinline__ void apply_tile_paper(int64_t tile, int64_t D, int64_t cap,
+template <int MT, typename OccT, bool BIGC, int NP>
+__device__ __forceinline__ double2 apply_tile_paper(Part<NP> part, int64_t tile, int64_t D, int64_t cap,
                                                  const double *sq, const OccT *__restrict__ occ,
                                                  const int32_t *__restrict__ t1,
                                                  const uint64_t *__restrict__ pmask,
@@ -1268,10 +1178,9 @@ __device__ __forceinline__ void apply_tile_paper(int64_t tile, int64_t D, int64_
                                                  const int32_t *__restrict__ t2,
                                                  const double2 *__restrict__ h,
                                                  const double2 *__restrict__ gp,
-                                                 const double2 *__restrict__ C,
-                                                 double2 *__restrict__ HC)
+                                                 const double2 *__restrict__ C)
 {
-    if constexpr (MC_PAPER_STREAM && MT >= 2 && MT <= kStreamMaxMPaper) {
+    if constexpr (MT >= 2 && MT <= kStreamMaxMPaper) {
         constexpr int P = MT * (MT + 1) / 2, W = (P + 63) / 64, NS = MT * MT;
         int64_t off0, off1;
         t2_block(t2_off, tile, cap, off0, off1);
@@ -1298,17 +1207,40 @@ __device__ __forceinline__ void apply_tile_paper(int64_t tile, int64_t D, int64_
                 dr = fma(h[k * MT + k].x, (double)n[k], dr);
                 di = fma(h[k * MT + k].y, (double)n[k], di);
             }
-            double ar = dr * cg.x - di * cg.y, ai = dr * cg.y + di * cg.x;
+            double ar = 0.0, ai = 0.0;
+            if (part.own()) {
+                ar = dr * cg.x - di * cg.y;
+                ai = dr * cg.y + di * cg.x;
+            }
             const MapSlots<MT, 1> src{
                 make_rsrc(t1 + tile * NS * kTile, (uint32_t)(NS * kTile * 4)),
                 make_rsrc(t2 + off0, (uint32_t)(P * NS * kTile * 4)), lane};
             const ClassConsts<MT, 1> k{h, gp};
-            class_stream<MT, 1, BIGC>(src, live ? (int32_t)g : -2, cg, n, R, k, ldc, ar, ai);
-            if (live) HC[g] = make_double2(ar, ai);
-            return;
+            class_stream<MT, 1, BIGC>(part, src, live ? (int32_t)g : -2, cg, n, R, k, ldc, ar, ai);
+            return make_double2(ar, ai);
         }
     }
-    apply_tile_t2<MT, OccT, BIGC>(tile, D, cap, sq, occ, t1, pmask, t2_off, t2, h, gp, C, HC);
+    return apply_tile_t2<MT, OccT, BIGC>(part, tile, D, cap, sq, occ, t1, pmask, t2_off, t2, h, gp, C);
+}
+
+// One tile through the tables in any kind; `ca` holds the case-split constants
+// or h, `cb` the paper form's G'.
+template <int MT, typename OccT, int KIND, int NP>
+__device__ __forceinline__ double2 apply_tile_tables(
+    Part<NP> part, int64_t tile, int64_t D, int64_t cap, const double *sq,
+    const OccT *__restrict__ occ, const int32_t *__restrict__ t1,
+    const uint64_t *__restrict__ pmask, const int64_t *__restrict__ t2_off,
+    const int32_t *__restrict__ t2, const double2 *__restrict__ ca,
+    const double2 *__restrict__ cb, const double2 *__restrict__ C)
+{
+    if constexpr (KIND == kPaperMap)
+        return apply_tile_paper<MT, OccT, false>(part, tile, D, cap, sq, occ, t1, pmask, t2_off, t2,
+                                                 ca, cb, C);
+    else if constexpr (KIND == kPaperChain)
+        return apply_tile_chained<MT, OccT, false>(part, tile, D, sq, occ, t1, ca, cb, C);
+    else
+        return apply_tile_split<MT, OccT, false, KIND == kSplitMap>(part, tile, D, cap, sq, occ, t1,
+                                                                    pmask, t2_off, t2, ca, C);
 }
 
 }  // namespace mc

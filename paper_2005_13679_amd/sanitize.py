@@ -38,19 +38,20 @@ def _host_flags():
                 "-fno-sanitize-recover=undefined", "-Xarch_host", "-shared-libsan"]
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(ASAN_DIR, os.path.splitext(src)[0] + ".o")
-    cmd = [B.HIPCC, *B.FLAGS, *_host_flags(), "-g", "-c", os.path.join(B.CSRC, src), "-o", obj]
+def _compile(unit) -> str:
+    src, name, extra = unit
+    obj = os.path.join(ASAN_DIR, name + ".o")
+    cmd = [B.HIPCC, *B.FLAGS, *extra, *_host_flags(), "-g", "-c", os.path.join(B.CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
-        raise RuntimeError(f"hipcc failed for {src}:\n{r.stderr}")
+        raise RuntimeError(f"hipcc failed for {src} ({name}):\n{r.stderr}")
     return obj
 
 
 def build_sanitized() -> tuple[str, str]:
     os.makedirs(ASAN_DIR, exist_ok=True)
     os.makedirs(ORACLE_DIR, exist_ok=True)
-    with cf.ThreadPoolExecutor(max_workers=len(B.SOURCES)) as ex:
+    with cf.ThreadPoolExecutor(max_workers=min(len(B.SOURCES), 8)) as ex:
         objs = list(ex.map(_compile, B.SOURCES))
     lib = os.path.join(ASAN_DIR, "libmc.so")
     san = ",".join(SAN)

@@ -1,0 +1,75 @@
+"""H.C on both sides of the limit of small spaces (1,024 tiles of 64 rows: the
+wavefronts of a block share a tile up to it, from five orbitals on), for every
+kind of space, alone and in a batch; and with a workspace that holds the staged
+constants only.
+
+Tolerance: 1e-12 relative to the largest element, the bar of every apply."""
+
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from tests.gpu_helpers import rel_inf
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-12
+# 58,905 and 66,045 rows, 53,130 and 65,780, 54,264 and 74,613, 50,388 and 77,520;
+# one tile; a single row
+SIZES = [(32, 5), (33, 5), (20, 6), (21, 6), (15, 7), (16, 7), (12, 8), (13, 8), (4, 5), (1, 1)]
+KINDS = [("direct", False), ("reduced", True), ("reduced", False), ("paper", True), ("paper", False)]
+
+
+def dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+@pytest.mark.parametrize("N,M", SIZES)
+def test_every_kind_matches_oracle_and_batch(mc, oracle_native, N, M):
+    rng = np.random.default_rng(17 * N + M)
+    D = oracle_native.dim(N, M)
+    h = rng.standard_normal((M, M)) + 1j * rng.standard_normal((M, M))
+    g = rng.standard_normal((M,) * 4) + 1j * rng.standard_normal((M,) * 4)
+    C = rng.standard_normal(D) + 1j * rng.standard_normal(D)
+    rows = np.unique(np.concatenate([rng.integers(0, D, 1500), np.arange(min(D, 128)),
+                                     D - 1 - np.arange(min(D, 128))]))
+    ref = oracle_native.apply_h(N, M, h, g, C, rows)
+    r = torch.from_numpy(rows).cuda()
+    spaces = [mc.DirectSpace(N, M) if form == "direct" else
+              mc.build_tables(N, M, form=form, double_jumps=maps) for form, maps in KINDS]
+    hd, gd, Cd = dev(h), dev(g), dev(C)
+    alone = [mc.apply_H(hd, gd, Cd, s) for s in spaces]
+    for (form, maps), out in zip(KINDS, alone):
+        assert rel_inf(out[r].cpu().numpy(), ref) <= TOL, (form, maps)
+    for sched in (None, {"blocks_per_cu": 1, "order": 1}, {"blocks_per_cu": 1, "order": 2}):
+        b = mc.Batch([(s, hd, gd) for s in spaces], sched)
+        out = b.apply_H(Cd.repeat(len(spaces)), b.vector())
+        for i, a in enumerate(alone):
+            assert torch.equal(b.segment(out, i), a), (KINDS[i], sched)
+
+
+@pytest.mark.parametrize("N,M", [(32, 5), (40, 5), (20, 8)])
+def test_workspace_with_room_for_the_constants_only(mc, oracle_native, N, M):
+    """mc_workspace_size's bytes may go to the four-row kernel's tables; the
+    staged constants alone are enough for an apply."""
+    from paper_2005_13679_amd import _lib as L
+    lib = L.load()
+    P = M * (M + 1) // 2
+    least = (P * M * M + M * M) * 16
+    least = max(least, 4 * (1 + 64 + 2 * 36 + 8 * 28 + 28 * 21) + 16 * (
+        M + P + M * M + M ** 3 + M * (M * (M - 1) // 2) +
+        (M * (M - 1) // 2) * ((M - 1) * (M - 2) // 2)))
+    C, h, g = W.random_instance(N, M, 3)
+    hd, gd, Cd = dev(h), dev(g), dev(C)
+    out = torch.empty_like(Cd)
+    ws = torch.empty(least, dtype=torch.uint8, device="cuda")
+    p = lambda t: ctypes.c_void_p(t.data_ptr())
+    st = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    assert lib.mc_apply_H_direct(N, M, p(hd), p(gd), p(Cd), p(out), p(ws), least, st) == L.MC_OK
+    rows = np.unique(np.random.default_rng(5).integers(0, C.size, 1500))
+    ref = oracle_native.apply_h(N, M, h, g, C, rows)
+    assert rel_inf(out[torch.from_numpy(rows).cuda()].cpu().numpy(), ref) <= TOL
+    assert lib.mc_apply_H_direct(N, M, p(hd), p(gd), p(Cd), p(out), p(ws), least - 1, st) == L.MC_ENOMEM
