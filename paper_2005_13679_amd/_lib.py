@@ -173,6 +173,8 @@ _lib = None
 def load():
     """Loads libmc.so once and declares every exported symbol."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is not None:
             return _lib

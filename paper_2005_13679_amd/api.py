@@ -11,15 +11,40 @@ import torch
 from . import _lib as L
 
 
-def _stream(device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+def _stream(device) -> int:
+    """The current stream of `device` as the pointer the library takes."""
+    i = device.index
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if i is None else i)
 
 
-def _ptr(t: torch.Tensor) -> ctypes.c_void_p:
-    return ctypes.c_void_p(t.data_ptr())
+def _ptr(t: torch.Tensor) -> int:
+    return t.data_ptr()
+
+
+class _Here:
+    """Stands for ``with torch.cuda.device(dev)`` where dev is current already."""
+
+    def __enter__(self):
+        return None
+
+    def __exit__(self, *exc):
+        return False
+
+
+_here = _Here()
+
+
+def _on(device):
+    """A context with `device` current (nothing to do where it is)."""
+    return (_here if device.index is None or torch.cuda.current_device() == device.index
+            else torch.cuda.device(device))
 
 
 def _require(t: torch.Tensor, name: str, dtype, device, numel=None, shape=None):
+    if (isinstance(t, torch.Tensor) and t.dtype == dtype and t.device == device
+            and t.is_contiguous() and (numel is None or t.numel() == numel)
+            and (shape is None or tuple(t.shape) == tuple(shape))):
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.dtype != dtype:
@@ -267,6 +292,10 @@ class DirectSpace:
 
 
 def _as_dev(x, device, shape=None) -> torch.Tensor:
+    if (isinstance(x, torch.Tensor) and x.dtype == torch.complex128 and x.device == device
+            and x.is_contiguous() and not x.is_conj() and not x.is_neg()
+            and (shape is None or x.shape == shape)):
+        return x
     if not isinstance(x, torch.Tensor):
         x = torch.as_tensor(np.asarray(x))
     x = x.to(device=device, dtype=torch.complex128)
@@ -288,7 +317,7 @@ def apply_H(h, g, C: torch.Tensor, tables, out: torch.Tensor | None = None) -> t
         out = torch.empty_like(C)
     _require(out, "out", torch.complex128, dev, numel=tables.dim)
     ws = tables.workspace(L.MC_OP_APPLY)
-    with torch.cuda.device(dev):
+    with _on(dev):
         L.check(L.load().mc_apply_H(N, M, _ptr(h), _ptr(g), ctypes.byref(tables.c), _ptr(C),
                                     _ptr(out), _ptr(ws), ws.numel(), _stream(dev)), "mc_apply_H")
     return out
@@ -307,7 +336,7 @@ def apply_H_sparse(h, g, C: torch.Tensor, tables: Tables,
         out = torch.empty_like(C)
     _require(out, "out", torch.complex128, dev, numel=tables.dim)
     ws = tables.workspace(L.MC_OP_APPLY)
-    with torch.cuda.device(dev):
+    with _on(dev):
         L.check(L.load().mc_apply_H_sparse(N, M, _ptr(h), _ptr(g), ctypes.byref(tables.c),
                                            _ptr(C), _ptr(out), _ptr(ws), ws.numel(),
                                            _stream(dev)), "mc_apply_H_sparse")
@@ -338,7 +367,7 @@ def apply_H_direct(h, g, C: torch.Tensor, N: int, M: int,
         out = torch.empty_like(C)
     _require(out, "out", torch.complex128, dev, numel=D)
     ws = sp.workspace(L.MC_OP_APPLY)
-    with torch.cuda.device(dev):
+    with _on(dev):
         L.check(L.load().mc_apply_H_direct(N, M, _ptr(h), _ptr(g), _ptr(C), _ptr(out), _ptr(ws),
                                            ws.numel(), _stream(dev)), "mc_apply_H_direct")
     return out
@@ -355,7 +384,7 @@ def apply_H_adjoint(h, g, C: torch.Tensor, tables, out: torch.Tensor | None = No
         out = torch.empty_like(C)
     _require(out, "out", torch.complex128, dev, numel=tables.dim)
     ws = tables.workspace(L.MC_OP_APPLY)
-    with torch.cuda.device(dev):
+    with _on(dev):
         if isinstance(tables, DirectSpace):
             L.check(L.load().mc_apply_H_direct_adjoint(N, M, _ptr(h), _ptr(g), _ptr(C), _ptr(out),
                                                        _ptr(ws), ws.numel(), _stream(dev)),
@@ -373,7 +402,7 @@ def is_hermitian(h, g, M: int, device) -> bool:
     h = _as_dev(h, device, (M, M))
     g = _as_dev(g, device, (M, M, M, M))
     flag = torch.empty(1, dtype=torch.int32, device=device)
-    with torch.cuda.device(device):
+    with _on(device):
         L.check(L.load().mc_is_hermitian(M, _ptr(h), _ptr(g), _ptr(flag), _stream(device)),
                 "mc_is_hermitian")
     return bool(flag.item())
@@ -396,7 +425,7 @@ def zaxpby(x: torch.Tensor, a: torch.Tensor | None = None, y: torch.Tensor | Non
     flags = ((L.MC_CONJ_A if conj_a else 0) | (L.MC_CONJ_X if conj_x else 0)
              | (L.MC_CONJ_B if conj_b else 0) | (L.MC_CONJ_Y if conj_y else 0))
     nul = ctypes.c_void_p(None)
-    with torch.cuda.device(dev):
+    with _on(dev):
         L.check(L.load().mc_zaxpby(x.numel(), _ptr(a) if a is not None else nul, _ptr(x),
                                    _ptr(b) if b is not None else nul,
                                    _ptr(y) if y is not None else nul, float(scale), flags,
@@ -414,11 +443,11 @@ def rho1(C: torch.Tensor, tables: Tables, out: torch.Tensor | None = None) -> to
     _require(out, "out", torch.complex128, dev, numel=M * M)
     ws = tables.workspace(L.MC_OP_RHO1)
     if isinstance(tables, DirectSpace):
-        with torch.cuda.device(dev):
+        with _on(dev):
             L.check(L.load().mc_rho1_direct(tables.N, M, _ptr(C), _ptr(out), _ptr(ws), ws.numel(),
                                             _stream(dev)), "mc_rho1_direct")
         return out
-    with torch.cuda.device(dev):
+    with _on(dev):
         L.check(L.load().mc_rho1(tables.N, M, ctypes.byref(tables.c), _ptr(C), _ptr(out),
                                  _ptr(ws), ws.numel(), _stream(dev)), "mc_rho1")
     return out
@@ -434,11 +463,11 @@ def rho2(C: torch.Tensor, tables: Tables, out: torch.Tensor | None = None) -> to
     _require(out, "out", torch.complex128, dev, numel=M ** 4)
     ws = tables.workspace(L.MC_OP_RHO2)
     if isinstance(tables, DirectSpace):
-        with torch.cuda.device(dev):
+        with _on(dev):
             L.check(L.load().mc_rho2_direct(tables.N, M, _ptr(C), _ptr(out), _ptr(ws), ws.numel(),
                                             _stream(dev)), "mc_rho2_direct")
         return out
-    with torch.cuda.device(dev):
+    with _on(dev):
         L.check(L.load().mc_rho2(tables.N, M, ctypes.byref(tables.c), _ptr(C), _ptr(out),
                                  _ptr(ws), ws.numel(), _stream(dev)), "mc_rho2")
     return out
@@ -458,7 +487,7 @@ def zdotc(x: torch.Tensor, y: torch.Tensor, out: torch.Tensor | None = None) -> 
     if ws is None:
         ws = torch.empty((L.MC_DOT_BLOCKS + 1) * 16, dtype=torch.uint8, device=dev)
         _dot_ws[dev] = ws
-    with torch.cuda.device(dev):
+    with _on(dev):
         L.check(L.load().mc_zdotc(x.numel(), _ptr(x), _ptr(y), _ptr(out), _ptr(ws), ws.numel(),
                                   _stream(dev)), "mc_zdotc")
     return out
@@ -470,7 +499,7 @@ def hash_batch(occ: torch.Tensor, tables: Tables) -> torch.Tensor:
     _require(occ, "occ", torch.int32, dev)
     count = occ.numel() // tables.M
     out = torch.empty(count, dtype=torch.int64, device=dev)
-    with torch.cuda.device(dev):
+    with _on(dev):
         L.check(L.load().mc_hash_batch(tables.N, tables.M, ctypes.byref(tables.c), _ptr(occ),
                                        _ptr(out), count, _stream(dev)), "mc_hash_batch")
     return out
@@ -481,7 +510,7 @@ def unhash_batch(idx: torch.Tensor, tables: Tables) -> torch.Tensor:
     dev = tables.device
     _require(idx, "idx", torch.int64, dev)
     out = torch.empty((idx.numel(), tables.M), dtype=torch.int32, device=dev)
-    with torch.cuda.device(dev):
+    with _on(dev):
         L.check(L.load().mc_unhash_batch(tables.N, tables.M, ctypes.byref(tables.c), _ptr(idx),
                                          _ptr(out), idx.numel(), _stream(dev)), "mc_unhash_batch")
     return out
@@ -493,7 +522,7 @@ def t2_lookup(queries: torch.Tensor, tables: Tables) -> torch.Tensor:
     _require(queries, "queries", torch.int64, dev)
     count = queries.numel() // 5
     out = torch.empty(count, dtype=torch.int32, device=dev)
-    with torch.cuda.device(dev):
+    with _on(dev):
         L.check(L.load().mc_t2_lookup(tables.N, tables.M, ctypes.byref(tables.c), _ptr(queries),
                                       _ptr(out), count, _stream(dev)), "mc_t2_lookup")
     return out
