@@ -22,7 +22,7 @@ LIB = os.path.join(HERE, "libmc.so")
 SOURCES = [("mc_tiles.hip", f"mc_tiles_{m}_{p}", (f"-DMC_TILES_M={m}", f"-DMC_TILES_PART={p}"))
            for m in range(8, 0, -1) for p in (2, 0, 1)]
 SOURCES += [(f"{n}.hip", n, ()) for n in
-            ("mc_ops", "mc_block", "mc_host", "mc_tables", "mc_direct", "mc_batch", "mc_krylov",
+            ("mc_ops", "mc_block", "mc_block_sparse", "mc_host", "mc_tables", "mc_direct", "mc_batch", "mc_krylov",
              "mc_gram_direct", "mc_gram_tables")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -43,15 +43,15 @@ void k_apply_block(int N, int64_t D, int items, int64_t nblocks, const int *__re
     apply_block<MT>(live ? (int)i : items - 1, live, D, N, lt, sq, cf, C, HC);
 }
 
+}  // namespace
+
 // Rows whose n_b is divisible by R.
-int64_t block_items(int N, int M)
+int64_t block_items(int32_t N, int32_t M)
 {
     int64_t items = 0;
     for (int S = N; S >= 0; S -= kBlockRows) items += dim_checked(S, M - 1);
     return items;
 }
-
-}  // namespace
 
 size_t block_workspace(int32_t N, int32_t M)
 {
@@ -67,11 +67,21 @@ size_t block_workspace(int32_t N, int32_t M)
 // 30, N = 50 (316 k) 44 / 35; M = 6, N = 20 (53 k) 46 / 50, N = 27 (201 k) 63 /
 // 49; M = 7, N = 16 (75 k) 72 / 78, N = 20 (230 k) 112 / 99; M = 8, N = 17
 // (346 k) 223 / 321, N = 20 (888 k) 519 / 460.
+bool block_fits(int32_t N, int32_t M, int64_t D)
+{
+    return M >= 3 && M <= 8 && N < 4096 && D * 32 <= (int64_t)0xFFFFFFF0u;
+}
+
 bool block_serves(int32_t N, int32_t M, int64_t D)
 {
-    if (M < 3 || M > 8 || N >= 4096) return false;
-    if (D * 32 > (int64_t)0xFFFFFFF0u) return false;
-    return D >= (M <= 7 ? 131072 : 786432);
+    return block_fits(N, M, D) && D >= (M <= 7 ? 131072 : 786432);
+}
+
+void launch_prep_block(int32_t N, int32_t M, int adjoint, const double *g_d, const double *h_d,
+                       double2 *cf, int32_t *tab, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_prep_block, dim3(5), dim3(256), 0, s, N, M, adjoint,
+                       (const double2 *)g_d, (const double2 *)h_d, cf, tab);
 }
 
 int apply_block_run(int32_t N, int32_t M, int64_t D, const double2 *cf, const int32_t *tab,
@@ -92,8 +102,7 @@ int apply_block_launch(int32_t N, int32_t M, int64_t D, const double *h_d, const
 {
     double2 *cf = (double2 *)ws_d;
     int *tab = (int *)(cf + split_total(M));
-    hipLaunchKernelGGL(k_prep_block, dim3(5), dim3(256), 0, s, N, M, adjoint,
-                       (const double2 *)g_d, (const double2 *)h_d, cf, tab);
+    launch_prep_block(N, M, adjoint, g_d, h_d, cf, tab, s);
     return apply_block_run(N, M, D, cf, tab, C_d, HC_d, s);
 }
 

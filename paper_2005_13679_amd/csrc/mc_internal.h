@@ -71,15 +71,27 @@ int rho1_generic(int32_t N, int32_t M, const mc_tables *t, const double *C_d, do
 // H.C with four rows per lane and targets in closed form (mc_block.h): whether
 // it serves the space, its workspace bytes, staging and launch, and the launch
 // alone on staged constants `cf` and tables `tab`.
+bool block_fits(int32_t N, int32_t M, int64_t D);
 bool block_serves(int32_t N, int32_t M, int64_t D);
 size_t block_workspace(int32_t N, int32_t M);
 // Workspace bytes without which no apply of M orbitals runs; one between
 // these and mc_workspace_size's takes the one-row kernels.
 size_t apply_workspace_least(int32_t M);
+int64_t block_items(int32_t N, int32_t M);
+void launch_prep_block(int32_t N, int32_t M, int adjoint, const double *g_d, const double *h_d,
+                       double2 *cf, int32_t *tab, hipStream_t s);
 int apply_block_launch(int32_t N, int32_t M, int64_t D, const double *h_d, const double *g_d,
                        int adjoint, const double *C_d, double *HC_d, void *ws_d, hipStream_t s);
 int apply_block_run(int32_t N, int32_t M, int64_t D, const double2 *cf, const int32_t *tab,
                     const double *C_d, double *HC_d, hipStream_t s);
+// The same over non-zero constants only (mc_block_sparse.hip; its workspace is
+// the larger one), and the lists of those constants.
+bool block_sparse_serves(int32_t N, int32_t M, int64_t D);
+size_t block_sparse_workspace(int32_t N, int32_t M);
+int apply_block_sparse_launch(int32_t N, int32_t M, int64_t D, const double *h_d,
+                              const double *g_d, const double *C_d, double *HC_d, void *ws_d,
+                              hipStream_t s);
+void launch_sparse_lists(int32_t M, const double2 *cf, int32_t *sl, hipStream_t s);
 // The one-row table-free apply (mc_direct.h): staging and launch.
 int apply_direct_launch(int32_t N, int32_t M, int64_t D, const double *h_d, const double *g_d,
                         int adjoint, const double *C_d, double *HC_d, void *ws_d, hipStream_t s);

@@ -1,6 +1,6 @@
 // H.C in the case-split form for interactions with many vanishing
 // coefficients (momentum-conserving plane-wave g, lattice models).  After the
-// case-split constants are staged, k_sparse_lists compacts the single jumps
+// case-split constants are staged, k_sparse_lists (mc_block_sparse.hip) compacts the single jumps
 // and the reduced double-jump slots whose constants are not all zero into
 // lists; the tile walks only those (the row's own term is always taken).
 // Entries are wave-uniform, orbitals run-time; the roots come from the
@@ -15,46 +15,14 @@ namespace mc {
 //   [0]                    number of active single jumps
 //   [kSlSingles + i]       active single jump j = a*M + b
 //   [kSlPairs + 2p]        first entry of pair p, [kSlPairs + 2p + 1] count
-//   [kSlEntries + e]       r | q << 8 | l << 16  (reduced slot r of its pair)
+//   [kSlEntries + e]       gd | q << 10 | l << 13 | k << 16 | s << 19: the jump
+//                          {k, s} -> {q, l}, constant number gd of GD
 constexpr int kSlSingles = 1;
 constexpr int kSlPairs = kSlSingles + 64;
 constexpr int kSlEntries = kSlPairs + 2 * 36;
 constexpr int kSlInts = kSlEntries + 8 * 28 + 28 * 21;   // M <= 8
 
 __device__ __forceinline__ bool nonzero(double2 v) { return v.x != 0.0 || v.y != 0.0; }
-
-// One thread builds the lists from the staged constants cf (layout of
-// mc_split.h).  Run after k_prep_split, before the apply.
-__global__ void k_sparse_lists(int M, const double2 *__restrict__ cf, int32_t *__restrict__ sl)
-{
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
-    const double2 *HS = cf + split_hs_offset(M), *GS = cf + split_gs_offset(M);
-    const double2 *GD = cf + split_gd_offset(M);
-    int ns = 0;
-    for (int j = 0; j < M * M; ++j) {
-        if (j / M == j % M) continue;
-        bool any = nonzero(HS[j]);
-        for (int c = 0; c < M; ++c) any = any || nonzero(GS[j * M + c]);
-        if (any) sl[kSlSingles + ns++] = j;
-    }
-    sl[0] = ns;
-    int p = 0, e = 0, co = 0;
-    for (int k = 0; k < M; ++k) {
-        for (int s = k; s < M; ++s, ++p) {
-            sl[kSlPairs + 2 * p] = e;
-            int r = 0;
-            for (int q = 0; q < M; ++q) {
-                for (int l = q; l < M; ++l) {
-                    if (q == k || q == s || l == k || l == s) continue;
-                    if (nonzero(GD[co + r])) sl[kSlEntries + e++] = r | (q << 8) | (l << 16);
-                    ++r;
-                }
-            }
-            co += r;
-            sl[kSlPairs + 2 * p + 1] = e - sl[kSlPairs + 2 * p];
-        }
-    }
-}
 
 template <int MT>
 __device__ __forceinline__ int occ_at(const int (&n)[MT], int m)
@@ -195,7 +163,7 @@ __device__ __forceinline__ void apply_tile_sparse(int64_t tile, int64_t D, int64
                     ent[i] = i0 + i < cnt ? sl[kSlEntries + first + i0 + i] : -1;
                     int32_t v = -1;
                     if (ent[i] >= 0) {
-                        const int r = ent[i] & 255, q = (ent[i] >> 8) & 255, l = (ent[i] >> 16) & 255;
+                        const int r = (ent[i] & 1023) - cbase, q = ent[i] >> 10 & 7, l = ent[i] >> 13 & 7;
                         if constexpr (MAP) {
                             v = buf_ld_i32(r2, (uint32_t)((r * kTile + lane) * 4), 0);
                         } else {
@@ -214,7 +182,7 @@ __device__ __forceinline__ void apply_tile_sparse(int64_t tile, int64_t D, int64
 #pragma unroll
                 for (int i = 0; i < SB; ++i) {
                     if (ent[i] < 0) break;
-                    const int r = ent[i] & 255, q = (ent[i] >> 8) & 255, l = (ent[i] >> 16) & 255;
+                    const int r = (ent[i] & 1023) - cbase, q = ent[i] >> 10 & 7, l = ent[i] >> 13 & 7;
                     const int nq = occ_at(n, q), nl = occ_at(n, l);
                     const double Bf = q == l ? sq[nq + 1] * sq[nq + 2] : sq[nq + 1] * sq[nl + 1];
                     const double2 Gv = GD[cbase + r];
