@@ -249,9 +249,10 @@ int mc_workspace_size(int32_t N, int32_t M, int32_t op, size_t *bytes);
  * No symmetry of h or g is assumed. */
 /* Spaces of more than 65,536 rows (M <= 8) are evaluated with every target in
  * closed form, as mc_apply_H_direct does there: it is faster than reading the
- * tables, which are checked and not read.  From 131,072 rows (786,432 for M =
- * 8) to 2^27, with M >= 3 and N < 4096, four rows per lane; else one, and so
- * too with a workspace smaller than mc_workspace_size's that holds the staged
+ * tables, which are checked and not read.  From 262,144 rows (131,072 for M =
+ * 7, 786,432 for M = 8) to 2^27, with M >= 3 and N < 4096, four rows per lane;
+ * else one, and so too with a workspace smaller than mc_workspace_size's that
+ * holds the staged
  * constants.  Results agree with the table-driven kernels up to rounding
  * order.  The same holds for mc_apply_H_adjoint and for the instances of a
  * batch. */

@@ -63,10 +63,13 @@ size_t block_workspace(int32_t N, int32_t M)
 // 16 G_a, G_a < D), and the root table 64 KB of LDS.  From below: its lanes
 // hold four rows, so it fills the GPU at four times the rows of the one-row
 // kernel, and its wavefronts take longer.  Measured against that kernel (us,
-// one row / four rows): M = 5, N = 30 (46 k rows) 26 / 29, N = 40 (136 k) 31 /
-// 30, N = 50 (316 k) 44 / 35; M = 6, N = 20 (53 k) 46 / 50, N = 27 (201 k) 63 /
-// 49; M = 7, N = 16 (75 k) 72 / 78, N = 20 (230 k) 112 / 99; M = 8, N = 17
-// (346 k) 223 / 321, N = 20 (888 k) 519 / 460.
+// one row / four rows): M = 3, N = 700 (246 k rows) 11 / 13, N = 1,000 (502 k)
+// 18 / 15; M = 4, N = 110 (234 k) 15 / 18, N = 130 (383 k) 21 / 19; M = 5, N = 42
+// (163 k) 24 / 31, N = 48 (271 k) 35 / 35, N = 52 (367 k) 39 / 35; M = 6, N = 28
+// (237 k) 53 / 56, N = 30 (325 k) 58 / 56; M = 7, N = 18 (135 k) 81 / 80, N = 22
+// (377 k) 126 / 102; M = 8, N = 19 (658 k) 415 / 414, N = 21 (1,184 k) 720 / 621.
+// Just past a whole number of wavefronts per SIMD it can lose a few per cent
+// above the line (M = 6, N = 32, 436 k rows, 77 / 82; M = 5, N = 56, 48 / 49).
 bool block_fits(int32_t N, int32_t M, int64_t D)
 {
     return M >= 3 && M <= 8 && N < 4096 && D * 32 <= (int64_t)0xFFFFFFF0u;
@@ -74,7 +77,7 @@ bool block_fits(int32_t N, int32_t M, int64_t D)
 
 bool block_serves(int32_t N, int32_t M, int64_t D)
 {
-    return block_fits(N, M, D) && D >= (M <= 7 ? 131072 : 786432);
+    return block_fits(N, M, D) && D >= (M <= 6 ? 262144 : M == 7 ? 131072 : 786432);
 }
 
 void launch_prep_block(int32_t N, int32_t M, int adjoint, const double *g_d, const double *h_d,

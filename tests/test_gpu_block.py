@@ -1,7 +1,7 @@
-"""Table-free H.C with four rows per lane (spaces of at least 131,072 rows,
-786,432 for 8 orbitals): against the oracle at the smallest spaces it serves,
-every remainder of N by 4, each orbital count, with general inputs and the
-adjoint; and which rows a value that is not finite reaches.
+"""Table-free H.C with four rows per lane (spaces of at least 262,144 rows,
+131,072 for 7 orbitals, 786,432 for 8): against the oracle at the smallest
+spaces it serves, every remainder of N by 4, each orbital count, with general
+inputs and the adjoint; and which rows a value that is not finite reaches.
 
 Tolerance: 1e-12 relative to the largest element, the bar of every apply (a
 row sums at most 869 products of size max|H.C| or less in double)."""
@@ -20,7 +20,9 @@ pytestmark = pytest.mark.gpu
 TOL = 1e-12
 # the smallest N served per M, its neighbours below (one row per lane) and above
 SIZES = [(510, 3), (511, 3), (513, 3), (90, 4), (91, 4), (92, 4), (39, 5), (40, 5), (41, 5),
-         (42, 5), (43, 5), (24, 6), (25, 6), (26, 6), (17, 7), (18, 7), (19, 8), (20, 8)]
+         (42, 5), (43, 5), (24, 6), (25, 6), (26, 6), (17, 7), (18, 7), (19, 8), (20, 8),
+         (722, 3), (723, 3), (725, 3), (114, 4), (115, 4), (116, 4), (47, 5), (48, 5), (49, 5),
+         (50, 5), (51, 5), (28, 6), (29, 6), (30, 6)]
 
 
 def dev(x):
@@ -64,7 +66,8 @@ def coupled(mc, N, M, k):
     return sorted(mc.hash_occ(N, M, o) for o in seen)
 
 
-@pytest.mark.parametrize("N,M", [(511, 3), (91, 4), (41, 5), (25, 6), (18, 7), (20, 8)])
+@pytest.mark.parametrize("N,M", [(511, 3), (91, 4), (41, 5), (25, 6), (18, 7), (20, 8), (723, 3),
+                                 (116, 4), (49, 5), (30, 6)])
 def test_values_that_are_not_finite_stay_with_coupled_rows(mc, N, M):
     D = mc.dim(N, M)
     h, g, C, rng = general(N, M, D)
