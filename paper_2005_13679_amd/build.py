@@ -19,8 +19,14 @@ LIB = os.path.join(HERE, "libmc.so")
 
 # (source, object, extra flags); mc_tiles.hip holds the kernels of one orbital
 # count and part per compilation, the longest ones first
-SOURCES = [("mc_tiles.hip", f"mc_tiles_{m}_{p}", (f"-DMC_TILES_M={m}", f"-DMC_TILES_PART={p}"))
+# The one-row kernels fuse multiplications and additions per expression, not as the
+# back end sees fit: the same tile then has the same bits in every kernel it is
+# compiled into (alone, in a batch's group, in a joint launch).
+TILE_FLAGS = ("-ffp-contract=on",)
+SOURCES = [("mc_tiles.hip", f"mc_tiles_{m}_{p}",
+            (f"-DMC_TILES_M={m}", f"-DMC_TILES_PART={p}", *TILE_FLAGS))
            for m in range(8, 0, -1) for p in (2, 0, 1)]
+SOURCES += [("mc_joint.hip", f"mc_joint_{k}", (f"-DMC_JOINT_KIND={k}", *TILE_FLAGS)) for k in range(5)]
 SOURCES += [(f"{n}.hip", n, ()) for n in
             ("mc_ops", "mc_block", "mc_block_sparse", "mc_host", "mc_tables", "mc_direct", "mc_batch", "mc_krylov",
              "mc_gram_direct", "mc_gram_tables")]

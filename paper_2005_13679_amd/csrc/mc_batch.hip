@@ -87,11 +87,14 @@ struct mc_batch {
     int32_t count;
     int32_t ngroups;
     int32_t group_M[48];
-    int32_t group_kind[48];   // BatchKind of the group's instances
+    int32_t group_kind[48];   // ApplyKind of the group's instances
     int32_t group_first[48];  // first entry in the sorted instance order
     int32_t group_count[48];
     int64_t group_tiles[48];
     int64_t group_blocks[48];
+    bool group_joined[48];    // runs with others of its kind in one launch
+    mc::JointGroups joint[mc::kJointKinds];   // those groups, by kind
+    int64_t joint_blocks[mc::kJointKinds];
     int64_t nchunks;
     int64_t total_len;        // batch-vector length
     int32_t order;
@@ -108,6 +111,46 @@ struct mc_batch {
 };
 
 namespace mc {
+
+// Puts small groups of one kind, the one with the most orbitals first, into one
+// launch, two at least.  Small: at most 64 tiles per CU and eight wavefronts, 16
+// for the chained case-split sum.  One apply of a batch, us, each group a launch
+// / up to 16 / up to 64, without tables, through the map, chained: 24 instances
+// (N 8..20, M 3..5) 45 / 36 / 36, 55 / 45 / 45, 50 / 37 / 37; 30 (8..20, 3..6)
+// 127 / 106 / 106, 180 / 139 / 139, 139 / 114 / 114; 100 (8..28, 3..5) 170 / 165
+// / 135, 232 / 224 / 191, 166 / 155 / 163; 80 (20..40, 4..5) 454 / 448 / 433, 561
+// / 561 / 532, 447 / 448 / 486; 300 (40..120, 3..4) 1,095 / 1,096 / 1,093, 1,252 /
+// 1,206 / 1,206, 1,278 / 1,239 / 1,236.
+static void batch_join(mc_batch *b, int cus)
+{
+    memset(b->group_joined, 0, sizeof b->group_joined);
+    memset(b->joint, 0, sizeof b->joint);
+    for (int kind = 0; kind < kJointKinds; ++kind) {
+        JointGroups &J = b->joint[kind];
+        int64_t blocks = 0;
+        int member[48], n = 0;
+        for (int gi = b->ngroups - 1; gi >= 0; --gi) {
+            const int M = b->group_M[gi];
+            if (b->group_kind[gi] != kind || M < kJointMinM || M > kJointMaxM || b->order != 3)
+                continue;
+            const bool parts = small_parts(M, kind);
+            const int64_t tiles = b->group_tiles[gi];
+            const int64_t need = parts ? tiles : (tiles + kTileParts - 1) / kTileParts;
+            if (need > (int64_t)(kind == kSplitChain ? 16 : 64) * cus) continue;
+            const int64_t own = parts ? b->group_blocks[gi]
+                                      : (b->group_blocks[gi] * 4 + kTileParts - 1) / kTileParts;
+            J.g[n] = JointGroup{M, b->group_first[gi], b->group_count[gi],
+                                batch_grab(tiles, parts ? own : own * kTileParts), gi,
+                                (int32_t)blocks, tiles};
+            member[n++] = gi;
+            blocks += own;
+        }
+        if (n < 2) continue;
+        J.n = n;
+        b->joint_blocks[kind] = blocks;
+        for (int i = 0; i < n; ++i) b->group_joined[member[i]] = true;
+    }
+}
 
 __global__ void k_batch_prep(const BatchInst *__restrict__ inst, uint32_t *__restrict__ counters)
 {
@@ -545,6 +588,7 @@ int mc_batch_create(int32_t count, const mc_batch_item *items, const mc_batch_sc
         b->group_blocks[gi] = need < cap_blocks ? need : cap_blocks;
         if (b->group_blocks[gi] < 1) b->group_blocks[gi] = 1;
     }
+    batch_join(b, cus);
     b->inst_d = (BatchInst *)(base + L.inst);
     b->tile_prefix_d = (int64_t *)(base + L.prefix);
     b->chunks_d = (BatchChunk *)(base + L.chunks);
@@ -600,7 +644,15 @@ static int batch_apply_staged(const mc_batch *b, const double *C_d, double *HC_d
                                        C_d + 2 * o.vec_off, HC_d + 2 * o.vec_off, s);
         if (st) return st;
     }
+    for (int kind = 0; kind < kJointKinds; ++kind) {
+        if (!b->joint[kind].n) continue;
+        const JointCall c{&b->joint[kind], b->joint_blocks[kind], b->inst_d, b->tile_prefix_d,
+                          b->counters_d, b->coef_d, (const double2 *)C_d, (double2 *)HC_d, s};
+        const int st = tiles_joint(kind, c);
+        if (st) return st;
+    }
     for (int gi = 0; gi < b->ngroups; ++gi) {
+        if (b->group_joined[gi]) continue;
         const int M = b->group_M[gi];
         const int64_t blocks = b->group_blocks[gi];
         const int64_t workers = small_parts(M, b->group_kind[gi]) ? blocks : blocks * 4;

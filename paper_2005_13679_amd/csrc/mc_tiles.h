@@ -96,6 +96,44 @@ MC_TILES_DECLARE(8)
      : (M) == 5 ? tiles_##what##_5(call) : (M) == 6 ? tiles_##what##_6(call)              \
      : (M) == 7 ? tiles_##what##_7(call) : tiles_##what##_8(call))
 
+// Groups of one kind in one launch (mc_joint.hip): group i has the blocks from
+// block0 on, up to the next group's.
+struct JointGroup {
+    int32_t M, first, count, grab, counter, block0;
+    int64_t items;
+};
+constexpr int kJointMinM = 3, kJointMaxM = 6, kJointKinds = 5;
+struct JointGroups {
+    int32_t n;
+    JointGroup g[kJointMaxM - kJointMinM + 1];
+};
+struct JointCall {
+    const JointGroups *groups;
+    int64_t blocks;
+    const BatchInst *inst;
+    const int64_t *prefix;
+    uint32_t *counters;
+    const double2 *coef, *C;
+    double2 *HC;
+    hipStream_t s;
+};
+int tiles_joint_0(const JointCall &);
+int tiles_joint_1(const JointCall &);
+int tiles_joint_2(const JointCall &);
+int tiles_joint_3(const JointCall &);
+int tiles_joint_4(const JointCall &);
+inline int tiles_joint(int kind, const JointCall &c)
+{
+    switch (kind) {
+    case kPaperMap: return tiles_joint_0(c);
+    case kPaperChain: return tiles_joint_1(c);
+    case kSplitMap: return tiles_joint_2(c);
+    case kSplitChain: return tiles_joint_3(c);
+    case kDirect: return tiles_joint_4(c);
+    default: return MC_EINVAL;
+    }
+}
+
 // Blocks of 256 threads per four tiles, or one block per tile whose wavefronts
 // share it (from M = 5 on, in small spaces; mc_apply.h has the reason).
 inline bool small_parts(int M, int kind) { return M >= 5 && kind != kDirectLarge; }

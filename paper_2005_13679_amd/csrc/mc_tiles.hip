@@ -5,6 +5,7 @@
 
 #include "mc_apply.h"
 #include "mc_direct.h"
+#include "mc_group.h"
 #include "mc_split.h"
 
 #define MC_TILES_NAME2(what, M) tiles_##what##_##M
@@ -125,8 +126,6 @@ int MC_TILES_NAME(direct)(const DirectCall &c)
 // at a time from a per-group counter (dynamic balance, like a plain launch).
 // With NP > 1 a worker is a block, whose wavefronts share each tile, instead of
 // a wavefront.
-constexpr int kBatchMaxN = 255;
-
 template <int MT, int KIND, int NP>
 __global__ __launch_bounds__(NP == 1 ? 256 : NP * 64) __attribute__((amdgpu_waves_per_eu(MC_APPLY_WAVES)))
 void k_batch_apply(const BatchInst *__restrict__ inst, const int64_t *__restrict__ prefix,
@@ -140,42 +139,12 @@ void k_batch_apply(const BatchInst *__restrict__ inst, const int64_t *__restrict
     __shared__ uint32_t taken;
     const Part<NP> part{NP == 1 ? 0 : wave_in_block()};
     auto tile_body = [&](int64_t i, int &j) __attribute__((always_inline)) {
-        // instance of item i (prefix is non-decreasing; a worker visits items
-        // in increasing order, so the search resumes where it stopped)
-        while (j + 1 < count && prefix[first + j + 1] <= i) ++j;
-        const BatchInst I = inst[first + j];
-        const int64_t tile = i - prefix[first + j];
-        const double2 *C = Cb + I.vec_off, *gp = coef + I.gp_off, *hp = coef + I.hp_off;
-        double2 v;
-        if constexpr (KIND == kDirect || KIND == kDirectLarge)
-            v = apply_tile_direct<MT, false>(part, tile, I.N, I.dim, sq, gp, C);
-        else
-            v = apply_tile_tables<MT, uint8_t, KIND>(part, tile, I.dim, I.cap, sq, I.occ, I.t1,
-                                                     I.pmask, I.t2_off, I.t2,
-                                                     KIND == kPaperMap || KIND == kPaperChain ? hp : gp,
-                                                     gp, C);
-        store_tile<NP>(v, part.part, tile, I.dim, red, HCb + I.vec_off);
+        batch_item<MT, KIND, NP>(part, i, j, inst, prefix, first, count, sq, red, coef, Cb, HCb);
     };
     int j = 0;
     constexpr int WB = NP == 1 ? 4 : 1;   // workers per block
     if (order == 3) {
-        // dynamic: take `grab` items at a time from the group's counter (a
-        // vector atomic of one lane; the count is zeroed before each apply)
-        for (;;) {
-            uint32_t base = 0;
-            if constexpr (NP == 1) {
-                if ((threadIdx.x & 63) == 0) base = atomicAdd(counter, (uint32_t)grab);
-                base = __builtin_amdgcn_readfirstlane(base);
-            } else {
-                __syncthreads();   // the last value is read
-                if (threadIdx.x == 0) taken = atomicAdd(counter, (uint32_t)grab);
-                __syncthreads();
-                base = __builtin_amdgcn_readfirstlane(taken);
-            }
-            if ((int64_t)base >= items) break;
-            const int64_t end = (int64_t)base + grab < items ? (int64_t)base + grab : items;
-            for (int64_t i = base; i < end; ++i) tile_body(i, j);
-        }
+        batch_take<NP>(counter, items, grab, &taken, tile_body);
         return;
     }
     const int64_t W = nblocks * WB;

@@ -73,3 +73,43 @@ def test_workspace_with_room_for_the_constants_only(mc, oracle_native, N, M):
     ref = oracle_native.apply_h(N, M, h, g, C, rows)
     assert rel_inf(out[torch.from_numpy(rows).cuda()].cpu().numpy(), ref) <= TOL
     assert lib.mc_apply_H_direct(N, M, p(hd), p(gd), p(Cd), p(out), p(ws), least - 1, st) == L.MC_ENOMEM
+
+
+@pytest.mark.parametrize("form,maps", KINDS)
+def test_groups_of_several_orbital_counts(mc, form, maps):
+    """Small groups of 3 to 6 orbitals share a launch (with order 3), others
+    have their own: the bits of each instance alone, eagerly and replayed from a
+    graph with other work between the replays."""
+    shapes = [(1, 3), (10, 3), (11, 4), (12, 4), (3, 5), (14, 5), (9, 6), (1, 6), (6, 7), (60, 2)]
+    items, alone, vecs = [], [], []
+    for i, (N, M) in enumerate(shapes):
+        rng = np.random.default_rng(i)
+        h = dev(rng.standard_normal((M, M)) + 1j * rng.standard_normal((M, M)))
+        g = dev(rng.standard_normal((M,) * 4) + 1j * rng.standard_normal((M,) * 4))
+        s = mc.DirectSpace(N, M) if form == "direct" else \
+            mc.build_tables(N, M, form=form, double_jumps=maps)
+        C = dev(rng.standard_normal(mc.dim(N, M)) + 1j * rng.standard_normal(mc.dim(N, M)))
+        items.append((s, h, g))
+        vecs.append(C)
+        alone.append(mc.apply_H(h, g, C, s))
+    for pick in (range(len(items)), [1, 2], [0, 6], [4, 5], [2, 3]):
+        x = torch.cat([vecs[i] for i in pick])
+        for sched in (None, {"blocks_per_cu": 1, "order": 3}, {"blocks_per_cu": 2, "order": 0}):
+            b = mc.Batch([items[i] for i in pick], sched)
+            out = b.vector()
+            for _ in range(2):
+                b.apply_H(x, out.zero_())
+                for k, i in enumerate(pick):
+                    assert torch.equal(b.segment(out, k), alone[i]), (shapes[i], sched)
+        b = mc.Batch([items[i] for i in pick])
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            b.apply_H(x, out)
+        for _ in range(3):
+            out.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            for k, i in enumerate(pick):
+                assert torch.equal(b.segment(out, k), alone[i]), shapes[i]
