@@ -79,21 +79,29 @@ __host__ __device__ constexpr int col_q() { return L == 1 ? c : pair_k(MT, c); }
 template <int MT, int L, int c>
 __host__ __device__ constexpr int col_l() { return L == 1 ? -1 : pair_s(MT, c); }
 
-// Ladder amplitude of column (q, l) (l < 0: one particle) on occupations m;
-// from M = 5 on the roots come from an LDS table of sqrt(i), i = 0 .. N+2
-// (below, N can be too large for one).
+// Ladder amplitude of column (q, l) (l < 0: one particle) on occupations m.
+// From M = 5 on it comes from an LDS table of { sqrt(i), sqrt(1 / 2i) }, i = 0 ..
+// N+2 (below, N can be too large for one): the product f of two roots, and one
+// Newton step f + (a b - f f) / 2f on it, after which it is rounded once, as the
+// root of the product is.  Without the step the error does not average out where
+// few occupations are large (N=20, M=7, against 64 bits 1.9e-16; 1.6e-16 with the
+// root of the product).
 template <int MT, int q, int l>
-__device__ __forceinline__ double lift_amp(const int (&m)[MT], const double *sq)
+__device__ __forceinline__ double lift_amp(const int (&m)[MT], const double2 *roots)
 {
-    if constexpr (kLdsRoots<MT>) {
-        if constexpr (l < 0) return sq[m[q] + 1];
-        else if constexpr (q == l) return sq[m[q] + 1] * sq[m[q] + 2];
-        else return sq[m[q] + 1] * sq[m[l] + 1];
+    const double a = (double)m[q] + 1.0;
+    if constexpr (l < 0) {
+        if constexpr (kLdsRoots<MT>) return roots[m[q] + 1].x;
+        else return sqrt(a);
     } else {
-        const double a = (double)m[q] + 1.0;
-        if constexpr (l < 0) return sqrt(a);
-        else if constexpr (q == l) return sqrt(a * (a + 1.0));
-        else return sqrt(a * ((double)m[l] + 1.0));
+        const double b = q == l ? a + 1.0 : (double)m[l] + 1.0;
+        if constexpr (kLdsRoots<MT>) {
+            const double2 ra = roots[m[q] + 1], rb = roots[q == l ? m[q] + 2 : m[l] + 1];
+            const double f = ra.x * rb.x;
+            return fma(fma(-f, f, a * b), ra.y * rb.y, f);
+        } else {
+            return sqrt(a * b);
+        }
     }
 }
 
@@ -103,7 +111,7 @@ constexpr int kGramBatch = 12;   // gathers per basic block
 // index (-1: none), the values amp * C[index] go to xrow[c].
 template <int MT, int L, bool BIGC, int C0, class Tgt, int... Is>
 __device__ __forceinline__ void gram_batch(std::integer_sequence<int, Is...>, const Tgt &tgt,
-                                           const int (&m)[MT], const double *sq,
+                                           const int (&m)[MT], const double2 *sq,
                                            const Gather<BIGC> &ldc, double2 *xrow)
 {
     constexpr int P = Lift<MT, L>::P;
@@ -133,7 +141,7 @@ __device__ __forceinline__ void gram_batch(std::integer_sequence<int, Is...>, co
 
 template <int MT, int L, bool BIGC, class Tgt, int... Bs>
 __device__ __forceinline__ void gram_row(std::integer_sequence<int, Bs...>, const Tgt &tgt,
-                                         const int (&m)[MT], const double *sq,
+                                         const int (&m)[MT], const double2 *sq,
                                          const Gather<BIGC> &ldc, double2 *xrow)
 {
     (
@@ -204,7 +212,7 @@ struct DirectSource {
     }
 
     // the lane's row of X
-    __device__ __forceinline__ bool fill(int64_t ch, int lane, const double *sq,
+    __device__ __forceinline__ bool fill(int64_t ch, int lane, const double2 *sq,
                                          const Gather<BIGC> &ldc, double2 *xrow) const
     {
         Tgt tg;
@@ -327,7 +335,7 @@ struct MapSource {
         return __builtin_amdgcn_readfirstlane(__ballot(tg.live) != 0);
     }
 
-    __device__ __forceinline__ bool fill(int64_t tile, int lane, const double *sq,
+    __device__ __forceinline__ bool fill(int64_t tile, int lane, const double2 *sq,
                                          const Gather<BIGC> &ldc, double2 *xrow) const
     {
         Raw w;
@@ -355,7 +363,7 @@ __device__ __forceinline__ void gram_issue(std::integer_sequence<int, Cs...>, co
 
 template <int MT, int L, int... Cs>
 __device__ __forceinline__ void gram_commit(std::integer_sequence<int, Cs...>, const int (&m)[MT],
-                                            const double *sq, const double2 (&v)[Lift<MT, L>::P], double2 *xrow)
+                                            const double2 *sq, const double2 (&v)[Lift<MT, L>::P], double2 *xrow)
 {
     (
         [&] {
@@ -427,8 +435,9 @@ __global__ __launch_bounds__(64) void k_gram(Src src, int64_t DN, int64_t chunks
     extern __shared__ double2 X[];   // [64][STRIDE], then the roots
     const int lane = threadIdx.x;
     const int wave = blockIdx.x;
-    double *sq = (double *)(X + 64 * LF::STRIDE);
-    for (int i = lane; i < nroots; i += 64) sq[i] = sqrt((double)i);
+    double2 *sq = X + 64 * LF::STRIDE;
+    for (int i = lane; i < nroots; i += 64)
+        sq[i] = make_double2(sqrt((double)i), i > 0 ? sqrt(0.5 / (double)i) : 0.0);
 #pragma unroll
     for (int c = LF::P; c < LF::PP; ++c) X[lane * LF::STRIDE + c] = make_double2(0.0, 0.0);
     __syncthreads();
@@ -572,7 +581,7 @@ template <int MT, int L>
 void gram_shape_t(int N, int64_t chunks, GramShape *g)
 {
     g->nroots = gram_roots(N, MT);
-    g->lds = Lift<MT, L>::LDS + (size_t)g->nroots * 8;
+    g->lds = Lift<MT, L>::LDS + (size_t)g->nroots * 16;
     int64_t per_cu = (160 * 1024) / (int64_t)g->lds;
     per_cu = per_cu < 1 ? 1 : (per_cu > kGramWavesPerCu ? kGramWavesPerCu : per_cu);
     const int64_t w = 256 * per_cu;
