@@ -250,12 +250,10 @@ int mc_workspace_size(int32_t N, int32_t M, int32_t op, size_t *bytes);
 /* Spaces of more than 65,536 rows (M <= 8) are evaluated with every target in
  * closed form, as mc_apply_H_direct does there: it is faster than reading the
  * tables, which are checked and not read.  From 262,144 rows (131,072 for M =
- * 7, 786,432 for M = 8) to 2^27, with M >= 3 and N < 4096, four rows per lane;
- * else one, and so too with a workspace smaller than mc_workspace_size's that
- * holds the staged
- * constants.  Results agree with the table-driven kernels up to rounding
- * order.  The same holds for mc_apply_H_adjoint and for the instances of a
- * batch. */
+ * 7, 786,432 for M = 8) to 2^27, with M >= 4 and N < 4096, four rows per lane;
+ * else one, and so too with a workspace too small for that kernel's tables.
+ * Results agree with the table-driven kernels up to rounding order.  The same
+ * holds for mc_apply_H_adjoint and for the instances of a batch. */
 /* Table reads of the apply through a double-jump map (host query, no
  * device work).  Within a run of rows (consecutive indices that differ by one
  * particle moved between orbitals 0 and 1, Eq. TotalCost) a jump's target is
@@ -288,8 +286,9 @@ int mc_apply_H_adjoint(int32_t N, int32_t M, const double *h_d, const double *g_
  * plane-wave g of the Lieb-Liniger model, Sec. VI: 44 of 462 true double
  * jumps per row survive at M = 7, and no single-jump term).  After staging,
  * one kernel lists the single jumps and reduced slots whose constants are not
- * all zero; the apply gathers only those.  Needs reduced-form tables (with or
- * without the map) and M <= 8, else MC_EINVAL; other arguments as mc_apply_H.
+ * all zero; the apply gathers only those, from 131,072 rows to 2^27 (M >= 3)
+ * with targets in closed form.  Needs reduced-form tables (with or without the
+ * map) and M <= 8, else MC_EINVAL; other arguments as mc_apply_H.
  * Results equal mc_apply_H's up to rounding order for any g. */
 int mc_apply_H_sparse(int32_t N, int32_t M, const double *h_d, const double *g_d,
                       const mc_tables *t, const double *C_d, double *HC_d,

@@ -20,7 +20,7 @@ __global__ __launch_bounds__(256) void k_prep_block(int N, int M, int adjoint,
         stage_block_tables(N, M, tab, sum);
 }
 
-// Bound: the L1's tag look-ups.  At M = 5 a wavefront's 296 gathers make 21
+// Bound: the L1's look-ups.  At M = 5 a wavefront's 296 gathers make 21
 // look-ups each (16 when they start on 64 bytes), 95 % of the kernel's cycles;
 // the vector ALU is at 72 % and FETCH_SIZE at 2.7 GB.  One item per lane, 256
 // consecutive items per block, blocks in XCD chunks as in the one-row kernel.
@@ -58,26 +58,29 @@ size_t block_workspace(int32_t N, int32_t M)
     return (size_t)split_total(M) * 16 + (size_t)block_table_ints(N, M) * 4;
 }
 
-// Which spaces the four-row kernel serves.  From above: every offset of a
-// gather, the out-of-range ones included, has to fit 32 bits (16 D plus
-// 16 G_a, G_a < D), and the root table 64 KB of LDS.  From below: its lanes
-// hold four rows, so it fills the GPU at four times the rows of the one-row
-// kernel, and its wavefronts take longer.  Measured against that kernel (us,
-// one row / four rows): M = 3, N = 700 (246 k rows) 11 / 13, N = 1,000 (502 k)
-// 18 / 15; M = 4, N = 110 (234 k) 15 / 18, N = 130 (383 k) 21 / 19; M = 5, N = 42
-// (163 k) 24 / 31, N = 48 (271 k) 35 / 35, N = 52 (367 k) 39 / 35; M = 6, N = 28
-// (237 k) 53 / 56, N = 30 (325 k) 58 / 56; M = 7, N = 18 (135 k) 81 / 80, N = 22
-// (377 k) 126 / 102; M = 8, N = 19 (658 k) 415 / 414, N = 21 (1,184 k) 720 / 621.
-// Just past a whole number of wavefronts per SIMD it can lose a few per cent
-// above the line (M = 6, N = 32, 436 k rows, 77 / 82; M = 5, N = 56, 48 / 49).
+// What the kernel's addresses allow: every offset of a gather, the out-of-range
+// ones included, has to fit 32 bits (16 D plus 16 G_a, G_a < D), and the root
+// table 64 KB of LDS.
 bool block_fits(int32_t N, int32_t M, int64_t D)
 {
     return M >= 3 && M <= 8 && N < 4096 && D * 32 <= (int64_t)0xFFFFFFF0u;
 }
 
+// Which spaces the four-row kernel serves.  Its lanes hold four rows, so it fills
+// the GPU at four times the rows of the one-row kernel, and its wavefronts take
+// longer.  Measured against that kernel (us, one row / four rows): M = 4, N = 110
+// (234 k rows) 15 / 18, N = 130 (383 k) 21 / 19; M = 5, N = 42 (163 k) 24 / 31,
+// N = 48 (271 k) 35 / 35, N = 52 (367 k) 39 / 35; M = 6, N = 28 (237 k) 53 / 56,
+// N = 30 (325 k) 58 / 56; M = 7, N = 18 (135 k) 81 / 80, N = 22 (377 k) 126 / 102;
+// M = 8, N = 19 (658 k) 415 / 414, N = 21 (1,184 k) 720 / 621.  Just past a whole
+// number of wavefronts per SIMD it can lose a few per cent above the line (M = 6,
+// N = 32, 436 k rows, 77 / 82; M = 5, N = 56, 48 / 49).
+// Three orbitals stay with the one-row kernel, which takes the root of a product
+// where this one multiplies two rounded roots: against 64 bits, N = 900, mean of
+// eight states, 2.77e-16 and 2.94e-16, for 18 and 15 us at N = 1,000.
 bool block_serves(int32_t N, int32_t M, int64_t D)
 {
-    return block_fits(N, M, D) && D >= (M <= 6 ? 262144 : M == 7 ? 131072 : 786432);
+    return M >= 4 && block_fits(N, M, D) && D >= (M <= 6 ? 262144 : M == 7 ? 131072 : 786432);
 }
 
 void launch_prep_block(int32_t N, int32_t M, int adjoint, const double *g_d, const double *h_d,
@@ -93,7 +96,7 @@ int apply_block_run(int32_t N, int32_t M, int64_t D, const double2 *cf, const in
     const int64_t items = block_items(N, M);
     const int64_t nblocks = (items + 255) / 256;
     const size_t lds = (size_t)(N + 3 + kBlockRows) * 8 + (size_t)block_table_ints(N, M) * 4;
-    MC_DISPATCH_M(M, if constexpr (MT >= 3 && MT <= 8) {
+    MC_DISPATCH_M(M, if constexpr (MT >= 4 && MT <= 8) {
         hipLaunchKernelGGL((k_apply_block<MT>), dim3(nblocks), dim3(256), lds, s, N, D, (int)items,
                            nblocks, tab, cf, (const double2 *)C_d, (double2 *)HC_d);
     });
