@@ -43,14 +43,29 @@ PATHS = {
     "paper_chained": ("paper", False),     # the paper's sum, every slot chained
     "direct": (None, False),               # case-split sum, no table: targets in closed form
 }
-# dominant kernel of each path (the one the roofline and profiles refer to)
-KERNELS = {
-    "reduced_map": "k_apply_split<5, uint8, false, MAP=true>",
-    "reduced_chained": "k_apply_split<5, uint8, false, MAP=false>",
-    "paper_map": "k_apply<5, uint8, false>",
-    "paper_chained": "k_apply_chained<5, uint8, false>",
-    "direct": "k_apply_direct<5, false>",
-}
+# Spaces of more rows are evaluated in closed form whatever the tables hold: an
+# apply then reads the coefficients only.
+TABLE_ROWS = 65536
+# dominant kernel of each path on such spaces (the one the roofline and profiles
+# refer to)
+KERNELS = {p: "k_apply_block<5>" for p in PATHS}
+
+
+def apply_bytes(mc, tab, N: int, M: int, path: str) -> dict:
+    """Bytes one apply must move through the kernel that runs it, each once."""
+    D = math.comb(N + M - 1, N)
+    if D > TABLE_ROWS and M <= 8:
+        return algorithmic_bytes(N, M, "direct")
+    return stream_bytes(mc, tab) if PATHS[path][1] else algorithmic_bytes(N, M, path)
+
+
+def kernel_name(path: str, N: int, M: int) -> str:
+    D = math.comb(N + M - 1, N)
+    if D >= (262144 if M <= 6 else 131072 if M == 7 else 786432) and M >= 4:
+        return KERNELS[path].replace("<5", f"<{M}")
+    if D > TABLE_ROWS or PATHS[path][0] is None:
+        return f"k_apply_direct<{M}>"
+    return f"k_apply_tables<{M}>"
 
 
 def algorithmic_bytes(N: int, M: int, path: str = "reduced_map") -> dict:
@@ -128,18 +143,10 @@ def stream_bytes(mc, tab) -> dict:
 
 
 # what the counters show limits each path's apply kernel (the HBM roofline is
-# the one that bounds the byte model; these kernels stop short of it)
-LIMITERS = {
-    "reduced_map": "texture data path (98 % busy, 36 % of it waiting on L1 misses of the anchor "
-                   "gathers) and vector ALU (2,550 instructions per tile, about 68 % of the "
-                   "cycles): 195 vector memory reads per tile; HBM-side traffic 27.1 GB per apply "
-                   "at 3.4 TB/s (rocprofv3 FETCH_SIZE)",
-    "reduced_chained": "coefficient gathers through L1/TA (chained second hops)",
-    "paper_map": "vector ALU (the paper's 395 slots of arithmetic per row on 131 gathered "
-                 "targets) and the anchor gathers",
-    "paper_chained": "coefficient gathers through L1/TA (chained second hops)",
-    "direct": "vector ALU (closed-form targets and amplitudes) and coefficient gathers",
-}
+# the one that bounds the byte model; the kernel stops short of it)
+LIMITERS = {p: "gathers through the L1: 299 of 64 x 16 bytes per 256 rows at 21 look-ups each, 95 % "
+               "of the cycles; vector ALU 73 % (rocprofv3 TCP_TOTAL_CACHE_ACCESSES, "
+               "SQ_ACTIVE_INST_VALU)" for p in PATHS}
 TARGET_FRAC = 0.60   # of HBM peak on the path's byte model, N = 200, M = 5
 FP64_PEAK_TFLOPS = 78.6
 
@@ -166,13 +173,8 @@ def rho_models(N: int, M: int) -> dict:
 
 
 # sources each path's apply kernel is built from
-KERNEL_SOURCES = {
-    "reduced_map": ("mc_ops.hip", "mc_internal.h", "mc_apply.h", "mc_split.h"),
-    "reduced_chained": ("mc_ops.hip", "mc_internal.h", "mc_apply.h", "mc_split.h"),
-    "paper_map": ("mc_ops.hip", "mc_internal.h", "mc_apply.h", "mc_split.h"),
-    "paper_chained": ("mc_ops.hip", "mc_internal.h", "mc_apply.h"),
-    "direct": ("mc_ops.hip", "mc_internal.h", "mc_apply.h", "mc_split.h", "mc_direct.h"),
-}
+KERNEL_SOURCES = {p: ("mc_block.hip", "mc_block.h", "mc_internal.h")
+                  + (("mc_direct.h",) if p == "direct" else ()) for p in PATHS}
 
 
 def kernel_source_hash(path: str = "reduced_map") -> str:
@@ -566,9 +568,7 @@ def main(argv=None):
     ms = start.elapsed_time(end) / args.steps
     print(f"[bench] {args.steps} applies ({args.path}): {ms:.3f} ms each", file=sys.stderr, flush=True)
 
-    B = algorithmic_bytes(N, M, args.path)
-    if has_map:
-        B = stream_bytes(mc, tab)
+    B = apply_bytes(mc, tab, N, M, args.path)
     achieved = B["total"] / (ms * 1e-3) / 1e9
     traffic = measured_traffic(N, M, args.path)
     out = {
@@ -589,7 +589,7 @@ def main(argv=None):
                    "N": N, "M": M, "dim": D, "path": args.path, "table_form": form,
                    "double_jump_map": has_map, "parallelism": "single GPU"},
         "roofline": {
-            "kernel": KERNELS[args.path].replace("<5", f"<{M}"),
+            "kernel": kernel_name(args.path, N, M),
             "bound": "hbm",
             "achieved": achieved,
             "peak": HBM_PEAK_GBS,
@@ -640,12 +640,12 @@ def main(argv=None):
             for _ in range(2):
                 ap2()
             ms2 = _median_ms(lambda: [ap2() for _ in range(5)], 3, stream) / 5
-            B2 = (stream_bytes(mc, t2) if m2 else algorithmic_bytes(N, M, name))["total"]
+            B2 = apply_bytes(mc, t2, N, M, name)["total"]
             others[name] = {"ms_per_apply": ms2, "applies_per_s": 1e3 / ms2,
                             "algorithmic_bytes": B2, "GB_per_s": B2 / (ms2 * 1e-3) / 1e9,
                             "frac_of_hbm_peak": B2 / (ms2 * 1e-3) / 1e9 / HBM_PEAK_GBS,
                             "table_bytes": sum(t2.nbytes().values()) if t2 is not None else 0,
-                            "kernel": KERNELS[name].replace("<5", f"<{M}")}
+                            "kernel": kernel_name(name, N, M)}
             del ap2, t2
             torch.cuda.empty_cache()
         out["other_paths"] = others
