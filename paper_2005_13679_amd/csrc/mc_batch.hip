@@ -13,11 +13,10 @@
 #include <stdlib.h>
 #include <string.h>
 
-#include <algorithm>
-#include <numeric>
 #include <vector>
 
 #include "mc_block.h"
+#include "mc_plan.h"
 #include "mc_tiles.h"
 
 namespace mc {
@@ -460,7 +459,6 @@ int mc_batch_create(int32_t count, const mc_batch_item *items, const mc_batch_sc
     const int order = sched ? sched->order : 0;
     if (order < 0 || order > 3) return MC_EINVAL;
 
-    // instance order: by orbital count, then kind, then decreasing dimension
     auto kind_of = [](const mc_tables *t) -> int32_t {
         // above kSmallTiles, what the four-row kernel does not serve runs
         // table-free as in mc_apply_H
@@ -469,14 +467,14 @@ int mc_batch_create(int32_t count, const mc_batch_item *items, const mc_batch_sc
         const bool split = t->form == MC_FORM_REDUCED, map = t->t2_d != nullptr;
         return split ? (map ? kSplitMap : kSplitChain) : (map ? kPaperMap : kPaperChain);
     };
-    std::vector<int32_t> sorted(count);
-    std::iota(sorted.begin(), sorted.end(), 0);
-    std::stable_sort(sorted.begin(), sorted.end(), [&](int a, int b) {
-        const mc_tables *x = items[a].tables, *y = items[b].tables;
-        if (x->M != y->M) return x->M < y->M;
-        if (kind_of(x) != kind_of(y)) return kind_of(x) < kind_of(y);
-        return x->dim > y->dim;
-    });
+    std::vector<PlanItem> plan(count);
+    for (int i = 0; i < count; ++i) {
+        const mc_tables *t = items[i].tables;
+        plan[i] = PlanItem{t->M, kind_of(t), t->dim, t->tiles, batch_block(t)};
+    }
+    std::vector<int32_t> sorted;
+    std::vector<int64_t> prefix;
+    const std::vector<PlanGroup> groups = plan_groups(plan, sorted, prefix);
     mc_batch *b = (mc_batch *)calloc(1, sizeof(mc_batch));
     if (!b) return MC_ENOMEM;
     b->own = (OwnLaunch *)calloc((size_t)count, sizeof(OwnLaunch));
@@ -488,7 +486,6 @@ int mc_batch_create(int32_t count, const mc_batch_item *items, const mc_batch_sc
     b->order = order;
     std::vector<int32_t> pos(count);
     std::vector<BatchInst> inst(count);
-    std::vector<int64_t> prefix(count + 1, 0);
     std::vector<BatchChunk> chunks;
     chunks.reserve(nchunks);
     char *base = (char *)plan_d;
@@ -501,7 +498,7 @@ int mc_batch_create(int32_t count, const mc_batch_item *items, const mc_batch_sc
         BatchInst &I = inst[j];
         I.N = t->N;
         I.M = t->M;
-        I.kind = kind_of(t);
+        I.kind = plan[i].kind;
         I.dim = t->dim;
         I.tiles = t->tiles;
         I.cap = t->t2_d ? t->t2_entries : 0;
@@ -517,7 +514,7 @@ int mc_batch_create(int32_t count, const mc_batch_item *items, const mc_batch_sc
         I.hp = coef + cpos + (int64_t)npairs(t->M) * t->M * t->M;
         I.gp_off = cpos;
         I.hp_off = cpos + (int64_t)npairs(t->M) * t->M * t->M;
-        const bool block = batch_block(t);
+        const bool block = plan[i].own;
         I.btab = block ? (int32_t *)(coef + cpos + batch_const_elems(t->M)) : nullptr;
         cpos += batch_coef_elems(t);
         // an instance of the four-row kernel gets a launch of its own; the
@@ -530,23 +527,15 @@ int mc_batch_create(int32_t count, const mc_batch_item *items, const mc_batch_sc
             o.dim = t->dim;
             o.gp_off = I.gp_off;
             o.btab = I.btab;
-            prefix[j] = 0;
-            continue;
         }
-        // group bookkeeping
-        if (b->ngroups == 0 || b->group_M[b->ngroups - 1] != t->M ||
-            b->group_kind[b->ngroups - 1] != I.kind) {
-            b->group_M[b->ngroups] = t->M;
-            b->group_kind[b->ngroups] = I.kind;
-            b->group_first[b->ngroups] = j;
-            b->group_count[b->ngroups] = 0;
-            b->group_tiles[b->ngroups] = 0;
-            ++b->ngroups;
-        }
-        const int gi = b->ngroups - 1;
-        prefix[j] = b->group_tiles[gi];
-        b->group_tiles[gi] += t->tiles;
-        ++b->group_count[gi];
+    }
+    for (const PlanGroup &g : groups) {
+        const int gi = b->ngroups++;
+        b->group_M[gi] = g.M;
+        b->group_kind[gi] = g.kind;
+        b->group_first[gi] = g.first;
+        b->group_count[gi] = g.count;
+        b->group_tiles[gi] = g.tiles;
     }
     // vector offsets follow the caller's order so that batch vectors are laid
     // out instance by instance as the caller listed them
