@@ -73,6 +73,11 @@ constexpr int kSparseFlush = 8;
 // do not exist, or that have no such jump (smallest index -4).
 constexpr int kRootPad = 8;
 
+// Zeros below the space's tables: what load() reads at prefix sums below 0, on
+// rows without such a jump (smallest -5).  With three orbitals these words are
+// subtracted from the index that stands for "past the vector".
+constexpr int kTablePad = 8;
+
 // Three bits of every orbital from o on: a particle entering o adds one to
 // each S_m, m >= o.
 __device__ __forceinline__ uint32_t from_orbital(int o) { return 0x249249u << 3 * o; }
@@ -146,10 +151,11 @@ __global__ __launch_bounds__(256) void k_sparse_block(
     constexpr int M = MT, R = kBlockRows, IA = M - 2, IB = M - 1, NP = M * (M + 1) / 2;
     extern __shared__ double lds[];   // roots, the space's tables, the occupations
     double *sq = lds + kRootPad;
-    int *lt = (int *)(sq + N + 3 + kBlockRows);
+    int *lt = (int *)(sq + N + 3 + kBlockRows) + kTablePad;
     const int nt = block_table_ints(N, M);
     int *occ = lt + nt + threadIdx.x;
     if (threadIdx.x < kRootPad) lds[threadIdx.x] = 0.0;
+    if (threadIdx.x < kTablePad) lt[(int)threadIdx.x - kTablePad] = 0;
     for (int i = threadIdx.x; i < nt; i += 256) lt[i] = tab[i];
     fill_sqrt_table(sq, N + 3 + kBlockRows);
     const int64_t it = xcd_block(blockIdx.x, nblocks) * 256 + threadIdx.x;
@@ -328,7 +334,8 @@ size_t block_sparse_workspace(int32_t N, int32_t M)
 
 static size_t sparse_lds(int32_t N, int32_t M)
 {
-    return (size_t)(kRootPad + N + 3 + kBlockRows) * 8 + (size_t)(block_table_ints(N, M) + 256 * M) * 4;
+    return (size_t)(kRootPad + N + 3 + kBlockRows) * 8 +
+           (size_t)(kTablePad + block_table_ints(N, M) + 256 * M) * 4;
 }
 
 // Spaces served: from above those of the four-row kernel; from below 131,072
