@@ -399,6 +399,7 @@ def apply_H_adjoint(h, g, C: torch.Tensor, tables, out: torch.Tensor | None = No
 def is_hermitian(h, g, M: int, device) -> bool:
     """True if h = h^dagger and g_ksql = conj(g_lqsk) elementwise (then
     H^dagger = H); one small kernel and a 4-byte read back."""
+    device = torch.device(device)
     h = _as_dev(h, device, (M, M))
     g = _as_dev(g, device, (M, M, M, M))
     flag = torch.empty(1, dtype=torch.int32, device=device)
