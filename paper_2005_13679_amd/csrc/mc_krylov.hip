@@ -32,15 +32,17 @@ __device__ __forceinline__ double block_sum(double v, double *s)
     return (s[0] + s[1]) + (s[2] + s[3]);
 }
 
-// part[(K0 + k) G + b] = sum over part b of conj(V_{K0+k}) w, k < KT.
+// part[k G + b] = sum over part b of conj(V_k) w, for the KT vectors k from
+// first + KT blockIdx.y on.
 template <int KT>
-__global__ __launch_bounds__(256) void k_proj(int64_t n, int64_t len, int K0,
+__global__ __launch_bounds__(256) void k_proj(int64_t n, int64_t len, int first,
                                               const double2 *__restrict__ V, int64_t ldv,
                                               const double2 *__restrict__ w,
                                               double2 *__restrict__ part)
 {
     __shared__ double s[4];
     const int64_t lo = blockIdx.x * len, hi = lo + len < n ? lo + len : n;
+    const int K0 = first + KT * (int)blockIdx.y;
     const double2 *v = V + K0 * ldv;
     double ar[KT], ai[KT];
 #pragma unroll
@@ -171,13 +173,16 @@ __global__ __launch_bounds__(256) void k_scale(int G, int64_t n, int64_t len,
     }
 }
 
+// `sets` sets of kt vectors each from vector `first` on
 template <int KT>
-void proj_launch(int kt, int G, int64_t n, int64_t len, int K0, const double2 *V, int64_t ldv,
-                 const double2 *w, double2 *part, hipStream_t s)
+void proj_launch(int kt, int sets, int G, int64_t n, int64_t len, int first, const double2 *V,
+                 int64_t ldv, const double2 *w, double2 *part, hipStream_t s)
 {
     if (kt == KT)
-        hipLaunchKernelGGL((k_proj<KT>), dim3(G), dim3(256), 0, s, n, len, K0, V, ldv, w, part);
-    else if constexpr (KT > 1) proj_launch<KT - 1>(kt, G, n, len, K0, V, ldv, w, part, s);
+        hipLaunchKernelGGL((k_proj<KT>), dim3(G, sets), dim3(256), 0, s, n, len, first, V, ldv, w,
+                           part);
+    else if constexpr (KT > 1)
+        proj_launch<KT - 1>(kt, sets, G, n, len, first, V, ldv, w, part, s);
 }
 
 template <int K>
@@ -214,23 +219,33 @@ int mc_lanczos_reorth(int32_t K, int64_t n, const double *V_d, int64_t ldv, doub
     double2 *w = (double2 *)w_d, *out = (double2 *)out_d;
     double2 *part = (double2 *)ws_d, *c = part + (size_t)K * MC_REORTH_BLOCKS;
     double *norm = (double *)(c + K);
-    auto project = [&] {
-        for (int k = 0; k < K; k += kKryTile)
-            proj_launch<kKryTile>(K - k < kKryTile ? K - k : kKryTile, G, n, len, k, V, ldv, w,
-                                  part, s);
+    // Projections of many vectors: one launch for every whole set of kKryTile
+    // and one for the rest (with a launch per set a step waited for the host),
+    // on longer parts, since a block sums 16 numbers over its threads at the
+    // end: up to 2,048 elements while there are 1,024 blocks.  100 vectors made
+    // one after another, ms, as four calls per vector / a launch per set / so:
+    // N=20, M=7 24.3 / 31.3 / 24.0; N=30, M=5 10.8 / 12.1 / 8.5; N=60, M=5 47.5 / 54.4
+    // / 44.3.
+    const int sets = K / kKryTile, rest = K % kKryTile;
+    int64_t plen = len;
+    if (K > kKryFused)
+        while (plen < 2048 && (n + 2 * plen - 1) / (2 * plen) * sets >= 1024) plen *= 2;
+    const int PG = (int)((n + plen - 1) / plen);
+    auto project = [&](double2 *alpha) {
+        if (sets) proj_launch<kKryTile>(kKryTile, sets, PG, n, plen, 0, V, ldv, w, part, s);
+        if (rest) proj_launch<kKryTile>(rest, 1, PG, n, plen, K - rest, V, ldv, w, part, s);
+        hipLaunchKernelGGL(k_proj_sum, dim3(K), dim3(256), 0, s, PG, (const double2 *)part, c, alpha);
     };
-    project();
-    hipLaunchKernelGGL(k_proj_sum, dim3(K), dim3(256), 0, s, G, (const double2 *)part, c,
-                       (double2 *)alpha_d);
+    project((double2 *)alpha_d);
     if (K <= kKryFused) {
         sub_proj_launch<kKryFused>(K, G, n, len, V, ldv, c, w, part, s);
+        hipLaunchKernelGGL(k_proj_sum, dim3(K), dim3(256), 0, s, G, (const double2 *)part, c,
+                           (double2 *)nullptr);
     } else {
         hipLaunchKernelGGL(k_sub_norm<false>, dim3(G), dim3(256), 0, s, K, n, len, V, ldv,
                            (const double2 *)c, (const double2 *)w, w, (double *)nullptr);
-        project();
+        project(nullptr);
     }
-    hipLaunchKernelGGL(k_proj_sum, dim3(K), dim3(256), 0, s, G, (const double2 *)part, c,
-                       (double2 *)nullptr);
     hipLaunchKernelGGL(k_sub_norm<true>, dim3(G), dim3(256), 0, s, K, n, len, V, ldv,
                        (const double2 *)c, (const double2 *)w, out, norm);
     hipLaunchKernelGGL(k_scale, dim3(G), dim3(256), 0, s, G, n, len, (const double *)norm, out,
