@@ -43,7 +43,8 @@
 // products, here the same block of columns over four groups of four rows).
 // With X = R + iI a block (bi < bj) takes R'R + I'I and R'I - I'R, four
 // products, a diagonal block three, its imaginary part being R'I less its
-// transpose.  The 4 x 4 form measured 62 TFLOP/s in double on this card and
+// transpose; up to ten columns a block is R and I of two columns and takes one
+// product.  The 4 x 4 form measured 62 TFLOP/s in double on this card and
 // the 16 x 16 form 40, and it pads the columns least (15 of 16 at M = 5, 21 of
 // 24 at M = 6).  Partials per wavefront go to the workspace and are summed over
 // wavefronts by a fixed tree: results are bitwise reproducible.
@@ -61,15 +62,22 @@ namespace mc {
 
 // Column layout of the lift of L particles (L = 1: one column per orbital;
 // L = 2: one per unordered pair, lexicographic).
-constexpr int kGramBlock = 4;   // columns per matrix block
+// Columns per matrix block.  Two: the 4 x 4 products are over R and I of two
+// columns, so a block pair is one product, and up to ten columns that takes
+// fewer products than blocks of four (15 instead of 21 for 16 rows at M = 4, 6
+// instead of 10 at M = 3); above, it takes as many and twice the accumulators.
+// rho2 at N=200, M=4 (us, four columns / two): 55 / 39 without tables, 59 / 44
+// through the maps, 77 / 52 chained.
+__host__ __device__ constexpr int gram_block(int P) { return P <= 10 ? 2 : 4; }
 
 template <int MT, int L>
 struct Lift {
-    static constexpr int P = L == 1 ? MT : MT * (MT + 1) / 2;     // columns
-    static constexpr int PB = (P + kGramBlock - 1) / kGramBlock;  // column blocks
-    static constexpr int PP = kGramBlock * PB;                    // padded columns
-    static constexpr int NB = PB * (PB + 1) / 2;                  // block pairs bi <= bj
-    static constexpr int E = NB * kGramBlock * kGramBlock;        // partial entries per wave
+    static constexpr int P = L == 1 ? MT : MT * (MT + 1) / 2;   // columns
+    static constexpr int BS = gram_block(P);                    // columns per matrix block
+    static constexpr int PB = (P + BS - 1) / BS;                // column blocks
+    static constexpr int PP = BS * PB;                          // padded columns
+    static constexpr int NB = PB * (PB + 1) / 2;                // block pairs bi <= bj
+    static constexpr int E = NB * BS * BS;                      // partial entries per wave
     static constexpr int STRIDE = PP + 1;   // LDS row stride (double2): odd, no bank conflicts
     static constexpr int LDS = 64 * STRIDE * 16;                  // bytes
 };
@@ -383,12 +391,13 @@ __device__ __forceinline__ void gram_commit(std::integer_sequence<int, Cs...>, c
 // The Gram kernel over any source.
 // ---------------------------------------------------------------------------
 
-// Sums of one 4 x 4 block of columns pairs, spread over the lanes as the
+// Sums of one 4 x 4 block of column pairs, spread over the lanes as the
 // matrix instruction leaves them: lane j + 4 g + 16 i holds entry (i, j) over
-// the rows of group g.
+// the rows of group g.  With two columns per block (BS = 2) the 4 x 4 real
+// numbers are R and I of either column, and `im` has no use.
 template <int MT, int L>
 struct GramAcc {
-    double re[Lift<MT, L>::NB], im[Lift<MT, L>::NB];
+    double re[Lift<MT, L>::NB], im[Lift<MT, L>::BS == 2 ? 1 : Lift<MT, L>::NB];
 };
 
 // Block pair (BI, BJ) of 16 rows.
@@ -400,10 +409,12 @@ __device__ __forceinline__ void gram_pair(const double (&r)[Lift<MT, L>::PB],
     if constexpr (BI <= BJ) {
         constexpr int PB = Lift<MT, L>::PB, k = BI * PB - BI * (BI - 1) / 2 + (BJ - BI);
         A.re[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(r[BI], r[BJ], A.re[k], 0, 0, 0);
-        A.re[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(x[BI], x[BJ], A.re[k], 0, 0, 0);
-        A.im[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(r[BI], x[BJ], A.im[k], 0, 0, 0);
-        if constexpr (BI < BJ)
-            A.im[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(-x[BI], r[BJ], A.im[k], 0, 0, 0);
+        if constexpr (Lift<MT, L>::BS == 4) {
+            A.re[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(x[BI], x[BJ], A.re[k], 0, 0, 0);
+            A.im[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(r[BI], x[BJ], A.im[k], 0, 0, 0);
+            if constexpr (BI < BJ)
+                A.im[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(-x[BI], r[BJ], A.im[k], 0, 0, 0);
+        }
     }
 }
 
@@ -413,14 +424,18 @@ __device__ __forceinline__ void gram_rows(std::integer_sequence<int, Ks...>, con
 {
     constexpr int PB = Lift<MT, L>::PB, STRIDE = Lift<MT, L>::STRIDE;
     // operand lane: column lane % 4 of its block, row 4 (lane / 4 % 4) + lane / 16
-    const double2 *x0 = X + (4 * ((lane >> 2) & 3) + (lane >> 4)) * STRIDE + (lane & 3);
+    const double2 *row = X + (4 * ((lane >> 2) & 3) + (lane >> 4)) * STRIDE;
     for (int r0 = 0; r0 < 64; r0 += 16) {
         double r[PB], x[PB];
 #pragma unroll
         for (int c = 0; c < PB; ++c) {
-            const double2 v = x0[r0 * STRIDE + 4 * c];
-            r[c] = v.x;
-            x[c] = v.y;
+            if constexpr (Lift<MT, L>::BS == 2) {
+                r[c] = ((const double *)(row + r0 * STRIDE + 2 * c))[lane & 3];
+            } else {
+                const double2 v = row[r0 * STRIDE + 4 * c + (lane & 3)];
+                r[c] = v.x;
+                x[c] = v.y;
+            }
         }
         (gram_pair<MT, L, Ks / PB, Ks % PB>(r, x, A), ...);
     }
@@ -443,7 +458,10 @@ __global__ __launch_bounds__(64) void k_gram(Src src, int64_t DN, int64_t chunks
     __syncthreads();
     GramAcc<MT, L> A;
 #pragma unroll
-    for (int k = 0; k < LF::NB; ++k) A.re[k] = A.im[k] = 0.0;
+    for (int k = 0; k < LF::NB; ++k) {
+        A.re[k] = 0.0;
+        if constexpr (LF::BS == 4) A.im[k] = 0.0;
+    }
     const Gather<BIGC> ldc(C, DN);
     constexpr bool PRE = LF::P <= MC_GRAM_PREFETCH_MAX_P;
     typename Src::Tgt tg;
@@ -482,14 +500,23 @@ __global__ __launch_bounds__(64) void k_gram(Src src, int64_t DN, int64_t chunks
     // sum the four row groups; lanes 16 i + j then hold entry (i, j)
 #pragma unroll
     for (int k = 0; k < LF::NB; ++k) {
-        double re = A.re[k], im = A.im[k];
+        double re = A.re[k];
         re += __shfl_xor(re, 4, 64);
         re += __shfl_xor(re, 8, 64);
-        im += __shfl_xor(im, 4, 64);
-        im += __shfl_xor(im, 8, 64);
-        if (((lane >> 2) & 3) == 0) {
-            const int e = 16 * k + 4 * (lane >> 4) + (lane & 3);
-            part[(int64_t)e * nwaves + wave] = make_double2(re, im);
+        const int i = lane >> 4, j = lane & 3;
+        if constexpr (LF::BS == 2) {
+            // R R + I I on even lanes j of even i, R I - I R on odd ones
+            const double o = __shfl_xor(re, 17, 64);
+            if (((lane >> 2) & 3) == 0 && (i & 1) == 0) {
+                const int e = 4 * k + i + (j >> 1);
+                ((double *)(part + (int64_t)e * nwaves + wave))[j & 1] = j & 1 ? re - o : re + o;
+            }
+        } else {
+            double im = A.im[k];
+            im += __shfl_xor(im, 4, 64);
+            im += __shfl_xor(im, 8, 64);
+            if (((lane >> 2) & 3) == 0)
+                part[(int64_t)(16 * k + 4 * i + j) * nwaves + wave] = make_double2(re, im);
         }
     }
 }
@@ -532,7 +559,7 @@ __device__ __forceinline__ int upair(int M, int x, int y)
 // Gram entry (k, l); rho2[k][s][q][l] is entry ({k,s}, {q,l}).  Entries
 // below the diagonal are conjugates, diagonal entries are real.  canon =
 // NULL writes zeros (fewer than L particles).
-__global__ __launch_bounds__(256) void k_gram_expand(int M, int L, int PB,
+__global__ __launch_bounds__(256) void k_gram_expand(int M, int L, int PB, int BS,
                                                      const double2 *__restrict__ canon,
                                                      double2 *__restrict__ out)
 {
@@ -554,12 +581,12 @@ __global__ __launch_bounds__(256) void k_gram_expand(int M, int L, int PB,
     }
     const bool swap = c1 > c2;
     const int x = swap ? c2 : c1, y = swap ? c1 : c2;
-    constexpr int BS = kGramBlock;
     const int bi = x / BS, bj = y / BS;
     const double2 *blk = canon + (bi * PB - bi * (bi - 1) / 2 + (bj - bi)) * BS * BS;
     double2 v = blk[(x % BS) * BS + (y % BS)];
-    // a diagonal block holds R'I: the imaginary part is that less its transpose
-    if (bi == bj) v.y -= blk[(y % BS) * BS + (x % BS)].y;
+    // a diagonal block of four columns holds R'I: the imaginary part is that
+    // less its transpose
+    if (BS == 4 && bi == bj) v.y -= blk[(y % BS) * BS + (x % BS)].y;
     if (swap) v.y = -v.y;
     if (x == y) v.y = 0.0;
     out[idx] = v;
@@ -572,7 +599,7 @@ inline int gram_roots(int N, int M) { return M >= MC_LDS_ROOTS_FROM ? N + 3 : 0;
 // wavefronts of 256 CUs, at most 12 per CU, fixed per (N, M) so results are
 // reproducible on any device), partial entries, workspace bytes.
 struct GramShape {
-    int64_t chunks = 0, nwaves = 0, E = 0, PB = 0;
+    int64_t chunks = 0, nwaves = 0, E = 0, PB = 0, BS = 0;
     int nroots = 0;
     size_t lds = 0, ws = 0;
 };
@@ -587,8 +614,13 @@ void gram_shape_t(int N, int64_t chunks, GramShape *g)
     const int64_t w = 256 * per_cu;
     g->chunks = chunks;
     g->nwaves = chunks < w ? (chunks > 0 ? chunks : 1) : w;
+    // two chunks each at most: as many wavefronts as make them even.  Few columns
+    // only, N=110, M=4 (3,466 chunks) 19.0 -> 17.0 us; with more, where fewer
+    // wavefronts fit a CU, it cost 10 % (N=18, M=7 chained).
+    if (Lift<MT, L>::BS == 2 && chunks > w && chunks <= 2 * w) g->nwaves = (chunks + 1) / 2;
     g->E = Lift<MT, L>::E;
     g->PB = Lift<MT, L>::PB;
+    g->BS = Lift<MT, L>::BS;
     g->ws = (size_t)(g->E * g->nwaves + g->E) * 16;
 }
 
@@ -606,7 +638,7 @@ inline int gram_shape(int N, int M, int L, int64_t chunks, GramShape *g)
 inline int gram_zero(int M, int L, double *out_d, hipStream_t s)
 {
     const int total = L == 1 ? M * M : M * M * M * M;
-    hipLaunchKernelGGL(k_gram_expand, dim3((total + 255) / 256), dim3(256), 0, s, M, L, 1,
+    hipLaunchKernelGGL(k_gram_expand, dim3((total + 255) / 256), dim3(256), 0, s, M, L, 1, 1,
                        (const double2 *)nullptr, (double2 *)out_d);
     return launch_status();
 }
@@ -624,7 +656,7 @@ int gram_launch(const Src &src, int64_t DN, const GramShape &gs, const double *C
     hipLaunchKernelGGL(k_gram_sum, dim3((unsigned)gs.E), dim3(256), 0, s, (int)gs.nwaves, part,
                        canon);
     hipLaunchKernelGGL(k_gram_expand, dim3((total + 255) / 256), dim3(256), 0, s, MT, L,
-                       (int)gs.PB, (const double2 *)canon, (double2 *)out_d);
+                       (int)gs.PB, (int)gs.BS, (const double2 *)canon, (double2 *)out_d);
     return launch_status();
 }
 
