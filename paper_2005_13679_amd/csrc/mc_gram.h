@@ -246,17 +246,22 @@ struct MapTargets {
     int32_t d[ND];                          // (0, 0) -> (q, l), 1 <= q <= l (map kinds)
     const int32_t *__restrict__ t1;         // whole single-jump map (chained kind)
 
+    // T1[u][0][l]: tile u / 64, lane u % 64.  The load is made on every lane (of
+    // row 0 where there is no such jump): behind a branch each load was waited
+    // for before the next was issued (rho2 at N=100, M=5 chained 263 us, 164 so;
+    // N=35, M=6 92.7 and 64.9; N=26, M=8 1,125 and 647).
     __device__ __forceinline__ int32_t chain(int32_t u, int l) const
     {
-        // T1[u][0][l]: tile u / 64, lane u % 64 (u >= 0 on live rows)
-        const int64_t uu = u < 0 ? 0 : u;
+        const bool ok = live && u >= 0;
+        const int64_t uu = ok ? u : 0;
         const int32_t v = t1[((uu >> 6) * (MT * MT) + l) * kTile + (uu & 63)];
-        return u < 0 ? -1 : v;
+        return ok ? v : -1;
     }
 
     template <int q, int l>
     __device__ __forceinline__ int32_t target() const
     {
+        if constexpr (KIND == 0 && l > 0 && q > 0) return chain(s0[q], l);
         if (!live) return -1;
         if constexpr (l < 0) {
             return s0[q];   // one particle: m + e_q = T1[gamma][0][q]
@@ -264,10 +269,8 @@ struct MapTargets {
             return g;
         } else if constexpr (q == 0) {
             return s0[l];
-        } else if constexpr (KIND != 0) {
-            return d[reduced_rank(MT, 0, 0, q, l)];
         } else {
-            return chain(s0[q], l);
+            return d[reduced_rank(MT, 0, 0, q, l)];
         }
     }
 };
