@@ -444,8 +444,13 @@ __device__ __forceinline__ void gram_rows(std::integer_sequence<int, Ks...>, con
     }
 }
 
+// Seven orbitals are held to the registers of two wavefronts per SIMD: left to
+// itself the compiler took 284 for the 28 columns without tables, one wavefront
+// per SIMD where the launch counts on five per CU (N=18 31.1 us, 24.1 so; N=35
+// 499 and 399).  Eight orbitals would spill (N=15 36.5 and 44.0).
 template <int MT, int L, bool BIGC, class Src>
-__global__ __launch_bounds__(64) void k_gram(Src src, int64_t DN, int64_t chunks, int nwaves,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MT == 7 ? 2 : 1)))
+void k_gram(Src src, int64_t DN, int64_t chunks, int nwaves,
                                              int nroots, const double2 *__restrict__ C,
                                              double2 *__restrict__ part)
 {
