@@ -25,7 +25,7 @@ LIB = os.path.join(HERE, "libmc.so")
 TILE_FLAGS = ("-ffp-contract=on",)
 SOURCES = [("mc_tiles.hip", f"mc_tiles_{m}_{p}",
             (f"-DMC_TILES_M={m}", f"-DMC_TILES_PART={p}", *TILE_FLAGS))
-           for m in range(8, 0, -1) for p in (2, 0, 1)]
+           for m in range(8, 0, -1) for p in (3, 2, 0, 1) if p < 3 or m >= 5]
 SOURCES += [("mc_joint.hip", f"mc_joint_{k}", (f"-DMC_JOINT_KIND={k}", *TILE_FLAGS)) for k in range(5)]
 SOURCES += [(f"{n}.hip", n, ()) for n in
             ("mc_ops", "mc_block", "mc_block_sparse", "mc_host", "mc_tables", "mc_direct", "mc_batch", "mc_krylov",

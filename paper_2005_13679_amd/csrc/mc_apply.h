@@ -145,13 +145,22 @@ __device__ __forceinline__ bool opaque_true()
 // one wavefront per tile, 21 with eight; N=8, M=7 59 and 15; N=10, M=5 18.6 and
 // 14.7 (15 us is the caller's own time); through the paper's map 161 and 25, 97
 // and 20, 28 and 15.
+// A group of a batch with many tiles has the wavefronts without that, and a tile
+// would be decoded eight times; but its sums have to have the same bits, so one
+// wavefront keeps the kTileParts sums itself.
 constexpr int kTileParts = 8;
 template <int MT>
 constexpr int kSmallParts = MT >= 5 ? kTileParts : 1;   // M <= 4: at most 55 slots
 
-template <int NP>
+// A wavefront's part of a tile: one of NP, or all with NC sums kept apart, in LDS
+// (in registers they spilled through the maps from M = 6 on) or in registers.
+template <int NP, int NC = 1, bool LDS = true>
 struct Part {
-    int part;   // wave-uniform, 0 .. NP-1
+    static constexpr int kWaves = NP, kSums = NC;
+    static constexpr bool kSplit = NP * NC > 1;   // units are summed apart
+    static constexpr bool kLds = NC > 1 && LDS;
+    int part;        // wave-uniform, 0 .. NP-1
+    double2 *sums;   // kLds: the lane's first sum, the others every kTile
     template <int I>
     __device__ __forceinline__ bool has() const
     {
@@ -160,6 +169,43 @@ struct Part {
     }
     // the row's own term
     __device__ __forceinline__ bool own() const { return NP == 1 || part == NP - 1; }
+};
+
+// The sums that a wavefront keeps of a row; unit I goes into number I mod NC, the
+// row's own term into the last.
+template <class PT>
+struct RowSum {
+    static constexpr int NC = PT::kSums;
+    double2 v[PT::kLds ? 1 : NC];
+    double2 *s;
+    // own: the row's own term (zero where another wavefront has it)
+    __device__ __forceinline__ RowSum(const PT &part, double2 own)
+    {
+        s = part.sums;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) put(c, c + 1 < NC ? make_double2(0.0, 0.0) : own);
+    }
+    __device__ __forceinline__ double2 get(int unit) const
+    {
+        if constexpr (PT::kLds) return s[unit % NC * kTile];
+        else return v[unit % NC];
+    }
+    __device__ __forceinline__ void put(int unit, double2 u)
+    {
+        if constexpr (PT::kLds) s[unit % NC * kTile] = u;
+        else v[unit % NC] = u;
+    }
+    __device__ __forceinline__ double2 total() const
+    {
+        double2 t = get(0);
+#pragma unroll
+        for (int c = 1; c < NC; ++c) {
+            const double2 u = get(c);
+            t.x += u.x;
+            t.y += u.y;
+        }
+        return t;
+    }
 };
 
 // Adds the parts of a tile (`red` holds NP * 64 double2) and stores its rows.
@@ -349,21 +395,24 @@ __device__ __forceinline__ void pair_term(const int32_t *t2, int64_t pos, int64_
 // (uniform branch on the tile's pair mask), which keeps the scheduler from
 // hoisting later pairs' loads.  `tf` carries the prefetched first index
 // batch of the next block from pair to pair.
-template <int MT, bool BIGC, int NP, int... Ps>
-__device__ __forceinline__ void all_pairs(std::integer_sequence<int, Ps...>, Part<NP> part,
+template <int MT, bool BIGC, class PT, int... Ps>
+__device__ __forceinline__ void all_pairs(std::integer_sequence<int, Ps...>, PT part,
                                           const uint64_t *pm, const int32_t *t2, int64_t off0,
                                           int64_t off1, int lane, const int (&n)[MT],
                                           const RowSq<MT> &R, const double2 *__restrict__ gp,
                                           const Gather<BIGC> &ldc, int32_t (&tf)[kT2Batch<MT>],
-                                          double &ar, double &ai)
+                                          RowSum<PT> &A)
 {
     int64_t pos = off0;
     (
         [&] {
             constexpr int NSB = MT * MT * kTile;
             if (((pm[Ps >> 6] >> (Ps & 63)) & 1) && pos + NSB <= off1) {
-                if (NP == 1 || part.template has<Ps>())
-                    pair_term<MT, BIGC, Ps>(t2, pos, off1, lane, n, R, gp, ldc, tf, ar, ai);
+                if (PT::kWaves == 1 || part.template has<Ps>()) {
+                    double2 u = A.get(Ps);
+                    pair_term<MT, BIGC, Ps>(t2, pos, off1, lane, n, R, gp, ldc, tf, u.x, u.y);
+                    A.put(Ps, u);
+                }
                 pos += NSB;
             }
         }(),
@@ -373,8 +422,8 @@ __device__ __forceinline__ void all_pairs(std::integer_sequence<int, Ps...>, Par
 // One 64-row tile of H.C for a compile-time orbital count MT (1..8) through
 // the single- and double-jump maps; every orbital, pair and slot index is a
 // compile-time constant.  Called by one whole wavefront.
-template <int MT, typename OccT, bool BIGC, int NP>
-__device__ __forceinline__ double2 apply_tile_t2(Part<NP> part, int64_t tile, int64_t D, int64_t cap, const double *sq,
+template <int MT, typename OccT, bool BIGC, class PT>
+__device__ __forceinline__ double2 apply_tile_t2(PT part, int64_t tile, int64_t D, int64_t cap, const double *sq,
                                               const OccT *__restrict__ occ,
                                               const int32_t *__restrict__ t1,
                                               const uint64_t *__restrict__ pmask,
@@ -406,7 +455,7 @@ __device__ __forceinline__ double2 apply_tile_t2(Part<NP> part, int64_t tile, in
 
     // diagonal one-body part: sum_k h_kk n_k C_g
     const double2 cg = ldc(live ? (int32_t)g : -1);
-    double ar = 0.0, ai = 0.0;
+    double2 own = make_double2(0.0, 0.0);
     if (part.own()) {
         double dr = 0.0, di = 0.0;
 #pragma unroll
@@ -415,9 +464,10 @@ __device__ __forceinline__ double2 apply_tile_t2(Part<NP> part, int64_t tile, in
             dr = fma(hk.x, (double)n[k], dr);
             di = fma(hk.y, (double)n[k], di);
         }
-        ar = dr * cg.x - di * cg.y;
-        ai = dr * cg.y + di * cg.x;
+        own.x = dr * cg.x - di * cg.y;
+        own.y = dr * cg.y + di * cg.x;
     }
+    RowSum<PT> A(part, own);
 
     // single jumps k -> l (k != l): h_kl sqrt(n_k (n_l + 1)) C[T1], in
     // batches of kSlotBatch slots (table loads, then gathers, then FMAs)
@@ -427,7 +477,9 @@ __device__ __forceinline__ double2 apply_tile_t2(Part<NP> part, int64_t tile, in
             make_rsrc(t1 + tile * NS * kTile, (uint32_t)(NS * kTile * 4));
 #pragma unroll
         for (int j0 = 0; j0 < NS; j0 += SB) {
-            if (NP > 1 && part.part != j0 / SB % NP) continue;
+            if (PT::kWaves > 1 && part.part != j0 / SB % PT::kWaves) continue;
+            double2 u = A.get(j0 / SB);
+            double &ar = u.x, &ai = u.y;
             int32_t t[SB];
             double2 c[SB];
 #pragma unroll
@@ -455,13 +507,14 @@ __device__ __forceinline__ double2 apply_tile_t2(Part<NP> part, int64_t tile, in
                 ai = fma(hv.x, ci, ai);
                 ai = fma(hv.y, cr, ai);
             }
+            A.put(j0 / SB, u);
         }
     }
 
     // double jumps: one block of M*M*64 entries per pair present in the tile
     all_pairs<MT, BIGC>(std::make_integer_sequence<int, P>{}, part, pmask + tile * W, t2, off0, off1,
-                        lane, n, R, gp, ldc, tf, ar, ai);
-    return make_double2(ar, ai);
+                        lane, n, R, gp, ldc, tf, A);
+    return A.total();
 }
 
 
@@ -550,13 +603,13 @@ __device__ __forceinline__ void pair_term_chained(int64_t D, const int32_t *__re
 // values live at once there.  K and S are wave-uniform loop counters; q and
 // l stay compile-time, so the per-row occupations are picked with selects and
 // the roots come from the block's sqrt table.
-template <int MT, bool BIGC, int NP>
-__device__ __forceinline__ void pairs_chained_loop(Part<NP> part, int64_t D, int64_t g,
+template <int MT, bool BIGC, class PT>
+__device__ __forceinline__ void pairs_chained_loop(PT part, int64_t D, int64_t g,
                                                    const int32_t *__restrict__ t1,
                                                    __amdgpu_buffer_rsrc_t r1, int lane,
                                                    const int (&n)[MT], const double *sq,
                                                    const double2 *__restrict__ gp,
-                                                   const Gather<BIGC> &ldc, double &ar, double &ai)
+                                                   const Gather<BIGC> &ldc, RowSum<PT> &sum)
 {
     constexpr int NS = MT * MT, SB = kSlotBatch<MT>;
     int P = 0;
@@ -564,7 +617,7 @@ __device__ __forceinline__ void pairs_chained_loop(Part<NP> part, int64_t D, int
     for (int K = 0; K < MT; ++K) {
 #pragma unroll 1
         for (int S = K; S < MT; ++S, ++P) {
-            if (NP > 1 && part.part != P % NP) continue;
+            if (PT::kWaves > 1 && part.part != P % PT::kWaves) continue;
             int nK = 0, nS = 0;
 #pragma unroll
             for (int m = 0; m < MT; ++m) {
@@ -627,31 +680,36 @@ __device__ __forceinline__ void pairs_chained_loop(Part<NP> part, int64_t D, int
                     bi = fma(Gv.y, cr, bi);
                 }
             }
-            ar = fma(A, br, ar);
-            ai = fma(A, bi, ai);
+            double2 u = sum.get(P);
+            u.x = fma(A, br, u.x);
+            u.y = fma(A, bi, u.y);
+            sum.put(P, u);
         }
     }
 }
 
-template <int MT, bool BIGC, int NP, int... Ps>
-__device__ __forceinline__ void all_pairs_chained(std::integer_sequence<int, Ps...>, Part<NP> part, int64_t D,
+template <int MT, bool BIGC, class PT, int... Ps>
+__device__ __forceinline__ void all_pairs_chained(std::integer_sequence<int, Ps...>, PT part, int64_t D,
                                                   const int32_t *__restrict__ t1,
                                                   __amdgpu_buffer_rsrc_t r1, int lane,
                                                   const int (&n)[MT], const RowSq<MT, kLdsRootsChained<MT>> &R,
                                                   const double2 *__restrict__ gp,
-                                                  const Gather<BIGC> &ldc, double &ar, double &ai)
+                                                  const Gather<BIGC> &ldc, RowSum<PT> &A)
 {
     (
         [&] {
-            if (NP == 1 || part.template has<Ps>())
-                pair_term_chained<MT, BIGC, Ps>(D, t1, r1, lane, n, R, gp, ldc, ar, ai);
+            if (PT::kWaves == 1 || part.template has<Ps>()) {
+                double2 u = A.get(Ps);
+                pair_term_chained<MT, BIGC, Ps>(D, t1, r1, lane, n, R, gp, ldc, u.x, u.y);
+                A.put(Ps, u);
+            }
         }(),
         ...);
 }
 
 // One 64-row tile of H.C through single jumps only (see above).
-template <int MT, typename OccT, bool BIGC, int NP>
-__device__ __forceinline__ double2 apply_tile_chained(Part<NP> part, int64_t tile, int64_t D, const double *sq,
+template <int MT, typename OccT, bool BIGC, class PT>
+__device__ __forceinline__ double2 apply_tile_chained(PT part, int64_t tile, int64_t D, const double *sq,
                                                    const OccT *__restrict__ occ,
                                                    const int32_t *__restrict__ t1,
                                                    const double2 *__restrict__ h,
@@ -671,7 +729,7 @@ __device__ __forceinline__ double2 apply_tile_chained(Part<NP> part, int64_t til
     const __amdgpu_buffer_rsrc_t r1 =
         make_rsrc(t1 + tile * NS * kTile, (uint32_t)(NS * kTile * 4));
     const double2 cg = ldc(live ? (int32_t)g : -1);
-    double ar = 0.0, ai = 0.0;
+    double2 own = make_double2(0.0, 0.0);
     if (part.own()) {
         double dr = 0.0, di = 0.0;
 #pragma unroll
@@ -680,13 +738,16 @@ __device__ __forceinline__ double2 apply_tile_chained(Part<NP> part, int64_t til
             dr = fma(hk.x, (double)n[k], dr);
             di = fma(hk.y, (double)n[k], di);
         }
-        ar = dr * cg.x - di * cg.y;
-        ai = dr * cg.y + di * cg.x;
+        own.x = dr * cg.x - di * cg.y;
+        own.y = dr * cg.y + di * cg.x;
     }
+    RowSum<PT> A(part, own);
     // single jumps k -> l (k != l), in batches
 #pragma unroll
     for (int j0 = 0; j0 < NS; j0 += SB) {
-        if (NP > 1 && part.part != j0 / SB % NP) continue;
+        if (PT::kWaves > 1 && part.part != j0 / SB % PT::kWaves) continue;
+        double2 u = A.get(j0 / SB);
+        double &ar = u.x, &ai = u.y;
         int32_t t[SB];
         double2 c[SB];
 #pragma unroll
@@ -713,13 +774,14 @@ __device__ __forceinline__ double2 apply_tile_chained(Part<NP> part, int64_t til
             ai = fma(hv.x, ci, ai);
             ai = fma(hv.y, cr, ai);
         }
+        A.put(j0 / SB, u);
     }
     if constexpr (kLdsRootsChained<MT>)
-        pairs_chained_loop<MT, BIGC>(part, D, g, t1, r1, lane, n, sq, gp, ldc, ar, ai);
+        pairs_chained_loop<MT, BIGC>(part, D, g, t1, r1, lane, n, sq, gp, ldc, A);
     else
         all_pairs_chained<MT, BIGC>(std::make_integer_sequence<int, P>{}, part, D, t1, r1, lane, n, R,
-                                    gp, ldc, ar, ai);
-    return make_double2(ar, ai);
+                                    gp, ldc, A);
+    return A.total();
 }
 
 }  // namespace mc

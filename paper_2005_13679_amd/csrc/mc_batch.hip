@@ -91,6 +91,7 @@ struct mc_batch {
     int32_t group_count[48];
     int64_t group_tiles[48];
     int64_t group_blocks[48];
+    bool group_shared[48];    // its tiles are shared by blocks (shared_tiles)
     bool group_joined[48];    // runs with others of its kind in one launch
     mc::JointGroups joint[mc::kJointKinds];   // those groups, by kind
     int64_t joint_blocks[mc::kJointKinds];
@@ -132,7 +133,7 @@ static void batch_join(mc_batch *b, int cus)
             const int M = b->group_M[gi];
             if (b->group_kind[gi] != kind || M < kJointMinM || M > kJointMaxM || b->order != 3)
                 continue;
-            const bool parts = small_parts(M, kind);
+            const bool parts = b->group_shared[gi];
             const int64_t tiles = b->group_tiles[gi];
             const int64_t need = parts ? tiles : (tiles + kTileParts - 1) / kTileParts;
             if (need > (int64_t)(kind == kSplitChain ? 16 : 64) * cus) continue;
@@ -571,7 +572,9 @@ int mc_batch_create(int32_t count, const mc_batch_item *items, const mc_batch_sc
         if (hipGetDeviceProperties(&prop, dev) == hipSuccess) cus = prop.multiProcessorCount;
     }
     for (int gi = 0; gi < b->ngroups; ++gi) {
-        const bool parts = small_parts(b->group_M[gi], b->group_kind[gi]);
+        const bool parts = small_parts(b->group_M[gi], b->group_kind[gi]) &&
+                           b->group_tiles[gi] <= shared_tiles(b->group_M[gi], b->group_kind[gi], order);
+        b->group_shared[gi] = parts;
         const int64_t need = parts ? b->group_tiles[gi] : (b->group_tiles[gi] + 3) / 4;
         const int64_t cap_blocks = (int64_t)bpc * cus;
         b->group_blocks[gi] = need < cap_blocks ? need : cap_blocks;
@@ -644,12 +647,17 @@ static int batch_apply_staged(const mc_batch *b, const double *C_d, double *HC_d
         if (b->group_joined[gi]) continue;
         const int M = b->group_M[gi];
         const int64_t blocks = b->group_blocks[gi];
-        const int64_t workers = small_parts(M, b->group_kind[gi]) ? blocks : blocks * 4;
+        const int64_t workers = b->group_shared[gi] ? blocks : blocks * 4;
         const GroupCall c{b->group_kind[gi], b->group_first[gi], b->group_count[gi], b->order,
                           batch_grab(b->group_tiles[gi], workers), b->group_tiles[gi], blocks,
                           b->inst_d, b->tile_prefix_d, b->counters_d + gi, b->coef_d,
                           (const double2 *)C_d, (double2 *)HC_d, s};
-        const int st = MC_TILES_CALL(group, M, c);
+        int st;
+        if (b->group_shared[gi] || !small_parts(M, c.kind))
+            st = MC_TILES_CALL(group, M, c);
+        else
+            st = M == 5 ? tiles_many_5(c) : M == 6 ? tiles_many_6(c) : M == 7 ? tiles_many_7(c)
+                                                                        : tiles_many_8(c);
         if (st) return st;
     }
     return launch_status();

@@ -224,7 +224,7 @@ __device__ __forceinline__ void direct_fmas(std::integer_sequence<int, Is...>,
 }
 
 // A_KS of the pair that batch B ends inside of times the pair's sum so far:
-// with a wavefront per part of the batches, a pair does not go on in the next.
+// where batches are summed apart, a pair does not go on in the next.
 template <int MT, int LAST>
 __device__ __forceinline__ void direct_flush(const int (&n)[MT], const RowSq<MT> &R, double &br,
                                              double &bi, double &ar, double &ai)
@@ -248,34 +248,36 @@ __device__ __forceinline__ void direct_flush(const int (&n)[MT], const RowSq<MT>
 
 // Batch B of the stream in a basic block of its own (see opaque_true):
 // its targets, its gathers, its arithmetic.
-template <int MT, bool BIGC, int B, int NP>
-__device__ __forceinline__ void direct_batches(Part<NP> part, const DirectRow<MT> &row,
+template <int MT, bool BIGC, int B, class PT>
+__device__ __forceinline__ void direct_batches(PT part, const DirectRow<MT> &row,
                                                const int (&n)[MT], const RowSq<MT> &R,
                                                const double (&x)[MT],
                                                const double2 *__restrict__ HS,
                                                const double2 *__restrict__ GS,
                                                const double2 *__restrict__ GD,
                                                const Gather<BIGC> &ldc, double &br, double &bi,
-                                               double &ar, double &ai)
+                                               RowSum<PT> &A)
 {
     constexpr int SB = DirectStream<MT>::SB, NB = DirectStream<MT>::NB, U = DirectStream<MT>::U;
     if constexpr (B < NB) {
         if (part.template has<B>()) {
             double2 c[SB];
             direct_gathers<MT, BIGC, B * SB>(std::make_integer_sequence<int, SB>{}, c, row, n, ldc);
+            double2 u = A.get(B);
             direct_fmas<MT, B * SB>(std::make_integer_sequence<int, SB>{}, c, n, R, x, HS, GS, GD,
-                                    br, bi, ar, ai);
-            if constexpr (NP > 1)
-                direct_flush<MT, ((B + 1) * SB < U ? (B + 1) * SB : U) - 1>(n, R, br, bi, ar, ai);
+                                    br, bi, u.x, u.y);
+            if constexpr (PT::kSplit)
+                direct_flush<MT, ((B + 1) * SB < U ? (B + 1) * SB : U) - 1>(n, R, br, bi, u.x, u.y);
+            A.put(B, u);
         }
-        direct_batches<MT, BIGC, B + 1>(part, row, n, R, x, HS, GS, GD, ldc, br, bi, ar, ai);
+        direct_batches<MT, BIGC, B + 1>(part, row, n, R, x, HS, GS, GD, ldc, br, bi, A);
     }
 }
 
 // One 64-row tile of H.C with no table (M <= 8, D < 2^31); `cf` holds the
 // constants staged by k_prep_split.
-template <int MT, bool BIGC, int NP>
-__device__ __forceinline__ double2 apply_tile_direct(Part<NP> part, int64_t tile, int N, int64_t D,
+template <int MT, bool BIGC, class PT>
+__device__ __forceinline__ double2 apply_tile_direct(PT part, int64_t tile, int N, int64_t D,
                                                      const double *sq,
                                                      const double2 *__restrict__ cf,
                                                      const double2 *__restrict__ C)
@@ -302,7 +304,7 @@ __device__ __forceinline__ double2 apply_tile_direct(Part<NP> part, int64_t tile
 
     // the row's own coefficient (one-body diagonal and coincident pairs)
     const double2 cg = ldc(live ? (int32_t)g : -1);
-    double ar = 0.0, ai = 0.0;
+    double2 own = make_double2(0.0, 0.0);
     if (part.own()) {
         double dr = 0.0, di = 0.0;
 #pragma unroll
@@ -316,13 +318,14 @@ __device__ __forceinline__ double2 apply_tile_direct(Part<NP> part, int64_t tile
             dr = fma(GI[p].x, w, dr);
             di = fma(GI[p].y, w, di);
         }
-        ar = dr * cg.x - di * cg.y;
-        ai = dr * cg.y + di * cg.x;
+        own.x = dr * cg.x - di * cg.y;
+        own.y = dr * cg.y + di * cg.x;
     }
+    RowSum<PT> A(part, own);
     // single jumps, then the true double jumps pair by pair
     double br = 0.0, bi = 0.0;
-    direct_batches<MT, BIGC, 0>(part, row, n, R, x, HS, GS, GD, ldc, br, bi, ar, ai);
-    return make_double2(ar, ai);
+    direct_batches<MT, BIGC, 0>(part, row, n, R, x, HS, GS, GD, ldc, br, bi, A);
+    return A.total();
 }
 
 }  // namespace mc

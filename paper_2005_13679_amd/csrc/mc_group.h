@@ -14,8 +14,8 @@ constexpr int kBatchMaxN = 255;
 // Work item i of a group: a tile of its instance.  j: position in the group,
 // which only rises (prefix is non-decreasing and a worker visits items in
 // increasing order, so the search resumes where it stopped).
-template <int MT, int KIND, int NP>
-__device__ __forceinline__ void batch_item(const Part<NP> &part, int64_t i, int &j,
+template <int MT, int KIND, class PT>
+__device__ __forceinline__ void batch_item(const PT &part, int64_t i, int &j,
                                            const BatchInst *__restrict__ inst,
                                            const int64_t *__restrict__ prefix, int first, int count,
                                            const double *sq, double2 *red,
@@ -35,7 +35,7 @@ __device__ __forceinline__ void batch_item(const Part<NP> &part, int64_t i, int 
                                                  I.t2_off, I.t2,
                                                  KIND == kPaperMap || KIND == kPaperChain ? hp : gp,
                                                  gp, C);
-    store_tile<NP>(v, part.part, tile, I.dim, red, HCb + I.vec_off);
+    store_tile<PT::kWaves>(v, part.part, tile, I.dim, red, HCb + I.vec_off);
 }
 
 // Calls item(i, j) for `grab` items at a time from the group's counter (a vector

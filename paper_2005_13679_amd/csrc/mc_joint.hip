@@ -28,10 +28,10 @@ void k_batch_joint(const BatchInst *__restrict__ inst, const int64_t *__restrict
     auto run = [&](auto m) __attribute__((always_inline)) {
         constexpr int MT = decltype(m)::value, NP = kSmallParts<MT>;
         if constexpr (kLdsRoots<MT>) fill_sqrt_table(sq, kBatchMaxN + 3);
-        const Part<NP> part{NP == 1 ? 0 : wave_in_block()};
+        const Part<NP> part{NP == 1 ? 0 : wave_in_block(), nullptr};
         batch_take<NP>(counters + G.counter, G.items, G.grab, &taken, [&](int64_t i, int &j)
                        __attribute__((always_inline)) {
-            batch_item<MT, KIND, NP>(part, i, j, inst, prefix, G.first, G.count, sq, red, coef, Cb,
+            batch_item<MT, KIND>(part, i, j, inst, prefix, G.first, G.count, sq, red, coef, Cb,
                                      HCb);
         });
     };

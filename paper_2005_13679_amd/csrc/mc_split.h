@@ -182,13 +182,13 @@ __device__ __forceinline__ void split_pair_map(const int32_t *t2r, int64_t pos, 
     ai = fma(A, bi, ai);
 }
 
-template <int MT, bool BIGC, int NP, int... Ps>
-__device__ __forceinline__ void split_pairs_map(std::integer_sequence<int, Ps...>, Part<NP> part,
+template <int MT, bool BIGC, class PT, int... Ps>
+__device__ __forceinline__ void split_pairs_map(std::integer_sequence<int, Ps...>, PT part,
                                                 const uint64_t *pm, const int32_t *t2r,
                                                 int64_t off0, int64_t off1, int lane,
                                                 const int (&n)[MT], const RowSq<MT> &R,
                                                 const double2 *__restrict__ gd,
-                                                const Gather<BIGC> &ldc, double &ar, double &ai)
+                                                const Gather<BIGC> &ldc, RowSum<PT> &A)
 {
     int64_t pos = off0;
     (
@@ -196,8 +196,11 @@ __device__ __forceinline__ void split_pairs_map(std::integer_sequence<int, Ps...
             constexpr int NSB = reduced_slots(MT, pair_k(MT, Ps), pair_s(MT, Ps)) * kTile;
             if constexpr (NSB > 0) {
                 if (((pm[Ps >> 6] >> (Ps & 63)) & 1) && pos + NSB <= off1) {
-                    if (NP == 1 || part.template has<Ps>())
-                        split_pair_map<MT, BIGC, Ps>(t2r, pos, lane, n, R, gd, ldc, ar, ai);
+                    if (PT::kWaves == 1 || part.template has<Ps>()) {
+                        double2 u = A.get(Ps);
+                        split_pair_map<MT, BIGC, Ps>(t2r, pos, lane, n, R, gd, ldc, u.x, u.y);
+                        A.put(Ps, u);
+                    }
                     pos += NSB;
                 }
             }
@@ -310,18 +313,21 @@ __device__ __forceinline__ void split_pair_chain(int64_t D, const int32_t *__res
     }
 }
 
-template <int MT, bool BIGC, int NP, int... Ps>
-__device__ __forceinline__ void split_pairs_chain(std::integer_sequence<int, Ps...>, Part<NP> part, int64_t D,
+template <int MT, bool BIGC, class PT, int... Ps>
+__device__ __forceinline__ void split_pairs_chain(std::integer_sequence<int, Ps...>, PT part, int64_t D,
                                                   const int32_t *__restrict__ t1,
                                                   __amdgpu_buffer_rsrc_t r1, int lane,
                                                   const int (&n)[MT], const RowSq<MT> &R,
                                                   const double2 *__restrict__ gd,
-                                                  const Gather<BIGC> &ldc, double &ar, double &ai)
+                                                  const Gather<BIGC> &ldc, RowSum<PT> &A)
 {
     (
         [&] {
-            if (NP == 1 || part.template has<Ps>())
-                split_pair_chain<MT, BIGC, Ps>(D, t1, r1, lane, n, R, gd, ldc, ar, ai);
+            if (PT::kWaves == 1 || part.template has<Ps>()) {
+                double2 u = A.get(Ps);
+                split_pair_chain<MT, BIGC, Ps>(D, t1, r1, lane, n, R, gd, ldc, u.x, u.y);
+                A.put(Ps, u);
+            }
         }(),
         ...);
 }
@@ -973,45 +979,46 @@ __device__ __forceinline__ void class_targets(std::integer_sequence<int, Is...>,
 // The whole stream.  One wavefront: batch B's block issues batch B+1's targets
 // (table loads in flight during B's gathers), then B's gathers and arithmetic;
 // several: each batch by itself.
-template <int MT, int FORM, bool BIGC, int B, int NP, class Src>
-__device__ __forceinline__ void class_batches(Part<NP> part, int32_t (&cur)[MC_CLASS_BATCH],
+template <int MT, int FORM, bool BIGC, int B, class PT, class Src>
+__device__ __forceinline__ void class_batches(PT part, int32_t (&cur)[MC_CLASS_BATCH],
                                               int32_t (&nxt)[MC_CLASS_BATCH], const Src &src,
                                               int32_t own_t, double2 own_c, const RowSq<MT> &R,
                                               const RunKeys<MT> &rk,
                                               const ClassConsts<MT, FORM> &k,
-                                              const Gather<BIGC> &ldc, double &ar, double &ai)
+                                              const Gather<BIGC> &ldc, RowSum<PT> &A)
 {
     constexpr int NB = kClassPlan<MT, FORM>.nb;
     if constexpr (B < NB) {
         // each batch in a basic block of its own (see opaque_true)
         if (part.template has<B>()) {
-            if constexpr (NP > 1)
+            if constexpr (PT::kWaves > 1)
                 class_targets<MT, FORM, B>(std::make_integer_sequence<int, MC_CLASS_BATCH>{}, src,
                                            cur);
             else if constexpr (B + 1 < NB)
                 class_targets<MT, FORM, B + 1>(std::make_integer_sequence<int, MC_CLASS_BATCH>{},
                                                src, nxt);
+            double2 u = A.get(B);
             class_batch<MT, FORM, BIGC, B>(std::make_integer_sequence<int, MC_CLASS_BATCH>{}, src,
-                                           cur, own_t, own_c, R, rk, k, ldc, ar, ai);
+                                           cur, own_t, own_c, R, rk, k, ldc, u.x, u.y);
+            A.put(B, u);
         }
-        class_batches<MT, FORM, BIGC, B + 1>(part, nxt, cur, src, own_t, own_c, R, rk, k, ldc, ar,
-                                             ai);
+        class_batches<MT, FORM, BIGC, B + 1>(part, nxt, cur, src, own_t, own_c, R, rk, k, ldc, A);
     }
 }
 
 // `n`: the row's occupations; own_t: its index (negative past the end).
-template <int MT, int FORM, bool BIGC, int NP, class Src>
-__device__ __forceinline__ void class_stream(Part<NP> part, const Src &src, int32_t own_t,
+template <int MT, int FORM, bool BIGC, class PT, class Src>
+__device__ __forceinline__ void class_stream(PT part, const Src &src, int32_t own_t,
                                              double2 own_c, const int (&n)[MT],
                                              const RowSq<MT> &R, const ClassConsts<MT, FORM> &k,
-                                             const Gather<BIGC> &ldc, double &ar, double &ai)
+                                             const Gather<BIGC> &ldc, RowSum<PT> &A)
 {
     RunKeys<MT> rk{n, own_t >= 0 ? own_t + n[0] : -1, {}};
     run_key_shifts(std::make_integer_sequence<int, 2 * kMaxShift + 1>{}, rk.key, rk.at);
     int32_t ta[MC_CLASS_BATCH], tb[MC_CLASS_BATCH];
-    if constexpr (NP == 1)
+    if constexpr (PT::kWaves == 1)
         class_targets<MT, FORM, 0>(std::make_integer_sequence<int, MC_CLASS_BATCH>{}, src, ta);
-    class_batches<MT, FORM, BIGC, 0>(part, ta, tb, src, own_t, own_c, R, rk, k, ldc, ar, ai);
+    class_batches<MT, FORM, BIGC, 0>(part, ta, tb, src, own_t, own_c, R, rk, k, ldc, A);
 }
 
 // Targets of a full tile through the tables: the tile's single-jump block
@@ -1037,8 +1044,8 @@ struct MapSlots {
 
 // One 64-row tile of H.C in the case-split form; MAP: true double jumps from
 // the reduced map, else chained.  `cf` holds the staged constants.
-template <int MT, typename OccT, bool BIGC, bool MAP, int NP>
-__device__ __forceinline__ double2 apply_tile_split(Part<NP> part, int64_t tile, int64_t D, int64_t cap,
+template <int MT, typename OccT, bool BIGC, bool MAP, class PT>
+__device__ __forceinline__ double2 apply_tile_split(PT part, int64_t tile, int64_t D, int64_t cap,
                                                  const double *sq, const OccT *__restrict__ occ,
                                                  const int32_t *__restrict__ t1,
                                                  const uint64_t *__restrict__ pmask,
@@ -1069,7 +1076,7 @@ __device__ __forceinline__ double2 apply_tile_split(Part<NP> part, int64_t tile,
 
     // the row's own coefficient (one-body diagonal and coincident pairs)
     const double2 cg = ldc(live ? (int32_t)g : -1);
-    double ar = 0.0, ai = 0.0;
+    double2 own = make_double2(0.0, 0.0);
     if (part.own()) {
         double dr = 0.0, di = 0.0;
 #pragma unroll
@@ -1083,9 +1090,10 @@ __device__ __forceinline__ double2 apply_tile_split(Part<NP> part, int64_t tile,
             dr = fma(GI[p].x, w, dr);
             di = fma(GI[p].y, w, di);
         }
-        ar = dr * cg.x - di * cg.y;
-        ai = dr * cg.y + di * cg.x;
+        own.x = dr * cg.x - di * cg.y;
+        own.y = dr * cg.y + di * cg.x;
     }
+    RowSum<PT> A(part, own);
 
     const __amdgpu_buffer_rsrc_t r1 = make_rsrc(t1 + tile * NS * kTile, (uint32_t)(NS * kTile * 4));
     if constexpr (MAP && MT <= kStreamMaxMReduced && FlatTile<MT>::NDBL > 0) {
@@ -1104,15 +1112,17 @@ __device__ __forceinline__ double2 apply_tile_split(Part<NP> part, int64_t tile,
                 make_rsrc(t2r + off0, (uint32_t)(FlatTile<MT>::NDBL * kTile * 4));
             const MapSlots<MT, 0> src{r1, r2, lane};
             const ClassConsts<MT, 0> k{HS, GS, GD, x};
-            class_stream<MT, 0, BIGC>(part, src, live ? (int32_t)g : -2, cg, n, R, k, ldc, ar, ai);
-            return make_double2(ar, ai);
+            class_stream<MT, 0, BIGC>(part, src, live ? (int32_t)g : -2, cg, n, R, k, ldc, A);
+            return A.total();
         }
     }
 
     // single jumps a -> b with coefficient sqrt(n_a (n_b+1)) (HS + sum_c n_c GS)
 #pragma unroll
     for (int j0 = 0; j0 < NS; j0 += SB) {
-        if (NP > 1 && part.part != j0 / SB % NP) continue;
+        if (PT::kWaves > 1 && part.part != j0 / SB % PT::kWaves) continue;
+        double2 u = A.get(j0 / SB);
+        double &ar = u.x, &ai = u.y;
         int32_t t[SB];
         double2 c[SB];
 #pragma unroll
@@ -1145,6 +1155,7 @@ __device__ __forceinline__ double2 apply_tile_split(Part<NP> part, int64_t tile,
             ai = fma(er, c[i].y, ai);
             ai = fma(ei, c[i].x, ai);
         }
+        A.put(j0 / SB, u);
     }
 
     // true double jumps: a compile-time fold over the removal pairs, one
@@ -1155,12 +1166,12 @@ __device__ __forceinline__ double2 apply_tile_split(Part<NP> part, int64_t tile,
         int64_t off0, off1;
         t2_block(t2_off, tile, cap, off0, off1);
         split_pairs_map<MT, BIGC>(std::make_integer_sequence<int, P>{}, part, pmask + tile * W, t2r,
-                                  off0, off1, lane, n, R, GD, ldc, ar, ai);
+                                  off0, off1, lane, n, R, GD, ldc, A);
     } else {
         split_pairs_chain<MT, BIGC>(std::make_integer_sequence<int, P>{}, part, D, t1, r1, lane, n, R, GD,
-                                    ldc, ar, ai);
+                                    ldc, A);
     }
-    return make_double2(ar, ai);
+    return A.total();
 }
 
 // One 64-row tile of H.C in the paper's form (the paper's double-jump map,
@@ -1169,8 +1180,8 @@ __device__ __forceinline__ double2 apply_tile_split(Part<NP> part, int64_t tile,
 // stream: the paper's sum over all its slots, reading only the anchors'
 // table columns and gathering each distinct target once; other tiles take
 // the per-pair path.
-template <int MT, typename OccT, bool BIGC, int NP>
-__device__ __forceinline__ double2 apply_tile_paper(Part<NP> part, int64_t tile, int64_t D, int64_t cap,
+template <int MT, typename OccT, bool BIGC, class PT>
+__device__ __forceinline__ double2 apply_tile_paper(PT part, int64_t tile, int64_t D, int64_t cap,
                                                  const double *sq, const OccT *__restrict__ occ,
                                                  const int32_t *__restrict__ t1,
                                                  const uint64_t *__restrict__ pmask,
@@ -1207,17 +1218,18 @@ __device__ __forceinline__ double2 apply_tile_paper(Part<NP> part, int64_t tile,
                 dr = fma(h[k * MT + k].x, (double)n[k], dr);
                 di = fma(h[k * MT + k].y, (double)n[k], di);
             }
-            double ar = 0.0, ai = 0.0;
+            double2 own = make_double2(0.0, 0.0);
             if (part.own()) {
-                ar = dr * cg.x - di * cg.y;
-                ai = dr * cg.y + di * cg.x;
+                own.x = dr * cg.x - di * cg.y;
+                own.y = dr * cg.y + di * cg.x;
             }
+            RowSum<PT> A(part, own);
             const MapSlots<MT, 1> src{
                 make_rsrc(t1 + tile * NS * kTile, (uint32_t)(NS * kTile * 4)),
                 make_rsrc(t2 + off0, (uint32_t)(P * NS * kTile * 4)), lane};
             const ClassConsts<MT, 1> k{h, gp};
-            class_stream<MT, 1, BIGC>(part, src, live ? (int32_t)g : -2, cg, n, R, k, ldc, ar, ai);
-            return make_double2(ar, ai);
+            class_stream<MT, 1, BIGC>(part, src, live ? (int32_t)g : -2, cg, n, R, k, ldc, A);
+            return A.total();
         }
     }
     return apply_tile_t2<MT, OccT, BIGC>(part, tile, D, cap, sq, occ, t1, pmask, t2_off, t2, h, gp, C);
@@ -1225,9 +1237,9 @@ __device__ __forceinline__ double2 apply_tile_paper(Part<NP> part, int64_t tile,
 
 // One tile through the tables in any kind; `ca` holds the case-split constants
 // or h, `cb` the paper form's G'.
-template <int MT, typename OccT, int KIND, int NP>
+template <int MT, typename OccT, int KIND, class PT>
 __device__ __forceinline__ double2 apply_tile_tables(
-    Part<NP> part, int64_t tile, int64_t D, int64_t cap, const double *sq,
+    PT part, int64_t tile, int64_t D, int64_t cap, const double *sq,
     const OccT *__restrict__ occ, const int32_t *__restrict__ t1,
     const uint64_t *__restrict__ pmask, const int64_t *__restrict__ t2_off,
     const int32_t *__restrict__ t2, const double2 *__restrict__ ca,

@@ -88,6 +88,10 @@ MC_TILES_DECLARE(6)
 MC_TILES_DECLARE(7)
 MC_TILES_DECLARE(8)
 #undef MC_TILES_DECLARE
+int tiles_many_5(const GroupCall &);
+int tiles_many_6(const GroupCall &);
+int tiles_many_7(const GroupCall &);
+int tiles_many_8(const GroupCall &);
 
 // Calls tiles_<what>_<M> (1 <= M <= 8).
 #define MC_TILES_CALL(what, M, call)                                                     \
@@ -134,8 +138,24 @@ inline int tiles_joint(int kind, const JointCall &c)
     }
 }
 
-// Blocks of 256 threads per four tiles, or one block per tile whose wavefronts
-// share it (from M = 5 on, in small spaces; mc_apply.h has the reason).
+// Whether instances of this kind are summed in kTileParts parts (from M = 5 on, in
+// small spaces; mc_apply.h has the reason).
 inline bool small_parts(int M, int kind) { return M >= 5 && kind != kDirectLarge; }
+
+// Groups of such instances with at most this many tiles have a block per tile,
+// whose wavefronts share it, larger ones a wavefront per tile, which keeps the
+// sums.  One apply in the better of orders 0 and 2, us, shared / kept, at the tiles
+// given: M = 5, N = 20, without tables 498 17 / 22, 996 25 / 21, 1,992 40 / 23, 8,134
+// 130 / 66; reduced map 19 / 28, 31 / 31, 51 / 34, 178 / 101; chained 13 / 27, 19 / 27,
+// 29 / 30, 88 / 83.  M = 6, N = 14, 910 35 / 35, 2,002 62 / 40, 8,190 216 / 121.  M = 8,
+// N = 8, 505 40 / 75, 1,010 68 / 75, 2,020 126 / 88, 8,181 456 / 308.  With order 3 the
+// counter costs more the more workers take from it, and sharing is level up to
+// 4,000 tiles and within 1.3 above.
+inline int64_t shared_tiles(int M, int kind, int order)
+{
+    if (order == 3) return INT64_MAX;
+    if (M == 5) return kind == kSplitChain ? 1600 : 768;
+    return M == 6 && kind == kDirect ? 768 : 1300;
+}
 
 }  // namespace mc

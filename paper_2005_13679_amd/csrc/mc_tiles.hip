@@ -1,6 +1,7 @@
 // Kernels with one row per lane for MC_TILES_M orbitals.  Compiled once per
 // orbital count, and in parts (MC_TILES_PART: 0 table-driven, 1 table-free, 2
-// groups of a batch), so that the long compilations run side by side.
+// groups of a batch, 3 its groups of many small instances), so that the long
+// compilations run side by side.
 #include "mc_tiles.h"
 
 #include "mc_apply.h"
@@ -10,7 +11,8 @@
 
 #define MC_TILES_NAME2(what, M) tiles_##what##_##M
 #define MC_TILES_NAME1(what, M) MC_TILES_NAME2(what, M)
-#define MC_TILES_NAME(what) MC_TILES_NAME1(what, MC_TILES_M)
+#define MC_TILES_NAME0(what, M) MC_TILES_NAME1(what, M)
+#define MC_TILES_NAME(what) MC_TILES_NAME0(what, MC_TILES_M)
 
 namespace mc {
 
@@ -34,7 +36,7 @@ void k_apply_tables(int N, int64_t D, int64_t tiles, int64_t cap, const OccT *__
     if constexpr (kLdsRoots<MT>) fill_sqrt_table(sq, N + 3);
     const int64_t tile = NP == 1 ? (int64_t)blockIdx.x * 4 + wave_in_block() : blockIdx.x;
     if (tile >= tiles) return;
-    const Part<NP> part{NP == 1 ? 0 : wave_in_block()};
+    const Part<NP> part{NP == 1 ? 0 : wave_in_block(), nullptr};
     store_tile<NP>(apply_tile_tables<MT, OccT, KIND>(part, tile, D, cap, sq, occ, t1, pmask, t2_off,
                                                      t2, ca, cb, C),
                    part.part, tile, D, red, HC);
@@ -92,7 +94,7 @@ void k_apply_direct(int N, int64_t D, int64_t tiles, int64_t nblocks,
     const int64_t block = xcd_block_as<kDirectRemap<MT>>(blockIdx.x, nblocks);
     const int64_t tile = NP == 1 ? block * 4 + wave_in_block() : block;
     if (tile >= tiles) return;
-    const Part<NP> part{NP == 1 ? 0 : wave_in_block()};
+    const Part<NP> part{NP == 1 ? 0 : wave_in_block(), nullptr};
     store_tile<NP>(apply_tile_direct<MT, BIGC>(part, tile, N, D, sq, cf, C), part.part, tile, D, red,
                    HC);
 }
@@ -125,8 +127,8 @@ int MC_TILES_NAME(direct)(const DirectCall &c)
 // interleaved over its wavefronts; with order 3 wavefronts take a few items
 // at a time from a per-group counter (dynamic balance, like a plain launch).
 // With NP > 1 a worker is a block, whose wavefronts share each tile, instead of
-// a wavefront.
-template <int MT, int KIND, int NP>
+// a wavefront, which keeps NC sums of a row.
+template <int MT, int KIND, int NP, int NC>
 __global__ __launch_bounds__(NP == 1 ? 256 : NP * 64) __attribute__((amdgpu_waves_per_eu(MC_APPLY_WAVES)))
 void k_batch_apply(const BatchInst *__restrict__ inst, const int64_t *__restrict__ prefix,
                    int first, int count, int64_t items, int64_t nblocks, int order, int grab,
@@ -135,11 +137,14 @@ void k_batch_apply(const BatchInst *__restrict__ inst, const int64_t *__restrict
 {
     __shared__ double sq[kLdsRoots<MT> ? kBatchMaxN + 3 : 1];
     if constexpr (kLdsRoots<MT>) fill_sqrt_table(sq, kBatchMaxN + 3);
-    __shared__ double2 red[NP > 1 ? NP * kTile : 1];
+    // the paper's map at M = 5 has the registers for the sums
+    using PT = Part<NP, NC, !(MT == 5 && KIND == kPaperMap)>;
+    __shared__ double2 red[NP > 1 ? NP * kTile : (PT::kLds ? 4 * NC * kTile : 1)];
     __shared__ uint32_t taken;
-    const Part<NP> part{NP == 1 ? 0 : wave_in_block()};
+    const PT part{NP == 1 ? 0 : wave_in_block(),
+                  PT::kLds ? red + wave_in_block() * NC * kTile + (threadIdx.x & 63) : nullptr};
     auto tile_body = [&](int64_t i, int &j) __attribute__((always_inline)) {
-        batch_item<MT, KIND, NP>(part, i, j, inst, prefix, first, count, sq, red, coef, Cb, HCb);
+        batch_item<MT, KIND>(part, i, j, inst, prefix, first, count, sq, red, coef, Cb, HCb);
     };
     int j = 0;
     constexpr int WB = NP == 1 ? 4 : 1;   // workers per block
@@ -174,26 +179,34 @@ void k_batch_apply(const BatchInst *__restrict__ inst, const int64_t *__restrict
     for (int64_t i = i0; i < iend; i += step) tile_body(i, j);
 }
 
-template <int KIND, int NP>
+template <int KIND, int NP, int NC>
 static int group_launch(const GroupCall &c)
 {
-    hipLaunchKernelGGL((k_batch_apply<MC_TILES_M, KIND, NP>), dim3(c.blocks),
+    hipLaunchKernelGGL((k_batch_apply<MC_TILES_M, KIND, NP, NC>), dim3(c.blocks),
                        dim3(NP == 1 ? 256 : NP * 64), 0, c.s, c.inst, c.prefix, c.first, c.count,
                        c.items, c.blocks, c.order, c.grab, c.counter, c.coef, c.C, c.HC);
     return launch_status();
 }
 
-int MC_TILES_NAME(group)(const GroupCall &c)
+#if MC_TILES_PART == 2
+#define MC_GROUP_NAME group
+constexpr int kGroupWaves = kSmallParts<MC_TILES_M>, kGroupSums = 1;
+#else
+#define MC_GROUP_NAME many
+constexpr int kGroupWaves = 1, kGroupSums = kTileParts;
+#endif
+
+int MC_TILES_NAME(MC_GROUP_NAME)(const GroupCall &c)
 {
-    constexpr int NP = kSmallParts<MC_TILES_M>;
+    constexpr int NP = kGroupWaves, NC = kGroupSums;
     switch (c.kind) {
-    case kPaperMap: return group_launch<kPaperMap, NP>(c);
-    case kPaperChain: return group_launch<kPaperChain, NP>(c);
-    case kSplitMap: return group_launch<kSplitMap, NP>(c);
-    case kSplitChain: return group_launch<kSplitChain, NP>(c);
-    case kDirect: return group_launch<kDirect, NP>(c);
-#if MC_TILES_M >= 5
-    case kDirectLarge: return group_launch<kDirectLarge, 1>(c);
+    case kPaperMap: return group_launch<kPaperMap, NP, NC>(c);
+    case kPaperChain: return group_launch<kPaperChain, NP, NC>(c);
+    case kSplitMap: return group_launch<kSplitMap, NP, NC>(c);
+    case kSplitChain: return group_launch<kSplitChain, NP, NC>(c);
+    case kDirect: return group_launch<kDirect, NP, NC>(c);
+#if MC_TILES_PART == 2 && MC_TILES_M >= 5
+    case kDirectLarge: return group_launch<kDirectLarge, 1, 1>(c);
 #endif
     default: return MC_EINVAL;
     }
