@@ -19,6 +19,7 @@ import hashlib
 import json
 import math
 import os
+import re
 import sys
 import time
 
@@ -172,15 +173,31 @@ def rho_models(N: int, M: int) -> dict:
     }
 
 
-# sources each path's apply kernel is built from
-KERNEL_SOURCES = {p: ("mc_block.hip", "mc_block.h", "mc_internal.h")
-                  + (("mc_direct.h",) if p == "direct" else ()) for p in PATHS}
+# the source each path's apply kernel is compiled from; the headers follow from it
+KERNEL_SOURCES = {p: ("mc_block.hip",) for p in PATHS}
+
+
+def kernel_sources(path: str = "reduced_map") -> list[str]:
+    """KERNEL_SOURCES of the path and every header of this repository that they
+    include, directly or not."""
+    dirs = [os.path.join(ROOT, "paper_2005_13679_amd", "csrc"), os.path.join(ROOT, "include")]
+    todo, found = list(KERNEL_SOURCES[path]), []
+    while todo:
+        name = todo.pop(0)
+        file = next((os.path.join(d, name) for d in dirs if os.path.exists(os.path.join(d, name))),
+                    None)
+        if file is None or file in found:
+            continue
+        found.append(file)
+        with open(file) as fh:
+            todo += re.findall(r'^#include "([^"]+)"', fh.read(), flags=re.M)
+    return found
 
 
 def kernel_source_hash(path: str = "reduced_map") -> str:
     h = hashlib.sha256()
-    for f in KERNEL_SOURCES[path]:
-        with open(os.path.join(ROOT, "paper_2005_13679_amd", "csrc", f), "rb") as fh:
+    for f in kernel_sources(path):
+        with open(f, "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
 
