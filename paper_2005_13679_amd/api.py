@@ -298,7 +298,7 @@ def _as_dev(x, device, shape=None) -> torch.Tensor:
         return x
     if not isinstance(x, torch.Tensor):
         x = torch.as_tensor(np.asarray(x))
-    x = x.to(device=device, dtype=torch.complex128)
+    x = x.to(device=device, dtype=torch.complex128).resolve_conj().resolve_neg()
     if shape is not None:
         x = x.reshape(shape)
     return x.contiguous()
