@@ -15,13 +15,6 @@
 #ifndef MC_APPLY_WAVES
 #define MC_APPLY_WAVES 2
 #endif
-// Double-jump index loads: 0 = each batch loads its indices, then gathers;
-// 1 = the next batch's indices are loaded while the current batch's gathers
-// are in flight (within a pair); 2 = also the first batch of the next block
-// (across pairs, and the first block during the one-body part).
-#ifndef MC_T2_PIPELINE
-#define MC_T2_PIPELINE 0
-#endif
 
 namespace mc {
 
@@ -291,56 +284,24 @@ __device__ __forceinline__ void load_t2_batch(int32_t (&t)[SB], __amdgpu_buffer_
             t[i] = buf_ld_i32(r, (uint32_t)((t2_col<MT>(J0 + i) * kTile + lane) * 4), 0);
 }
 
-// Resource over the double-jump block starting at `pos`, clipped to the
-// tile's [., off1) range (a zero-length resource makes loads return 0).
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t t2_block_rsrc(const int32_t *t2, int64_t pos,
-                                                                int64_t off1, int ns)
-{
-    int64_t n = off1 - pos;
-    n = n < 0 ? 0 : (n > (int64_t)ns * kTile ? (int64_t)ns * kTile : n);
-    return make_rsrc(t2 + (pos < off1 ? pos : off1), (uint32_t)(n * 4));
-}
-
 // Contribution of removal pair P = (K, S), K <= S, to one row:
 //   A_KS * sum_{q,l} G'_{P,ql} B_ql(m) C[T2 slot],   m = n - e_K - e_S,
 // for the pair's block at `pos` (M*M*64 entries).  Lanes whose row cannot
 // lose (K, S) hold -1 entries (gathers read 0) and get A = 0.
-// Software pipeline: `tf` holds the first index batch of this block on entry
-// (loaded earlier); batch b's gathers are issued, then the next batch's
-// indices are loaded (after the last batch: the first batch of the next
-// block, which is simply the next M*M*64 entries since the blocks of the
-// present pairs are contiguous), then batch b's arithmetic waits for its
-// gathers.
-template <int MT, bool BIGC, int B, int NB>
-__device__ __forceinline__ void pair_batches(const int32_t *t2, int64_t pos, int64_t off1, int lane,
-                                             __amdgpu_buffer_rsrc_t r2,
-                                             int32_t (&tf)[kT2Batch<MT>],
-                                             int32_t (&tn)[kT2Batch<MT>], const double (&rq)[MT],
-                                             const double (&dq)[MT], const double2 *__restrict__ G,
-                                             const Gather<BIGC> &ldc, double &br, double &bi)
+template <int MT, int B, int NB>
+__device__ __forceinline__ void pair_batches(int lane, __amdgpu_buffer_rsrc_t r2,
+                                             const double (&rq)[MT], const double (&dq)[MT],
+                                             const double2 *__restrict__ G,
+                                             const Gather<false> &ldc, double &br, double &bi)
 {
     if constexpr (B < NB) {
         constexpr int NS = kT2Slots<MT>, SB = kT2Batch<MT>, J0 = B * SB;
+        int32_t t[SB];
         double2 c[SB];
-        if constexpr (MC_T2_PIPELINE == 0) {
-            // indices of this batch, then its gathers
-            load_t2_batch<MT, SB, J0>(tn, r2, lane);
+        load_t2_batch<MT, SB, J0>(t, r2, lane);
 #pragma unroll
-            for (int i = 0; i < SB; ++i)
-                if (J0 + i < NS) c[i] = ldc(tn[i]);
-        } else {
-            if constexpr (MC_T2_PIPELINE == 1 && B == 0) load_t2_batch<MT, SB, 0>(tf, r2, lane);
-#pragma unroll
-            for (int i = 0; i < SB; ++i)
-                if (J0 + i < NS) c[i] = ldc(B == 0 ? tf[i] : tn[i]);
-            if constexpr (B + 1 < NB) {
-                load_t2_batch<MT, SB, J0 + SB>(tn, r2, lane);
-            } else if constexpr (MC_T2_PIPELINE == 2) {
-                const __amdgpu_buffer_rsrc_t rn =
-                    t2_block_rsrc(t2, pos + MT * MT * kTile, off1, MT * MT);
-                load_t2_batch<MT, SB, 0>(tf, rn, lane);
-            }
-        }
+        for (int i = 0; i < SB; ++i)
+            if (J0 + i < NS) c[i] = ldc(t[i]);
 #pragma unroll
         for (int i = 0; i < SB; ++i) {
             const int j = J0 + i;
@@ -358,15 +319,15 @@ __device__ __forceinline__ void pair_batches(const int32_t *t2, int64_t pos, int
             bi = fma(Gv.x, ci, bi);
             bi = fma(Gv.y, cr, bi);
         }
-        pair_batches<MT, BIGC, B + 1, NB>(t2, pos, off1, lane, r2, tf, tn, rq, dq, G, ldc, br, bi);
+        pair_batches<MT, B + 1, NB>(lane, r2, rq, dq, G, ldc, br, bi);
     }
 }
 
-template <int MT, bool BIGC, int P>
-__device__ __forceinline__ void pair_term(const int32_t *t2, int64_t pos, int64_t off1, int lane,
+template <int MT, int P>
+__device__ __forceinline__ void pair_term(const int32_t *t2, int64_t pos, int lane,
                                           const int (&n)[MT], const RowSq<MT> &R,
-                                          const double2 *__restrict__ gp, const Gather<BIGC> &ldc,
-                                          int32_t (&tf)[kT2Batch<MT>], double &ar, double &ai)
+                                          const double2 *__restrict__ gp, const Gather<false> &ldc,
+                                          double &ar, double &ai)
 {
     constexpr int K = pair_k(MT, P), S = pair_s(MT, P);
     constexpr int NS = MT * MT, SB = kT2Batch<MT>;
@@ -384,24 +345,21 @@ __device__ __forceinline__ void pair_term(const int32_t *t2, int64_t pos, int64_
         rq[q] = d == 0 ? R.template root<1>(q) : (d == 1 ? R.template root<0>(q) : R.template root<-1>(q));
         dq[q] = d == 0 ? R.template root<2>(q) : (d == 1 ? R.template root<1>(q) : R.template root<0>(q));
     }
-    int32_t tn[SB];
     double br = 0.0, bi = 0.0;
-    pair_batches<MT, BIGC, 0, NB>(t2, pos, off1, lane, r2, tf, tn, rq, dq, gp + P * NS, ldc, br, bi);
+    pair_batches<MT, 0, NB>(lane, r2, rq, dq, gp + P * NS, ldc, br, bi);
     ar = fma(A, br, ar);
     ai = fma(A, bi, ai);
 }
 
 // All removal pairs in order; each present pair is its own basic block
 // (uniform branch on the tile's pair mask), which keeps the scheduler from
-// hoisting later pairs' loads.  `tf` carries the prefetched first index
-// batch of the next block from pair to pair.
-template <int MT, bool BIGC, class PT, int... Ps>
+// hoisting later pairs' loads.
+template <int MT, class PT, int... Ps>
 __device__ __forceinline__ void all_pairs(std::integer_sequence<int, Ps...>, PT part,
                                           const uint64_t *pm, const int32_t *t2, int64_t off0,
                                           int64_t off1, int lane, const int (&n)[MT],
                                           const RowSq<MT> &R, const double2 *__restrict__ gp,
-                                          const Gather<BIGC> &ldc, int32_t (&tf)[kT2Batch<MT>],
-                                          RowSum<PT> &A)
+                                          const Gather<false> &ldc, RowSum<PT> &A)
 {
     int64_t pos = off0;
     (
@@ -410,7 +368,7 @@ __device__ __forceinline__ void all_pairs(std::integer_sequence<int, Ps...>, PT 
             if (((pm[Ps >> 6] >> (Ps & 63)) & 1) && pos + NSB <= off1) {
                 if (PT::kWaves == 1 || part.template has<Ps>()) {
                     double2 u = A.get(Ps);
-                    pair_term<MT, BIGC, Ps>(t2, pos, off1, lane, n, R, gp, ldc, tf, u.x, u.y);
+                    pair_term<MT, Ps>(t2, pos, lane, n, R, gp, ldc, u.x, u.y);
                     A.put(Ps, u);
                 }
                 pos += NSB;
@@ -422,7 +380,7 @@ __device__ __forceinline__ void all_pairs(std::integer_sequence<int, Ps...>, PT 
 // One 64-row tile of H.C for a compile-time orbital count MT (1..8) through
 // the single- and double-jump maps; every orbital, pair and slot index is a
 // compile-time constant.  Called by one whole wavefront.
-template <int MT, typename OccT, bool BIGC, class PT>
+template <int MT, typename OccT, class PT>
 __device__ __forceinline__ double2 apply_tile_t2(PT part, int64_t tile, int64_t D, int64_t cap, const double *sq,
                                               const OccT *__restrict__ occ,
                                               const int32_t *__restrict__ t1,
@@ -440,18 +398,12 @@ __device__ __forceinline__ double2 apply_tile_t2(PT part, int64_t tile, int64_t 
     const int64_t g = tile * kTile + lane;
     const bool live = g < D;
 
-    // first index batch of the tile's first double-jump block, in flight
-    // during the one-body part
     int64_t off0, off1;
     t2_block(t2_off, tile, cap, off0, off1);
-    int32_t tf[kT2Batch<MT>];
-    if constexpr (MC_T2_PIPELINE == 2)
-        load_t2_batch<MT, kT2Batch<MT>, 0>(tf, t2_block_rsrc(t2, off0, off1, M * M), lane);
-
     int n[M];
     RowSq<M> R;
     load_row<MT, OccT>(occ, tile, lane, n, R, sq);
-    const Gather<BIGC> ldc(C, D);
+    const Gather<false> ldc(C, D);
 
     // diagonal one-body part: sum_k h_kk n_k C_g
     const double2 cg = ldc(live ? (int32_t)g : -1);
@@ -512,8 +464,8 @@ __device__ __forceinline__ double2 apply_tile_t2(PT part, int64_t tile, int64_t 
     }
 
     // double jumps: one block of M*M*64 entries per pair present in the tile
-    all_pairs<MT, BIGC>(std::make_integer_sequence<int, P>{}, part, pmask + tile * W, t2, off0, off1,
-                        lane, n, R, gp, ldc, tf, A);
+    all_pairs<MT>(std::make_integer_sequence<int, P>{}, part, pmask + tile * W, t2, off0, off1,
+                        lane, n, R, gp, ldc, A);
     return A.total();
 }
 
@@ -529,12 +481,12 @@ __device__ __forceinline__ double2 apply_tile_t2(PT part, int64_t tile, int64_t 
 // from the tile's own single-jump block (coalesced, cache-resident); the
 // second hop is a gather from rows near g.
 // ---------------------------------------------------------------------------
-template <int MT, bool BIGC, int P>
+template <int MT, int P>
 __device__ __forceinline__ void pair_term_chained(int64_t D, const int32_t *__restrict__ t1,
                                                   __amdgpu_buffer_rsrc_t r1, int lane,
                                                   const int (&n)[MT], const RowSq<MT, kLdsRootsChained<MT>> &R,
                                                   const double2 *__restrict__ gp,
-                                                  const Gather<BIGC> &ldc, double &ar, double &ai)
+                                                  const Gather<false> &ldc, double &ar, double &ai)
 {
     constexpr int K = pair_k(MT, P), S = pair_s(MT, P);
     constexpr int NS = MT * MT, SB = kSlotBatch<MT>;
@@ -603,13 +555,13 @@ __device__ __forceinline__ void pair_term_chained(int64_t D, const int32_t *__re
 // values live at once there.  K and S are wave-uniform loop counters; q and
 // l stay compile-time, so the per-row occupations are picked with selects and
 // the roots come from the block's sqrt table.
-template <int MT, bool BIGC, class PT>
+template <int MT, class PT>
 __device__ __forceinline__ void pairs_chained_loop(PT part, int64_t D, int64_t g,
                                                    const int32_t *__restrict__ t1,
                                                    __amdgpu_buffer_rsrc_t r1, int lane,
                                                    const int (&n)[MT], const double *sq,
                                                    const double2 *__restrict__ gp,
-                                                   const Gather<BIGC> &ldc, RowSum<PT> &sum)
+                                                   const Gather<false> &ldc, RowSum<PT> &sum)
 {
     constexpr int NS = MT * MT, SB = kSlotBatch<MT>;
     int P = 0;
@@ -688,19 +640,19 @@ __device__ __forceinline__ void pairs_chained_loop(PT part, int64_t D, int64_t g
     }
 }
 
-template <int MT, bool BIGC, class PT, int... Ps>
+template <int MT, class PT, int... Ps>
 __device__ __forceinline__ void all_pairs_chained(std::integer_sequence<int, Ps...>, PT part, int64_t D,
                                                   const int32_t *__restrict__ t1,
                                                   __amdgpu_buffer_rsrc_t r1, int lane,
                                                   const int (&n)[MT], const RowSq<MT, kLdsRootsChained<MT>> &R,
                                                   const double2 *__restrict__ gp,
-                                                  const Gather<BIGC> &ldc, RowSum<PT> &A)
+                                                  const Gather<false> &ldc, RowSum<PT> &A)
 {
     (
         [&] {
             if (PT::kWaves == 1 || part.template has<Ps>()) {
                 double2 u = A.get(Ps);
-                pair_term_chained<MT, BIGC, Ps>(D, t1, r1, lane, n, R, gp, ldc, u.x, u.y);
+                pair_term_chained<MT, Ps>(D, t1, r1, lane, n, R, gp, ldc, u.x, u.y);
                 A.put(Ps, u);
             }
         }(),
@@ -708,7 +660,7 @@ __device__ __forceinline__ void all_pairs_chained(std::integer_sequence<int, Ps.
 }
 
 // One 64-row tile of H.C through single jumps only (see above).
-template <int MT, typename OccT, bool BIGC, class PT>
+template <int MT, typename OccT, class PT>
 __device__ __forceinline__ double2 apply_tile_chained(PT part, int64_t tile, int64_t D, const double *sq,
                                                    const OccT *__restrict__ occ,
                                                    const int32_t *__restrict__ t1,
@@ -725,7 +677,7 @@ __device__ __forceinline__ double2 apply_tile_chained(PT part, int64_t tile, int
     int n[M];
     RowSq<M, kLdsRootsChained<MT>> R;
     load_row<MT, OccT>(occ, tile, lane, n, R, sq);
-    const Gather<BIGC> ldc(C, D);
+    const Gather<false> ldc(C, D);
     const __amdgpu_buffer_rsrc_t r1 =
         make_rsrc(t1 + tile * NS * kTile, (uint32_t)(NS * kTile * 4));
     const double2 cg = ldc(live ? (int32_t)g : -1);
@@ -777,9 +729,9 @@ __device__ __forceinline__ double2 apply_tile_chained(PT part, int64_t tile, int
         A.put(j0 / SB, u);
     }
     if constexpr (kLdsRootsChained<MT>)
-        pairs_chained_loop<MT, BIGC>(part, D, g, t1, r1, lane, n, sq, gp, ldc, A);
+        pairs_chained_loop<MT>(part, D, g, t1, r1, lane, n, sq, gp, ldc, A);
     else
-        all_pairs_chained<MT, BIGC>(std::make_integer_sequence<int, P>{}, part, D, t1, r1, lane, n, R,
+        all_pairs_chained<MT>(std::make_integer_sequence<int, P>{}, part, D, t1, r1, lane, n, R,
                                     gp, ldc, A);
     return A.total();
 }

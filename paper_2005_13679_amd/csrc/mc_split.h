@@ -143,11 +143,11 @@ __device__ inline void stage_split_constants(int M, int adjoint, const double2 *
 // Contribution of removal pair P through the reduced map block at `pos`
 // (nd(K, S) * 64 entries): A_KS sum_r GD[P][r] B_r C[t2r slot r].  All
 // slot reads, then all gathers, then the arithmetic (nd <= 10 at M <= 5).
-template <int MT, bool BIGC, int P>
+template <int MT, int P>
 __device__ __forceinline__ void split_pair_map(const int32_t *t2r, int64_t pos, int lane,
                                                const int (&n)[MT], const RowSq<MT> &R,
                                                const double2 *__restrict__ gd,
-                                               const Gather<BIGC> &ldc, double &ar, double &ai)
+                                               const Gather<false> &ldc, double &ar, double &ai)
 {
     constexpr int K = pair_k(MT, P), S = pair_s(MT, P);
     constexpr int ND = reduced_slots(MT, K, S);
@@ -182,13 +182,13 @@ __device__ __forceinline__ void split_pair_map(const int32_t *t2r, int64_t pos, 
     ai = fma(A, bi, ai);
 }
 
-template <int MT, bool BIGC, class PT, int... Ps>
+template <int MT, class PT, int... Ps>
 __device__ __forceinline__ void split_pairs_map(std::integer_sequence<int, Ps...>, PT part,
                                                 const uint64_t *pm, const int32_t *t2r,
                                                 int64_t off0, int64_t off1, int lane,
                                                 const int (&n)[MT], const RowSq<MT> &R,
                                                 const double2 *__restrict__ gd,
-                                                const Gather<BIGC> &ldc, RowSum<PT> &A)
+                                                const Gather<false> &ldc, RowSum<PT> &A)
 {
     int64_t pos = off0;
     (
@@ -198,7 +198,7 @@ __device__ __forceinline__ void split_pairs_map(std::integer_sequence<int, Ps...
                 if (((pm[Ps >> 6] >> (Ps & 63)) & 1) && pos + NSB <= off1) {
                     if (PT::kWaves == 1 || part.template has<Ps>()) {
                         double2 u = A.get(Ps);
-                        split_pair_map<MT, BIGC, Ps>(t2r, pos, lane, n, R, gd, ldc, u.x, u.y);
+                        split_pair_map<MT, Ps>(t2r, pos, lane, n, R, gd, ldc, u.x, u.y);
                         A.put(Ps, u);
                     }
                     pos += NSB;
@@ -221,12 +221,12 @@ __host__ __device__ constexpr int reduced_in_range(int M, int K, int S, int J0, 
 
 // Slots j in [J0, J1) of pair P through two chained single jumps, in a basic
 // block of its own (gathers of one part in flight at a time).
-template <int MT, bool BIGC, int P, int J0, int J1, bool OWN_BLOCK>
+template <int MT, int P, int J0, int J1, bool OWN_BLOCK>
 __device__ __forceinline__ void split_chain_part(int64_t D, const int32_t *__restrict__ t1,
                                                  int lane, const int32_t (&fh)[MT], bool valid,
                                                  const RowSq<MT> &R,
                                                  const double2 *__restrict__ gd,
-                                                 const Gather<BIGC> &ldc, double &br, double &bi)
+                                                 const Gather<false> &ldc, double &br, double &bi)
 {
     constexpr int K = pair_k(MT, P), S = pair_s(MT, P), NS = MT * MT;
     constexpr int CO = reduced_pair_offset(MT, P);
@@ -267,16 +267,16 @@ __device__ __forceinline__ void split_chain_part(int64_t D, const int32_t *__res
     }
 }
 
-template <int MT, bool BIGC, int P, int... Hs>
+template <int MT, int P, int... Hs>
 __device__ __forceinline__ void split_chain_parts(std::integer_sequence<int, Hs...>, int64_t D,
                                                   const int32_t *__restrict__ t1, int lane,
                                                   const int32_t (&fh)[MT], bool valid,
                                                   const RowSq<MT> &R,
                                                   const double2 *__restrict__ gd,
-                                                  const Gather<BIGC> &ldc, double &br, double &bi)
+                                                  const Gather<false> &ldc, double &br, double &bi)
 {
     constexpr int NS = MT * MT, NH = sizeof...(Hs);
-    (split_chain_part<MT, BIGC, P, Hs * NS / NH, (Hs + 1) * NS / NH, (NH > 1)>(
+    (split_chain_part<MT, P, Hs * NS / NH, (Hs + 1) * NS / NH, (NH > 1)>(
          D, t1, lane, fh, valid, R, gd, ldc, br, bi),
      ...);
 }
@@ -284,12 +284,12 @@ __device__ __forceinline__ void split_chain_parts(std::integer_sequence<int, Hs.
 // The same pair through two chained single jumps: first K -> q from the
 // tile's own single-jump block, then S -> l from the intermediate row; the
 // slots in parts of at most 14 gathers.
-template <int MT, bool BIGC, int P>
+template <int MT, int P>
 __device__ __forceinline__ void split_pair_chain(int64_t D, const int32_t *__restrict__ t1,
                                                  __amdgpu_buffer_rsrc_t r1, int lane,
                                                  const int (&n)[MT], const RowSq<MT> &R,
                                                  const double2 *__restrict__ gd,
-                                                 const Gather<BIGC> &ldc, double &ar, double &ai)
+                                                 const Gather<false> &ldc, double &ar, double &ai)
 {
     constexpr int K = pair_k(MT, P), S = pair_s(MT, P);
     constexpr int ND = reduced_slots(MT, K, S);
@@ -306,26 +306,26 @@ __device__ __forceinline__ void split_pair_chain(int64_t D, const int32_t *__res
                         ? buf_ld_i32(r1, (uint32_t)(((K * MT + q) * kTile + lane) * 4), 0)
                         : -1;
         double br = 0.0, bi = 0.0;
-        split_chain_parts<MT, BIGC, P>(std::make_integer_sequence<int, (ND + 13) / 14>{}, D, t1,
+        split_chain_parts<MT, P>(std::make_integer_sequence<int, (ND + 13) / 14>{}, D, t1,
                                        lane, fh, valid, R, gd, ldc, br, bi);
         ar = fma(A, br, ar);
         ai = fma(A, bi, ai);
     }
 }
 
-template <int MT, bool BIGC, class PT, int... Ps>
+template <int MT, class PT, int... Ps>
 __device__ __forceinline__ void split_pairs_chain(std::integer_sequence<int, Ps...>, PT part, int64_t D,
                                                   const int32_t *__restrict__ t1,
                                                   __amdgpu_buffer_rsrc_t r1, int lane,
                                                   const int (&n)[MT], const RowSq<MT> &R,
                                                   const double2 *__restrict__ gd,
-                                                  const Gather<BIGC> &ldc, RowSum<PT> &A)
+                                                  const Gather<false> &ldc, RowSum<PT> &A)
 {
     (
         [&] {
             if (PT::kWaves == 1 || part.template has<Ps>()) {
                 double2 u = A.get(Ps);
-                split_pair_chain<MT, BIGC, Ps>(D, t1, r1, lane, n, R, gd, ldc, u.x, u.y);
+                split_pair_chain<MT, Ps>(D, t1, r1, lane, n, R, gd, ldc, u.x, u.y);
                 A.put(Ps, u);
             }
         }(),
@@ -338,18 +338,12 @@ __device__ __forceinline__ void split_pairs_chain(std::integer_sequence<int, Ps.
 // walks them in it; tiles through the maps whose pair mask has every pair walk
 // them class by class (below).
 // ---------------------------------------------------------------------------
-#ifndef MC_FLAT_BATCH
-#define MC_FLAT_BATCH 16
-#endif
-
 template <int MT>
 struct FlatTile {
     static constexpr int NSING = MT * (MT - 1);
     static constexpr int NDBL =
         MT * reduced_slots(MT, 0, 0) + (MT * (MT - 1) / 2) * (MT >= 2 ? reduced_slots(MT, 0, 1) : 0);
     static constexpr int U = NSING + NDBL;
-    static constexpr int SB = U < MC_FLAT_BATCH ? U : MC_FLAT_BATCH;
-    static constexpr int NB = (U + SB - 1) / SB;
 };
 
 // double slot e (pair-major) -> pair and slot within the pair
@@ -878,13 +872,13 @@ __device__ __forceinline__ void group_fma(std::integer_sequence<int, Js...>, con
 // gathered.  Only where the anchor is impossible at the lane itself (rare)
 // is the member's own target read from the source.  A member impossible at
 // a lane has a zero amplitude there and takes any finite value.
-template <int MT, int FORM, bool BIGC, int B, class Src, int... Is>
+template <int MT, int FORM, int B, class Src, int... Is>
 __device__ __forceinline__ void class_batch(std::integer_sequence<int, Is...>, const Src &src,
                                             const int32_t (&tix)[MC_CLASS_BATCH], int32_t own_t,
                                             double2 own_c, const RowSq<MT> &R,
                                             const RunKeys<MT> &rk,
                                             const ClassConsts<MT, FORM> &k,
-                                            const Gather<BIGC> &ldc, double &ar, double &ai)
+                                            const Gather<false> &ldc, double &ar, double &ai)
 {
     constexpr ClassPlan<MT, FORM> cp = kClassPlan<MT, FORM>;
     constexpr int I0 = cp.bstart[B], I1 = cp.bstart[B + 1];
@@ -979,13 +973,13 @@ __device__ __forceinline__ void class_targets(std::integer_sequence<int, Is...>,
 // The whole stream.  One wavefront: batch B's block issues batch B+1's targets
 // (table loads in flight during B's gathers), then B's gathers and arithmetic;
 // several: each batch by itself.
-template <int MT, int FORM, bool BIGC, int B, class PT, class Src>
+template <int MT, int FORM, int B, class PT, class Src>
 __device__ __forceinline__ void class_batches(PT part, int32_t (&cur)[MC_CLASS_BATCH],
                                               int32_t (&nxt)[MC_CLASS_BATCH], const Src &src,
                                               int32_t own_t, double2 own_c, const RowSq<MT> &R,
                                               const RunKeys<MT> &rk,
                                               const ClassConsts<MT, FORM> &k,
-                                              const Gather<BIGC> &ldc, RowSum<PT> &A)
+                                              const Gather<false> &ldc, RowSum<PT> &A)
 {
     constexpr int NB = kClassPlan<MT, FORM>.nb;
     if constexpr (B < NB) {
@@ -998,27 +992,27 @@ __device__ __forceinline__ void class_batches(PT part, int32_t (&cur)[MC_CLASS_B
                 class_targets<MT, FORM, B + 1>(std::make_integer_sequence<int, MC_CLASS_BATCH>{},
                                                src, nxt);
             double2 u = A.get(B);
-            class_batch<MT, FORM, BIGC, B>(std::make_integer_sequence<int, MC_CLASS_BATCH>{}, src,
+            class_batch<MT, FORM, B>(std::make_integer_sequence<int, MC_CLASS_BATCH>{}, src,
                                            cur, own_t, own_c, R, rk, k, ldc, u.x, u.y);
             A.put(B, u);
         }
-        class_batches<MT, FORM, BIGC, B + 1>(part, nxt, cur, src, own_t, own_c, R, rk, k, ldc, A);
+        class_batches<MT, FORM, B + 1>(part, nxt, cur, src, own_t, own_c, R, rk, k, ldc, A);
     }
 }
 
 // `n`: the row's occupations; own_t: its index (negative past the end).
-template <int MT, int FORM, bool BIGC, class PT, class Src>
+template <int MT, int FORM, class PT, class Src>
 __device__ __forceinline__ void class_stream(PT part, const Src &src, int32_t own_t,
                                              double2 own_c, const int (&n)[MT],
                                              const RowSq<MT> &R, const ClassConsts<MT, FORM> &k,
-                                             const Gather<BIGC> &ldc, RowSum<PT> &A)
+                                             const Gather<false> &ldc, RowSum<PT> &A)
 {
     RunKeys<MT> rk{n, own_t >= 0 ? own_t + n[0] : -1, {}};
     run_key_shifts(std::make_integer_sequence<int, 2 * kMaxShift + 1>{}, rk.key, rk.at);
     int32_t ta[MC_CLASS_BATCH], tb[MC_CLASS_BATCH];
     if constexpr (PT::kWaves == 1)
         class_targets<MT, FORM, 0>(std::make_integer_sequence<int, MC_CLASS_BATCH>{}, src, ta);
-    class_batches<MT, FORM, BIGC, 0>(part, ta, tb, src, own_t, own_c, R, rk, k, ldc, A);
+    class_batches<MT, FORM, 0>(part, ta, tb, src, own_t, own_c, R, rk, k, ldc, A);
 }
 
 // Targets of a full tile through the tables: the tile's single-jump block
@@ -1044,7 +1038,7 @@ struct MapSlots {
 
 // One 64-row tile of H.C in the case-split form; MAP: true double jumps from
 // the reduced map, else chained.  `cf` holds the staged constants.
-template <int MT, typename OccT, bool BIGC, bool MAP, class PT>
+template <int MT, typename OccT, bool MAP, class PT>
 __device__ __forceinline__ double2 apply_tile_split(PT part, int64_t tile, int64_t D, int64_t cap,
                                                  const double *sq, const OccT *__restrict__ occ,
                                                  const int32_t *__restrict__ t1,
@@ -1067,7 +1061,7 @@ __device__ __forceinline__ double2 apply_tile_split(PT part, int64_t tile, int64
     double x[M];
 #pragma unroll
     for (int m = 0; m < M; ++m) x[m] = (double)n[m];
-    const Gather<BIGC> ldc(C, D);
+    const Gather<false> ldc(C, D);
     const double2 *DL = cf + split_dl_offset(M);
     const double2 *GI = cf + split_gi_offset(M);
     const double2 *HS = cf + split_hs_offset(M);
@@ -1112,7 +1106,7 @@ __device__ __forceinline__ double2 apply_tile_split(PT part, int64_t tile, int64
                 make_rsrc(t2r + off0, (uint32_t)(FlatTile<MT>::NDBL * kTile * 4));
             const MapSlots<MT, 0> src{r1, r2, lane};
             const ClassConsts<MT, 0> k{HS, GS, GD, x};
-            class_stream<MT, 0, BIGC>(part, src, live ? (int32_t)g : -2, cg, n, R, k, ldc, A);
+            class_stream<MT, 0>(part, src, live ? (int32_t)g : -2, cg, n, R, k, ldc, A);
             return A.total();
         }
     }
@@ -1165,10 +1159,10 @@ __device__ __forceinline__ double2 apply_tile_split(PT part, int64_t tile, int64
     if constexpr (MAP) {
         int64_t off0, off1;
         t2_block(t2_off, tile, cap, off0, off1);
-        split_pairs_map<MT, BIGC>(std::make_integer_sequence<int, P>{}, part, pmask + tile * W, t2r,
+        split_pairs_map<MT>(std::make_integer_sequence<int, P>{}, part, pmask + tile * W, t2r,
                                   off0, off1, lane, n, R, GD, ldc, A);
     } else {
-        split_pairs_chain<MT, BIGC>(std::make_integer_sequence<int, P>{}, part, D, t1, r1, lane, n, R, GD,
+        split_pairs_chain<MT>(std::make_integer_sequence<int, P>{}, part, D, t1, r1, lane, n, R, GD,
                                     ldc, A);
     }
     return A.total();
@@ -1180,7 +1174,7 @@ __device__ __forceinline__ double2 apply_tile_split(PT part, int64_t tile, int64
 // stream: the paper's sum over all its slots, reading only the anchors'
 // table columns and gathering each distinct target once; other tiles take
 // the per-pair path.
-template <int MT, typename OccT, bool BIGC, class PT>
+template <int MT, typename OccT, class PT>
 __device__ __forceinline__ double2 apply_tile_paper(PT part, int64_t tile, int64_t D, int64_t cap,
                                                  const double *sq, const OccT *__restrict__ occ,
                                                  const int32_t *__restrict__ t1,
@@ -1209,7 +1203,7 @@ __device__ __forceinline__ double2 apply_tile_paper(PT part, int64_t tile, int64
             int n[MT];
             RowSq<MT> R;
             load_row<MT, OccT>(occ, tile, lane, n, R, sq);
-            const Gather<BIGC> ldc(C, D);
+            const Gather<false> ldc(C, D);
             const double2 cg = ldc(live ? (int32_t)g : -1);
             // diagonal one-body part: sum_k h_kk n_k C_g
             double dr = 0.0, di = 0.0;
@@ -1228,11 +1222,11 @@ __device__ __forceinline__ double2 apply_tile_paper(PT part, int64_t tile, int64
                 make_rsrc(t1 + tile * NS * kTile, (uint32_t)(NS * kTile * 4)),
                 make_rsrc(t2 + off0, (uint32_t)(P * NS * kTile * 4)), lane};
             const ClassConsts<MT, 1> k{h, gp};
-            class_stream<MT, 1, BIGC>(part, src, live ? (int32_t)g : -2, cg, n, R, k, ldc, A);
+            class_stream<MT, 1>(part, src, live ? (int32_t)g : -2, cg, n, R, k, ldc, A);
             return A.total();
         }
     }
-    return apply_tile_t2<MT, OccT, BIGC>(part, tile, D, cap, sq, occ, t1, pmask, t2_off, t2, h, gp, C);
+    return apply_tile_t2<MT, OccT>(part, tile, D, cap, sq, occ, t1, pmask, t2_off, t2, h, gp, C);
 }
 
 // One tile through the tables in any kind; `ca` holds the case-split constants
@@ -1246,12 +1240,12 @@ __device__ __forceinline__ double2 apply_tile_tables(
     const double2 *__restrict__ cb, const double2 *__restrict__ C)
 {
     if constexpr (KIND == kPaperMap)
-        return apply_tile_paper<MT, OccT, false>(part, tile, D, cap, sq, occ, t1, pmask, t2_off, t2,
+        return apply_tile_paper<MT, OccT>(part, tile, D, cap, sq, occ, t1, pmask, t2_off, t2,
                                                  ca, cb, C);
     else if constexpr (KIND == kPaperChain)
-        return apply_tile_chained<MT, OccT, false>(part, tile, D, sq, occ, t1, ca, cb, C);
+        return apply_tile_chained<MT, OccT>(part, tile, D, sq, occ, t1, ca, cb, C);
     else
-        return apply_tile_split<MT, OccT, false, KIND == kSplitMap>(part, tile, D, cap, sq, occ, t1,
+        return apply_tile_split<MT, OccT, KIND == kSplitMap>(part, tile, D, cap, sq, occ, t1,
                                                                     pmask, t2_off, t2, ca, C);
 }
 
