@@ -4,10 +4,10 @@
 // A batch vector is the concatenation of the instances' coefficient vectors
 // (instance i at offset vec_off[i]).  The plan, built once into a caller
 // buffer, holds per-instance descriptors and staged coefficients, the
-// instances grouped by orbital count, and a chunk table for segmented
-// reductions.  Each group runs as one persistent kernel: its wavefronts walk
-// the group's (instance, tile) work list, so instances of 45 rows and of
-// 6*10^7 rows share the same launch.  Every call only enqueues kernels (no
+// instances grouped by orbital count and kind, and a chunk table for segmented
+// reductions.  Each group runs as one persistent kernel whose wavefronts walk
+// the group's (instance, tile) work list; an instance that fills the GPU with
+// four rows per lane has a launch of its own (mc_plan.h).  Every call only enqueues kernels (no
 // host synchronisation, no memset), so a sequence of calls can be captured
 // into a HIP graph and replayed.
 #include <stdlib.h>

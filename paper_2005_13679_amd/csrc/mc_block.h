@@ -1,4 +1,5 @@
-// H.C with no table, four rows per lane (3 <= M <= 8, large spaces).
+// H.C with no table, four rows per lane (large spaces; 4 <= M <= 8, and M = 3 in
+// the apply over non-zero constants only).
 //
 // One row per lane (mc_direct.h) gathers every configuration that H reaches
 // from that row: 131 at M = 5.  Rows that differ by particles moved between

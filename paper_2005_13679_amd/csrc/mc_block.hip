@@ -22,9 +22,9 @@ __global__ __launch_bounds__(256) void k_prep_block(int N, int M, int adjoint,
 
 // Bound: the L1's look-ups.  At M = 5 a wavefront's 296 gathers make 21
 // look-ups each (16 when they start on 64 bytes), 95 % of the kernel's cycles;
-// the vector ALU is at 72 % and FETCH_SIZE at 2.7 GB.  One item per lane, 256
+// the vector ALU is at 72 % and HBM reads are 5.4 GB (C is 1.1).  One item per lane, 256
 // consecutive items per block, blocks in XCD chunks as in the one-row kernel.
-// N=200, M=5 (70,058,751 rows): 5.50 ms with one row per lane, 3.44 ms so;
+// N=200, M=5 (70,058,751 rows): 5.50 ms with one row per lane, 3.44 so;
 // N=50, M=6: 0.56 -> 0.40; N=29, M=7: 0.46 -> 0.37; N=24, M=8: 1.60 -> 1.24;
 // N=40, M=8 (62,891,499 rows): 39.9 -> 26.9 ms.
 template <int MT>

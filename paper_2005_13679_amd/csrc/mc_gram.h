@@ -60,8 +60,6 @@
 
 namespace mc {
 
-// Column layout of the lift of L particles (L = 1: one column per orbital;
-// L = 2: one per unordered pair, lexicographic).
 // Columns per matrix block.  Two: the 4 x 4 products are over R and I of two
 // columns, so a block pair is one product, and up to ten columns that takes
 // fewer products than blocks of four (15 instead of 21 for 16 rows at M = 4, 6
@@ -70,6 +68,8 @@ namespace mc {
 // through the maps, 77 / 52 chained.
 __host__ __device__ constexpr int gram_block(int P) { return P <= 10 ? 2 : 4; }
 
+// Column layout of the lift of L particles (L = 1: one column per orbital;
+// L = 2: one per unordered pair, lexicographic).
 template <int MT, int L>
 struct Lift {
     static constexpr int P = L == 1 ? MT : MT * (MT + 1) / 2;   // columns

@@ -225,10 +225,11 @@ __device__ __forceinline__ int wave_in_block()
 // past the last whole group of 8K map to themselves).  Neighbouring tiles
 // gather from overlapping coefficient windows, so chunks let one XCD's L2
 // serve them, while interleaved chunks keep all XCDs in one region of the
-// index space, whose windows the memory-side cache then shares.  Measured at
-// N=200, M=5 against the identity (K = 1) and the full remap: K = 512 is
-// 3 % (reduced map), 1.5 % (paper map), 6 % (no table) and 15 % (chained)
-// faster than the identity; the full remap is 2-8 % slower than it.
+// index space, whose windows the memory-side cache then shares.  Measured, us
+// with K = 512 / identity (K = 1) / full remap: k_apply_block at N=200, M=5
+// 3,560 / 3,731 / 3,665, at N=100, M=5 226 / 240 / 225, at N=50, M=6
+// 399 / 401 / 382, at N=29, M=7 362 / 362 / 361, at N=24, M=8
+// 1,273 / 1,262 / 1,247; k_sparse_block on a ring, N=40, M=7, 528 / 693 / 450.
 #ifndef MC_XCD_REMAP
 #define MC_XCD_REMAP 0
 #endif
