@@ -22,7 +22,7 @@ __global__ __launch_bounds__(256) void k_prep_block(int N, int M, int adjoint,
 
 // Bound: the L1's look-ups.  At M = 5 a wavefront's 296 gathers make 21
 // look-ups each (16 when they start on 64 bytes), 95 % of the kernel's cycles;
-// the vector ALU is at 72 % and HBM reads are 5.4 GB (C is 1.1).  One item per lane, 256
+// the vector ALU is at 73 % and HBM reads are 5.4 GB (C is 1.1).  One item per lane, 256
 // consecutive items per block, blocks in XCD chunks as in the one-row kernel.
 // N=200, M=5 (70,058,751 rows): 5.50 ms with one row per lane, 3.44 so;
 // N=50, M=6: 0.56 -> 0.40; N=29, M=7: 0.46 -> 0.37; N=24, M=8: 1.60 -> 1.24;
@@ -75,9 +75,9 @@ bool block_fits(int32_t N, int32_t M, int64_t D)
 // M = 8, N = 19 (658 k) 415 / 414, N = 21 (1,184 k) 720 / 621.  Just past a whole
 // number of wavefronts per SIMD it can lose a few per cent above the line (M = 6,
 // N = 32, 436 k rows, 77 / 82; M = 5, N = 56, 48 / 49).
-// Three orbitals stay with the one-row kernel, which takes the root of a product
-// where this one multiplies two rounded roots: against 64 bits, N = 900, mean of
-// eight states, 2.77e-16 and 2.94e-16, for 18 and 15 us at N = 1,000.
+// Three orbitals stay with the one-row kernel, whose error is the smaller there:
+// against 64 bits, N = 900, mean of eight states, 2.77e-16 and 2.94e-16 (in each of
+// the eight), for 18 and 15 us at N = 1,000.
 bool block_serves(int32_t N, int32_t M, int64_t D)
 {
     return M >= 4 && block_fits(N, M, D) && D >= (M <= 6 ? 262144 : M == 7 ? 131072 : 786432);
